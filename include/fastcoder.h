@@ -73,7 +73,7 @@ const char* fc_status_string(fc_status s);
  *                (about 28.6 bytes per token, 36.6 from 2^26 tokens on).
  * Built by prefix doubling: suffixes are sorted by their first 3 tokens, then
  * by (rank of the first h tokens, rank of the h tokens after them) with h
- * doubling, each round an LSD radix sort restricted to still-tied suffixes.
+ * doubling, each round sorting the still-tied suffixes inside their groups.
  * Synchronises `stream` once per round (it reads the number of tied
  * suffixes).  Requires n < 2^32 - 1.  n == 0 is a no-op.
  */
@@ -88,8 +88,9 @@ fc_status fc_datastore_build(const uint16_t* tokens, uint64_t n, uint32_t* sa_ou
  * prefix_len[r] tokens, and left unresolved[r] of them tied.  The last
  * round leaves none tied, so the longest common prefix of two suffixes is
  * below prefix_len[rounds - 1] and, when rounds > 1, at least
- * prefix_len[rounds - 2].  sort_passes counts the radix passes run (a pass
- * per key byte that is not the same for every suffix).
+ * prefix_len[rounds - 2].  sort_passes counts the radix passes run over
+ * global memory: one per byte of round 0's key and of the rank pairs, and one
+ * per byte of a rank in a round that sorts groups too large for one workgroup.
  */
 #define FC_MAX_BUILD_ROUNDS 40
 typedef struct fc_build_stats {

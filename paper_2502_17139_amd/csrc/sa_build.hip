@@ -11,21 +11,22 @@
 //            past the end, so a suffix that ends first sorts first; all n
 //            suffixes are sorted.
 //   round r  (h = 3 * 2^(r-1)) only suffixes still tied with another are
-//            re-sorted, by key(i) = (rank[i], rank[i+h] + 1, or 0 past the
-//            end), where rank[i] is the suffix-array index at which i's group
-//            of equal h-token prefixes starts (Larsson and Sadakane's group
+//            re-sorted, each inside its group of equal h-token prefixes, by
+//            rank[i+h] + 1 (0 past the end), where rank[i] is the suffix-array
+//            index at which i's group starts (Larsson and Sadakane's group
 //            numbering).  Suffixes whose group becomes a singleton drop out.
 //   a suffix whose group becomes a singleton has its final index, rank[i],
 //   and sa[rank[i]] = i is written in that round (in sorted order, so at
 //   nearly sequential addresses).
 //
-// Each radix sort is a global digit histogram followed by one "onesweep"
-// pass per 8-bit digit (Adinets and Merrill 2022): a workgroup takes a tile
-// of 4,096 keys (its tile id from an atomic ticket, so tiles start in order),
-// ranks them stably inside the tile with wave ballots, publishes per-digit
-// tile counts and resolves its global offsets by decoupled look-back over the
-// earlier tiles, stages the tile in LDS in digit order, and writes it out in
-// runs.  Digit passes in which every key has the same digit are skipped.
+// Round 0 and the rank pairs below are sorted by a global digit histogram
+// followed by one "onesweep" pass per 8-bit digit (Adinets and Merrill 2022):
+// a workgroup takes a tile of 4,096 keys (its tile id from an atomic ticket,
+// so tiles start in order), ranks them stably inside the tile with wave
+// ballots, publishes per-digit tile counts and resolves its global offsets by
+// decoupled look-back over the earlier tiles, stages the tile in LDS in digit
+// order, and writes it out in runs.  The later rounds sort inside the groups
+// (see "sorting inside groups").
 //
 // After each sort, head flags of the new and old groups are turned into
 // group starts with a three-phase scan (tile partials, one-workgroup scan of
@@ -59,6 +60,8 @@ constexpr int kScanThreads = 1024;
 constexpr int kMaxPasses = 1024;  // ticket counters per build
 constexpr int kMaxRounds = 40;
 constexpr int kHistBlocks = 2048;
+constexpr uint32_t kBigKeysBlocks = 2048;
+constexpr uint32_t kBigPassBlocks = 1024;  // resident: four tiles per CU
 constexpr uint32_t kSpinLimit = 1u << 22;
 constexpr int kLookWindow = 2;  // earlier tiles examined per look-back step (with the counts
                                 // published early, wider windows only add loads)
@@ -72,30 +75,52 @@ __device__ __forceinline__ uint64_t pack_status(uint32_t epoch, uint64_t flag, u
   return ((uint64_t)epoch << 48) | flag | count;
 }
 
-// ---------------------------------------------------------------- keys ----
-
-__global__ void __launch_bounds__(256) k_init_keys(const uint16_t* __restrict__ tok, uint32_t n, int tb,
-                                                     uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-  uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  uint64_t a = (uint64_t)tok[i] + 1;
-  uint64_t b = (i + 1 < n) ? (uint64_t)tok[i + 1] + 1 : 0;
-  uint64_t c = (i + 2 < n) ? (uint64_t)tok[i + 2] + 1 : 0;
-  keys[i] = (a << (2 * tb)) | (b << tb) | c;
-  vals[i] = i;
+// A value that is the same in every lane, in a scalar register (what is read
+// from LDS otherwise counts as different per lane, and so does all that
+// follows from it).
+__device__ __forceinline__ uint32_t uniform(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 
-// The high half of each key (the suffix's own rank) was written in place by
-// the previous round's k_seg_apply, in this round's order, so only the rank
-// h positions on is gathered.
-__global__ void __launch_bounds__(256) k_pair_keys(const uint32_t* __restrict__ vals, uint32_t U,
-                                                     const uint32_t* __restrict__ rank, uint32_t n, uint64_t h,
-                                                     uint64_t* __restrict__ keys) {
-  uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= U) return;
-  uint32_t i = vals[r];
-  uint64_t lo = ((uint64_t)i + h < n) ? (uint64_t)rank[i + h] + 1 : 0;
-  keys[r] |= lo;
+// ---------------------------------------------------------------- keys ----
+
+// Digit histogram of one workgroup in LDS, added to the global one at the end.
+struct LdsHist {
+  uint32_t (*s)[kRadix];
+  __device__ void zero() const {
+    for (int i = threadIdx.x; i < kMaxDigits * kRadix; i += blockDim.x) (&s[0][0])[i] = 0;
+    __syncthreads();
+  }
+  __device__ void add(uint64_t key, int digits) const {
+    for (int d = 0; d < digits; ++d) atomicAdd(&s[d][(uint32_t)(key >> (8 * d)) & 0xFF], 1u);
+  }
+  __device__ void flush(int digits, uint32_t* __restrict__ hist) const {
+    __syncthreads();
+    for (int i = threadIdx.x; i < digits * kRadix; i += blockDim.x) {
+      const uint32_t v = (&s[0][0])[i];
+      if (v) atomicAdd(&hist[i], v);
+    }
+  }
+};
+
+// Round 0's keys and their digit histogram in one pass (a histogram pass of
+// its own reads the 8-byte keys once more: 3.5 of 7.6 ms at 1B suffixes).
+__global__ void __launch_bounds__(256) k_init_keys(const uint16_t* __restrict__ tok, uint32_t n, int tb,
+                                                     int digits, uint64_t* __restrict__ keys,
+                                                     uint32_t* __restrict__ vals, uint32_t* __restrict__ hist) {
+  __shared__ uint32_t s_hist[kMaxDigits][kRadix];
+  const LdsHist lh{s_hist};
+  lh.zero();
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t a = (uint64_t)tok[i] + 1;
+    const uint64_t b = (i + 1 < n) ? (uint64_t)tok[i + 1] + 1 : 0;
+    const uint64_t c = (i + 2 < n) ? (uint64_t)tok[i + 2] + 1 : 0;
+    const uint64_t key = (a << (2 * tb)) | (b << tb) | c;
+    keys[i] = key;
+    vals[i] = (uint32_t)i;
+    lh.add(key, digits);
+  }
+  lh.flush(digits, hist);
 }
 
 // Batched build: position i belongs to the segment r with off[r] <= i <
@@ -109,34 +134,35 @@ __device__ __forceinline__ uint32_t segment_of(const uint64_t* __restrict__ off,
   return lo;
 }
 
-// Round 0 of a batched build: key = (segment, first two tokens as token+1,
-// 0 past the segment's end), so suffixes of different segments never share
-// a group and every suffix ends at its own segment's end.
+// Round 0 of a batched build: key = (segment, first `ntok` tokens as token+1
+// in tb bits, 0 past the segment's end), so suffixes of different segments
+// never share a group and every suffix ends at its own segment's end.
 __global__ void __launch_bounds__(256) k_init_keys_seg(const uint16_t* __restrict__ tok, uint32_t n,
-                                                         const uint64_t* __restrict__ off, uint32_t R,
-                                                         uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                         uint32_t* __restrict__ end_of) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t r = segment_of(off, R, i);
-  const uint32_t end = (uint32_t)off[r + 1];
-  const uint64_t a = (uint64_t)tok[i] + 1;
-  const uint64_t b = (i + 1 < end) ? (uint64_t)tok[i + 1] + 1 : 0;
-  keys[i] = ((uint64_t)r << 34) | (a << 17) | b;
-  vals[i] = i;
-  end_of[i] = end;
+                                                         const uint64_t* __restrict__ off, uint32_t R, int tb,
+                                                         int ntok, int digits, uint64_t* __restrict__ keys,
+                                                         uint32_t* __restrict__ vals, uint32_t* __restrict__ hist) {
+  __shared__ uint32_t s_hist[kMaxDigits][kRadix];
+  const LdsHist lh{s_hist};
+  lh.zero();
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint32_t r = segment_of(off, R, i);
+    const uint64_t end = off[r + 1];
+    uint64_t key = r;
+    for (int x = 0; x < ntok; ++x) key = (key << tb) | (i + x < end ? (uint64_t)tok[i + x] + 1 : 0ull);
+    keys[i] = key;
+    vals[i] = (uint32_t)i;
+    lh.add(key, digits);
+  }
+  lh.flush(digits, hist);
 }
 
-__global__ void __launch_bounds__(256) k_pair_keys_seg(const uint32_t* __restrict__ vals, uint32_t U,
-                                                         const uint32_t* __restrict__ rank,
-                                                         const uint32_t* __restrict__ end_of, uint64_t h,
-                                                         uint32_t sb, uint64_t* __restrict__ keys) {
+// One bit per position that starts a segment (bits zeroed before).
+__global__ void __launch_bounds__(256) k_seg_starts(const uint64_t* __restrict__ off, uint32_t R, uint32_t n,
+                                                      uint32_t* __restrict__ bits) {
   const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= U) return;
-  const uint32_t i = vals[r];
-  const uint64_t hi = rank[i];
-  const uint64_t lo = ((uint64_t)i + h < end_of[i]) ? (uint64_t)rank[i + h] + 1 : 0;
-  keys[r] = (hi << sb) | lo;
+  if (r >= R) return;
+  const uint64_t i = off[r];
+  if (i < n) atomicOr(&bits[i >> 5], 1u << (i & 31));
 }
 
 // Segment-major suffix array -> positions local to each segment.
@@ -294,14 +320,21 @@ __global__ void __launch_bounds__(256) k_ext_fix(const uint32_t* __restrict__ do
 // positions in the final array's order, so the rank of whatever follows the
 // first h tokens can be either kind.
 __global__ void __launch_bounds__(256) k_init_keys_ext(const uint16_t* __restrict__ tok, uint32_t o, uint64_t n,
-                                                         const uint32_t* __restrict__ ins, int two,
-                                                         uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-  const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= o) return;
-  const uint64_t a = (uint64_t)tok[p] + 1;
-  const uint64_t b = ((uint64_t)p + 1 < n) ? (uint64_t)tok[p + 1] + 1 : 0;
-  keys[p] = two ? (((uint64_t)ins[p] << 34) | (a << 17) | b) : (((uint64_t)ins[p] << 17) | a);
-  vals[p] = p;
+                                                         const uint32_t* __restrict__ ins, int two, int digits,
+                                                         uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                         uint32_t* __restrict__ hist) {
+  __shared__ uint32_t s_hist[kMaxDigits][kRadix];
+  const LdsHist lh{s_hist};
+  lh.zero();
+  for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < o; p += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t a = (uint64_t)tok[p] + 1;
+    const uint64_t b = (p + 1 < n) ? (uint64_t)tok[p + 1] + 1 : 0;
+    const uint64_t key = two ? (((uint64_t)ins[p] << 34) | (a << 17) | b) : (((uint64_t)ins[p] << 17) | a);
+    keys[p] = key;
+    vals[p] = (uint32_t)p;
+    lh.add(key, digits);
+  }
+  lh.flush(digits, hist);
 }
 
 __global__ void __launch_bounds__(256) k_ins_sorted(const uint64_t* __restrict__ keys, uint32_t o, int shift,
@@ -320,27 +353,35 @@ __device__ __forceinline__ uint32_t count_le(const uint32_t* __restrict__ s, uin
   return a;
 }
 
-__global__ void __launch_bounds__(256) k_pair_keys_ext(const uint32_t* __restrict__ vals, uint32_t U,
-                                                         const uint32_t* __restrict__ rank,
-                                                         const uint32_t* __restrict__ ins,
-                                                         const uint32_t* __restrict__ isa,
-                                                         const uint32_t* __restrict__ ins_sorted, uint32_t o,
-                                                         uint64_t n, uint64_t h, uint32_t sb,
-                                                         uint64_t* __restrict__ keys) {
-  const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= U) return;
-  const uint32_t p = vals[r];
-  const uint64_t z = (uint64_t)p + h;
-  uint64_t lo;
-  if (z < o) {
-    lo = (uint64_t)rank[z] + ins[z] + 1;
-  } else if (z < n) {
-    const uint32_t j = isa[z - o];
-    lo = (uint64_t)j + count_le(ins_sorted, o, j) + 1;
-  } else {
-    lo = 0;
+// The second half of a round's key: what the label of the position h on is.
+enum class Mode { kPlain, kBatched, kExtend };
+struct NextRank {
+  const uint32_t* rank;
+  const uint32_t* seg_bits;    // batched: a bit per position that starts a segment
+  const uint32_t* ins;         // extension: per new position
+  const uint32_t* isa;         // extension: inverse of the old suffix array
+  const uint32_t* ins_sorted;  // extension
+  uint64_t n;                  // positions (extension: of the whole text)
+  uint64_t h;
+  uint32_t o;                  // extension: new positions
+};
+
+// Batched build: a suffix that is still tied on its first h tokens has all of
+// them inside its segment (one that ends earlier holds its end mark at a
+// place no other suffix of the segment has it), so position i + h is at most
+// the segment's end, and it is the end where it starts another segment.
+template <Mode M>
+__device__ __forceinline__ uint32_t next_rank(const NextRank& a, uint32_t i) {
+  const uint64_t z = (uint64_t)i + a.h;
+  if (M == Mode::kExtend) {
+    if (z < a.o) return a.rank[z] + a.ins[z] + 1u;
+    if (z >= a.n) return 0u;
+    const uint32_t j = a.isa[z - a.o];
+    return j + count_le(a.ins_sorted, a.o, j) + 1u;
   }
-  keys[r] = ((uint64_t)rank[p] << sb) | lo;
+  if (z >= a.n) return 0u;
+  if (M == Mode::kBatched && ((a.seg_bits[z >> 5] >> (z & 31)) & 1u)) return 0u;
+  return a.rank[z] + 1u;
 }
 
 // merge: new suffix p goes to ins(p) + rank[p], old suffix at index j to
@@ -471,22 +512,61 @@ __global__ void __launch_bounds__(256) k_hist(const uint64_t* __restrict__ keys,
   }
 }
 
-// One workgroup of 256 threads: digit offsets (exclusive scan per digit) and
-// the "trivial" flag of each digit (all keys share it).
-__global__ void __launch_bounds__(256) k_hist_scan(const uint32_t* __restrict__ hist, uint32_t U, int digits,
-                                                     uint32_t* __restrict__ offsets, uint32_t* __restrict__ trivial) {
+// One workgroup of 256 threads per digit: its offsets (exclusive scan).
+__global__ void __launch_bounds__(256) k_hist_scan(const uint32_t* __restrict__ hist,
+                                                     uint32_t* __restrict__ offsets) {
   __shared__ uint32_t scratch[8];
-  for (int d = 0; d < digits; ++d) {
-    uint32_t v = hist[d * kRadix + threadIdx.x];
-    uint32_t total;
-    uint32_t ex = fc::block_excl_sum<uint32_t>(v, scratch, &total);
-    offsets[d * kRadix + threadIdx.x] = ex;
-    uint32_t any_full = fc::block_sum<uint32_t>(v == U ? 1u : 0u, scratch);
-    if (threadIdx.x == 0) trivial[d] = any_full ? 1u : 0u;
-  }
+  const uint32_t i = blockIdx.x * kRadix + threadIdx.x;
+  offsets[i] = fc::block_excl_sum<uint32_t>(hist[i], scratch, nullptr);
 }
 
 // ------------------------------------------------------------- onesweep ---
+
+// Decoupled look-back of digit t over tiles p, p - 1, .. p_end: the elements
+// of the digit in those tiles, kLookWindow tiles per step: their status words
+// are loaded together (for the block, a contiguous run per tile), then taken
+// nearest first - aggregates are added until an inclusive prefix ends the
+// walk; a tile that has published nothing yet makes the walk wait and reload
+// from there.  One round trip then covers as many tiles as the window
+// instead of one.  The wait is bounded: giving up sets *err.
+__device__ __forceinline__ uint64_t look_back(const uint64_t* status, int64_t p, int64_t p_end, uint32_t t,
+                                              uint32_t epoch, uint32_t* err) {
+  uint64_t excl = 0;
+  uint32_t spins = 0;
+  bool done = p < p_end;
+  while (!done) {
+    uint64_t sw[kLookWindow];
+#pragma unroll
+    for (int i = 0; i < kLookWindow; ++i)
+      sw[i] = p - i >= p_end ? __hip_atomic_load(status + (uint64_t)(p - i) * kRadix + t, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT)
+                             : pack_status(epoch, kFlagInc, 0);  // before the first tile: an empty prefix
+    int taken = 0;
+    bool stalled = false;
+#pragma unroll
+    for (int i = 0; i < kLookWindow; ++i) {
+      if (done || stalled) continue;
+      const uint64_t s = sw[i];
+      const uint64_t fl = s & kFlagMask;
+      if ((uint32_t)(s >> 48) != epoch || fl == 0) {
+        stalled = true;
+        continue;
+      }
+      excl += s & kCountMask;
+      ++taken;
+      if (fl == kFlagInc) done = true;
+    }
+    p -= taken;
+    if (stalled && !done) {
+      if (++spins > kSpinLimit) {
+        atomicOr(err, 1u);
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  return excl;
+}
 
 // kVals false: keys only (vin and vout unused), compiled for four waves per
 // SIMD, so four tiles share a CU.
@@ -510,12 +590,12 @@ __global__ void __launch_bounds__(kSortThreads, kVals ? 1 : 4) k_onesweep(const 
   __shared__ uint32_t s_vals[kVals ? kSortTile : 1];
 
   const int tid = threadIdx.x;
-  const int w = tid / fc::kWave;
+  const int w = (int)uniform((uint32_t)tid / fc::kWave);
   const int lane = fc::lane_id();
   for (int i = tid; i < (kSortThreads / fc::kWave) * kRadix; i += kSortThreads) (&s_wcnt[0][0])[i] = 0;
   if (tid == 0) s_tile = atomicAdd(ticket, 1u);
   __syncthreads();
-  const uint32_t tile = s_tile;
+  const uint32_t tile = uniform(s_tile);
   const uint64_t base = (uint64_t)tile * kSortTile;
   const uint32_t nvalid = (uint32_t)((U - base) < (uint64_t)kSortTile ? (U - base) : (uint64_t)kSortTile);
 
@@ -580,49 +660,7 @@ __global__ void __launch_bounds__(kSortThreads, kVals ? 1 : 4) k_onesweep(const 
     }
   }
 
-  // Decoupled look-back for this digit's global offset, kLookWindow earlier
-  // tiles per step: their status words are loaded together (for the block,
-  // a contiguous run per tile), then taken nearest first - aggregates are
-  // added until an inclusive prefix ends the walk; a tile that has published
-  // nothing yet makes the walk wait and reload from there.  One round trip
-  // then covers as many tiles as the window instead of one.
-  uint64_t excl = 0;
-  if (tile > 0) {
-    int64_t p = (int64_t)tile - 1;  // nearest tile not yet taken
-    uint32_t spins = 0;
-    bool done = false;
-    while (!done) {
-      uint64_t sw[kLookWindow];
-#pragma unroll
-      for (int i = 0; i < kLookWindow; ++i)
-        sw[i] = p - i >= 0 ? __hip_atomic_load(status + (uint64_t)(p - i) * kRadix + t, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT)
-                           : pack_status(epoch, kFlagInc, 0);  // before tile 0: an empty prefix
-      int taken = 0;
-      bool stalled = false;
-#pragma unroll
-      for (int i = 0; i < kLookWindow; ++i) {
-        if (done || stalled) continue;
-        const uint64_t s = sw[i];
-        const uint64_t fl = s & kFlagMask;
-        if ((uint32_t)(s >> 48) != epoch || fl == 0) {
-          stalled = true;
-          continue;
-        }
-        excl += s & kCountMask;
-        ++taken;
-        if (fl == kFlagInc) done = true;
-      }
-      p -= taken;
-      if (stalled && !done) {
-        if (++spins > kSpinLimit) {
-          atomicOr(err, 1u);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
-  }
+  const uint64_t excl = look_back(status, (int64_t)tile - 1, 0, t, epoch, err);
   if (tile > 0)
     __hip_atomic_store(mine, pack_status(epoch, kFlagInc, excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   s_gbase[t] = digit_base[t] + (uint32_t)excl;
@@ -639,32 +677,535 @@ __global__ void __launch_bounds__(kSortThreads, kVals ? 1 : 4) k_onesweep(const 
   }
 }
 
+// ------------------------------------------------- sorting inside groups ---
+//
+// Rounds after the first.  The still-tied suffixes lie in a list (grp, val):
+// group after group, grp = the group's first suffix-array index, so only the
+// order inside each group is open, by lo = the rank h positions on.  Sorting
+// (grp, lo) pairs globally moved every 12-byte element through eight digit
+// passes; instead
+//  - k_sort_small sorts the groups of at most kWin elements, a window of
+//    whole groups per workgroup, inside LDS: lo is gathered, and the list
+//    read and written, once;
+//  - the larger groups (few, but up to half of the elements) go through
+//    digit passes over lo alone (8-byte elements), every group for itself:
+//    k_big_plan sizes them and cuts them into tiles, k_big_keys gathers lo
+//    and counts each group's digits, k_big_pass is a onesweep pass whose
+//    look-back ends at the group's first tile.
+// At 1B suffixes this replaced 48 passes over (8-byte key, suffix) elements
+// and their key and histogram kernels, 159 ms of a 305 ms build, by 77 ms
+// (small groups 28, keys of the large ones 25, their passes 24); 10M suffixes
+// 3.60 -> 2.83 ms, 64 repositories in one call 8.43 -> 6.04 ms.  The line
+// between the two lies at what one workgroup's LDS holds next to the groups
+// that start before it: about a third of the elements are in larger groups
+// in the first such round of a 10M store, two thirds of a 1B store's.
+
+constexpr int kWin = 2048;          // list positions whose groups a workgroup sorts
+constexpr int kCap = 2 * kWin;      // a window's last group may end this far
+constexpr int kSmallThreads = 256;
+constexpr int kSmallItems = kCap / kSmallThreads;
+constexpr uint32_t kCountMax = 48;  // groups up to this size are ranked by comparing all pairs
+constexpr int kMaxLoDigits = 4;
+constexpr uint32_t kNone = 0xFFFFFFFFu;
+
+// Stable rank of each wave's elements inside their digit: rk[j] = elements of
+// the wave with the same digit before element j of this lane; wcnt counts
+// the wave's digits (zeroed before).
+__device__ __forceinline__ uint32_t wave_digit_rank(uint32_t d, bool valid, uint64_t lt, uint16_t* wcnt) {
+  uint64_t peers = fc::ballot(valid);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const bool bit = (d >> b) & 1u;
+    const uint64_t ones = fc::ballot(valid && bit);
+    peers &= bit ? ones : ~ones;
+  }
+  const uint32_t below = (uint32_t)__popcll(peers & lt);
+  const uint32_t old = wcnt[d];
+  if (valid && below == 0) wcnt[d] = (uint16_t)(old + (uint32_t)__popcll(peers));
+  __builtin_amdgcn_sched_barrier(0);  // one element after another: interleaved, their masks spill
+  return old + below;
+}
+
+// Window b takes the groups that start at list positions [b kWin, (b+1) kWin).
+// All but the last one end inside the window or right after it; the last one
+// is small if it ends within kWin of its start, else it is registered as
+// large.  first_head[b] = where the window's first group starts (kNone: one
+// group covers it).  Small groups are one contiguous run of positions: those
+// of up to kCountMax elements are ranked by comparing all pairs (a group's
+// lanes read the same LDS words), the others by an LDS radix sort over lo and
+// then the group.  `val` is reordered in place: a position is read and
+// written by the one workgroup that owns its group.
+template <Mode M>
+__global__ void __launch_bounds__(kSmallThreads, 4) k_sort_small(const uint32_t* __restrict__ grp, uint32_t* val,
+                                                              uint32_t* __restrict__ lo,
+                                                              const uint32_t* __restrict__ u_dev, NextRank nr,
+                                                              int lo_digits, uint32_t* __restrict__ first_head,
+                                                              uint32_t* __restrict__ big_start,
+                                                              uint32_t* __restrict__ big_count) {
+  constexpr int kWaves = kSmallThreads / fc::kWave;
+  constexpr int kPer = kSmallItems * fc::kWave;  // positions per wave
+  __shared__ uint32_t s_a[kCap], s_b[kCap];
+  // a tied group has two elements or more
+  __shared__ uint16_t s_head[kWin / 2 + 1];  // start of each small group (and the end), relative to the window
+  __shared__ uint16_t s_slot[kWin / 2];      // first radix slot of each group that goes to the radix sort
+  __shared__ uint16_t s_delta[kCap / kCountMax + 1];  // per radix group: list position minus radix slot
+  __shared__ uint8_t s_rg[kWin / 2];         // its number among those
+  __shared__ uint16_t s_wcnt[kWaves][kRadix];
+  __shared__ uint16_t s_dstart[kRadix];
+  __shared__ uint32_t s_scan[kWaves + 1];
+  __shared__ uint32_t s_first[kWaves], s_heads[kWaves];
+  uint32_t* const s_last = s_scan;  // read before the first scan; with it the LDS fits four workgroups per CU
+  static_assert(kCap / (kCountMax + 1) < 256, "radix groups are numbered in 8 bits");
+
+  const uint32_t U = *u_dev;
+  const uint32_t w0 = blockIdx.x * kWin;
+  if (w0 >= U) return;
+  const int tid = (int)threadIdx.x, w = (int)uniform((uint32_t)tid / fc::kWave);
+  const uint32_t lane = (uint32_t)fc::lane_id();
+  const uint32_t room = U - w0;  // list positions from the window on
+  const uint32_t wbase = (uint32_t)(w * kPer);
+
+  // group starts among this wave's positions
+  uint64_t hm[kSmallItems];
+  uint32_t first = kNone, last = kNone;
+  {
+    uint32_t g[kSmallItems];
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+      const uint32_t x = wbase + (uint32_t)(j * fc::kWave) + lane;
+      g[j] = x < room ? grp[(uint64_t)w0 + x] : 0u;
+    }
+    uint32_t carry = (uint64_t)w0 + wbase > 0 && wbase < room ? grp[(uint64_t)w0 + wbase - 1] : 0u;
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+      const uint32_t x0 = wbase + (uint32_t)(j * fc::kWave);
+      const uint32_t x = x0 + lane;
+      const uint32_t before = fc::wave_shr1(g[j], carry);
+      carry = (uint32_t)__builtin_amdgcn_readlane((int)g[j], fc::kWave - 1);
+      hm[j] = fc::ballot(x < room && (w0 + x == 0 || g[j] != before));
+      if (hm[j]) {
+        if (first == kNone) first = x0 + (uint32_t)__builtin_ctzll(hm[j]);
+        last = x0 + 63u - (uint32_t)__builtin_clzll(hm[j]);
+      }
+    }
+  }
+  if (lane == 0) {
+    s_first[w] = first;
+    s_last[w] = last;
+  }
+  __syncthreads();
+  static_assert(kWaves == 4, "two waves hold the window, two what follows");
+  // the same for every lane: kept in scalar registers
+  const uint32_t F = uniform(s_first[0] != kNone ? s_first[0] : s_first[1]);
+  const uint32_t Lh = uniform(s_last[1] != kNone ? s_last[1] : s_last[0]);
+  uint32_t E = uniform(s_first[2] != kNone ? s_first[2] : s_first[3]);
+  if (E == kNone && room < (uint32_t)kCap) E = room;  // the list ends with the group
+  if (E != kNone && E > room) E = room;
+  if (tid == 0) first_head[blockIdx.x] = F == kNone ? kNone : w0 + F;
+  if (F == kNone) return;
+  const bool big = E == kNone || E - Lh > (uint32_t)kWin;
+  if (big && tid == 0) big_start[atomicAdd(big_count, 1u)] = w0 + Lh;
+  const uint32_t end = big ? Lh : E;  // the small groups: positions [F, end) of the window
+  if (F >= end) return;
+
+  // number the groups, gather lo
+  uint32_t nh = 0;
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    const uint32_t x0 = wbase + (uint32_t)(j * fc::kWave);
+    // heads below `end` (the head at `end`, if any, opens the next window's or the large group)
+    if (x0 >= end) hm[j] = 0;
+    else if (end - x0 < 64) hm[j] &= (1ull << (end - x0)) - 1;
+    nh += (uint32_t)__popcll(hm[j]);
+  }
+  if (lane == 0) s_heads[w] = nh;
+  uint32_t v[kSmallItems], key[kSmallItems];
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    const uint32_t x = wbase + (uint32_t)(j * fc::kWave) + lane;
+    v[j] = x >= F && x < end ? val[(uint64_t)w0 + x] : 0u;
+  }
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    const uint32_t x = wbase + (uint32_t)(j * fc::kWave) + lane;
+    key[j] = x >= F && x < end ? next_rank<M>(nr, v[j]) : 0u;
+  }
+  __syncthreads();
+  uint32_t gi0 = 0, groups = 0;
+#pragma unroll
+  for (int u = 0; u < kWaves; ++u) {
+    const uint32_t x = uniform(s_heads[u]);
+    if (u < w) gi0 += x;
+    groups += x;
+  }
+  const uint64_t le = lane == 63 ? ~0ull : (2ull << lane) - 1;
+  uint16_t gi[kSmallItems];
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    const uint32_t x = wbase + (uint32_t)(j * fc::kWave) + lane;
+    gi[j] = (uint16_t)(gi0 + (uint32_t)__popcll(hm[j] & le) - 1u);  // positions before F: no use is made of it
+    if ((hm[j] >> lane) & 1) s_head[gi[j]] = (uint16_t)x;
+    gi0 += (uint32_t)__popcll(hm[j]);
+    if (x >= F && x < end) s_a[x] = key[j];
+  }
+  if (tid == 0) s_head[groups] = (uint16_t)end;
+  __syncthreads();
+
+  // groups of up to kCountMax: every element counts those before it
+  uint32_t have_large = 0;
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    const uint32_t x = wbase + (uint32_t)(j * fc::kWave) + lane;
+    const bool valid = x >= F && x < end;
+    uint32_t gs = 0, ge = 0;
+    if (valid) {
+      gs = s_head[gi[j]];
+      ge = s_head[gi[j] + 1];
+    }
+    const bool large = ge - gs > kCountMax;
+    have_large |= large ? 1u : 0u;
+    if (valid && !large) {
+      uint32_t c = gs;
+#pragma clang loop unroll(disable) vectorize(disable)
+      for (uint32_t y = gs; y < ge; ++y) {
+        const uint32_t k2 = s_a[y];
+        c += (k2 < key[j] || (k2 == key[j] && y < x)) ? 1u : 0u;
+      }
+      lo[(uint64_t)w0 + c] = key[j];
+      val[(uint64_t)w0 + c] = v[j];
+    }
+  }
+  if (!__syncthreads_or((int)have_large)) return;
+
+  // the other groups: numbered, and packed into slots [0, nl)
+  uint32_t nl, nrg;
+  {
+    const uint32_t per = (groups + kSmallThreads - 1) / kSmallThreads;
+    const uint32_t a = (uint32_t)tid * per, e = a + per < groups ? a + per : groups;
+    uint32_t sum = 0;
+    for (uint32_t x = a; x < e; ++x) {
+      const uint32_t size = (uint32_t)s_head[x + 1] - s_head[x];
+      if (size > kCountMax) sum += (1u << 16) | size;
+    }
+    uint32_t total;
+    uint32_t run = fc::block_excl_sum<uint32_t>(sum, s_scan, &total);
+    for (uint32_t x = a; x < e; ++x) {
+      const uint32_t size = (uint32_t)s_head[x + 1] - s_head[x];
+      if (size > kCountMax) {
+        s_slot[x] = (uint16_t)(run & 0xFFFF);
+        s_rg[x] = (uint8_t)(run >> 16);
+        s_delta[run >> 16] = (uint16_t)(s_head[x] - (run & 0xFFFF));
+        run += (1u << 16) | size;
+      }
+    }
+    nl = uniform(total & 0xFFFF);
+    nrg = uniform(total >> 16);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    const uint32_t x = wbase + (uint32_t)(j * fc::kWave) + lane;
+    if (x >= F && x < end) {
+      const uint32_t gs = s_head[gi[j]];
+      if ((uint32_t)s_head[gi[j] + 1] - gs > kCountMax) {
+        const uint32_t slot = s_slot[gi[j]] + (x - gs);
+        s_a[slot] = key[j];
+        s_b[slot] = ((uint32_t)s_rg[gi[j]] << 16) | x;
+      }
+    }
+  }
+  const int items = (int)((nl + kSmallThreads - 1) / kSmallThreads);  // per lane; a wave's elements are contiguous
+  const uint32_t cbase = (uint32_t)(w * items * fc::kWave);
+  const uint64_t lt = fc::lanemask_lt();
+  const int passes = lo_digits + (nrg > 1 ? 1 : 0);
+  uint32_t a[kSmallItems], b[kSmallItems], rk[kSmallItems];
+  for (int ps = 0; ps < passes; ++ps) {
+    for (int i = tid; i < kWaves * kRadix; i += kSmallThreads) (&s_wcnt[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+      const uint32_t i = cbase + (uint32_t)(j * fc::kWave) + lane;
+      const bool valid = j < items && i < nl;
+      a[j] = valid ? s_a[i] : 0u;
+      b[j] = valid ? s_b[i] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+      if (j < items) {
+        const uint32_t d = ps < lo_digits ? (a[j] >> (8 * ps)) & 0xFF : b[j] >> 16;
+        rk[j] = wave_digit_rank(d, cbase + (uint32_t)(j * fc::kWave) + lane < nl, lt, s_wcnt[w]) | (d << 16);
+      }
+    }
+    __syncthreads();
+    uint32_t total = 0;
+#pragma unroll
+    for (int u = 0; u < kWaves; ++u) {
+      const uint32_t c = s_wcnt[u][tid];
+      s_wcnt[u][tid] = (uint16_t)total;
+      total += c;
+    }
+    s_dstart[tid] = (uint16_t)fc::block_excl_sum<uint32_t>(total, s_scan, nullptr);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+      const uint32_t i = cbase + (uint32_t)(j * fc::kWave) + lane;
+      if (j < items && i < nl) {
+        const uint32_t d = rk[j] >> 16;
+        const uint32_t pos = s_dstart[d] + s_wcnt[w][d] + (rk[j] & 0xFFFF);
+        s_a[pos] = a[j];
+        s_b[pos] = b[j];
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    const uint32_t i = (uint32_t)(j * kSmallThreads + tid);
+    if (i < nl) v[j] = val[(uint64_t)w0 + (s_b[i] & 0xFFFF)];
+  }
+  __syncthreads();  // every element is read before its place is written
+#pragma unroll
+  for (int j = 0; j < kSmallItems; ++j) {
+    const uint32_t i = (uint32_t)(j * kSmallThreads + tid);
+    if (i < nl) {
+      const uint64_t p = (uint64_t)w0 + i + s_delta[s_b[i] >> 16];
+      lo[p] = s_a[i];
+      val[p] = v[j];
+    }
+  }
+}
+
+// The large groups of a round.
+struct BigWs {
+  uint32_t* first_head;  // per window
+  uint32_t* start;       // per large group: first list position
+  uint32_t* size;
+  uint32_t* tile0;       // its first tile
+  uint32_t* tile_group;  // per tile: its group
+  uint32_t* hist;        // [group][digit place][256]
+  uint32_t* count;       // [0] groups, [1] tiles, [2..2+kMaxLoDigits) tickets of the passes
+};
+constexpr int kBigCounts = 2 + kMaxLoDigits;
+
+// One wave per large group: its end is the first group start of a later
+// window (or the list's end); its tiles are numbered consecutively and its
+// histogram cleared.
+__global__ void __launch_bounds__(256) k_big_plan(BigWs g, uint32_t U, int lo_digits) {
+  const uint32_t groups = g.count[0];
+  const uint32_t windows = (U + kWin - 1) / kWin;
+  const uint32_t lane = (uint32_t)fc::lane_id();
+  const uint32_t waves = gridDim.x * (blockDim.x / fc::kWave);
+  for (uint32_t i = blockIdx.x * (blockDim.x / fc::kWave) + threadIdx.x / fc::kWave; i < groups; i += waves) {
+    const uint32_t s = g.start[i];
+    uint32_t e = U;
+    for (uint32_t w = s / kWin + 1; w < windows; w += fc::kWave) {
+      const uint32_t x = w + lane < windows ? g.first_head[w + lane] : kNone;
+      const uint64_t hit = fc::ballot(x != kNone);
+      if (hit) {
+        e = (uint32_t)__shfl((int)x, (int)__builtin_ctzll(hit), fc::kWave);
+        break;
+      }
+    }
+    const uint32_t tiles = (e - s + kSortTile - 1) / kSortTile;
+    uint32_t t0 = 0;
+    if (lane == 0) {
+      t0 = atomicAdd(&g.count[1], tiles);
+      g.size[i] = e - s;
+      g.tile0[i] = t0;
+    }
+    t0 = (uint32_t)__shfl((int)t0, 0, fc::kWave);
+    for (uint32_t t = lane; t < tiles; t += fc::kWave) g.tile_group[t0 + t] = i;
+    for (int t = (int)lane; t < lo_digits * kRadix; t += fc::kWave) g.hist[(uint64_t)i * lo_digits * kRadix + t] = 0;
+  }
+}
+
+// lo of the large groups' elements, into the buffers the first digit pass
+// reads, and each group's digit histograms.  Every workgroup takes one run of
+// consecutive tiles and adds its counts once per group it meets.
+template <Mode M>
+__global__ void __launch_bounds__(256) k_big_keys(BigWs g, const uint32_t* __restrict__ val, NextRank nr,
+                                                    int lo_digits, uint32_t* __restrict__ lo_out,
+                                                    uint32_t* __restrict__ val_out) {
+  __shared__ uint32_t s_hist[kMaxLoDigits * kRadix];
+  const uint32_t tiles = g.count[1];
+  const uint32_t a = (uint32_t)((uint64_t)tiles * blockIdx.x / gridDim.x);
+  const uint32_t e = (uint32_t)((uint64_t)tiles * (blockIdx.x + 1) / gridDim.x);
+  if (a >= e) return;
+  const int bins = lo_digits * kRadix;
+  for (int i = threadIdx.x; i < bins; i += 256) s_hist[i] = 0;
+  __syncthreads();
+  for (uint32_t t = a; t < e; ++t) {
+    const uint32_t gr = uniform(g.tile_group[t]);
+    const uint32_t off = (t - uniform(g.tile0[gr])) * kSortTile;
+    const uint32_t left = uniform(g.size[gr]) - off;
+    const uint32_t nv = left < (uint32_t)kSortTile ? left : (uint32_t)kSortTile;
+    const uint64_t base = (uint64_t)g.start[gr] + off;
+    uint32_t v[kSortItems], k[kSortItems];
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j) {
+      const uint32_t i = (uint32_t)(j * 256) + threadIdx.x;
+      v[j] = i < nv ? val[base + i] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j) {
+      const uint32_t i = (uint32_t)(j * 256) + threadIdx.x;
+      k[j] = i < nv ? next_rank<M>(nr, v[j]) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j) {
+      const uint32_t i = (uint32_t)(j * 256) + threadIdx.x;
+      if (i < nv) {
+        lo_out[base + i] = k[j];
+        if (val_out) val_out[base + i] = v[j];
+        for (int d = 0; d < lo_digits; ++d) atomicAdd(&s_hist[d * kRadix + ((k[j] >> (8 * d)) & 0xFF)], 1u);
+      }
+    }
+    if (t + 1 == e || g.tile_group[t + 1] != gr) {
+      __syncthreads();
+      for (int i = threadIdx.x; i < bins; i += 256) {
+        const uint32_t c = s_hist[i];
+        if (c) atomicAdd(&g.hist[(uint64_t)gr * bins + i], c);
+        s_hist[i] = 0;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// One digit pass over every large group: a onesweep pass (see k_onesweep) on
+// 8-byte elements, by a resident grid that takes tiles from a ticket counter;
+// a tile's look-back stops at its group's first tile, and its digits start
+// from the group's own histogram.
+__global__ void __launch_bounds__(kSortThreads, 4) k_big_pass(BigWs g, int pass, int lo_digits,
+                                                             const uint32_t* __restrict__ kin,
+                                                             const uint32_t* __restrict__ vin,
+                                                             uint32_t* __restrict__ kout,
+                                                             uint32_t* __restrict__ vout, uint64_t* status,
+                                                             uint32_t epoch, uint32_t* err) {
+  constexpr int kWaves = kSortThreads / fc::kWave;
+  __shared__ uint32_t s_tile;
+  __shared__ uint16_t s_wcnt[kWaves][kRadix];
+  __shared__ uint16_t s_dstart[kRadix];
+  __shared__ uint32_t s_gbase[kRadix];
+  __shared__ uint32_t s_scan[kWaves + 1];
+  __shared__ uint32_t s_keys[kSortTile];
+  __shared__ uint32_t s_vals[kSortTile];
+  const int tid = threadIdx.x;
+  const int w = (int)uniform((uint32_t)tid / fc::kWave);
+  const int lane = fc::lane_id();
+  const uint32_t tiles = g.count[1];
+  const uint32_t shift = (uint32_t)(8 * pass);
+  const uint64_t lt = fc::lanemask_lt();
+  for (;;) {
+    for (int i = tid; i < kWaves * kRadix; i += kSortThreads) (&s_wcnt[0][0])[i] = 0;
+    if (tid == 0) s_tile = atomicAdd(&g.count[2 + pass], 1u);
+    __syncthreads();
+    const uint32_t tile = uniform(s_tile);
+    if (tile >= tiles) return;
+    const uint32_t gr = uniform(g.tile_group[tile]);
+    const uint32_t t0 = uniform(g.tile0[gr]);
+    const uint64_t gstart = uniform(g.start[gr]);
+    const uint64_t base = gstart + (uint64_t)(tile - t0) * kSortTile;
+    const uint32_t size = uniform(g.size[gr]);
+    const uint32_t left = size - (tile - t0) * kSortTile;
+    const uint32_t nvalid = left < (uint32_t)kSortTile ? left : (uint32_t)kSortTile;
+    const uint32_t* __restrict__ kt = kin + base;
+    const uint32_t* __restrict__ vt = vin + base;
+    uint32_t k[kSortItems], v[kSortItems], rk[kSortItems];
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j) {
+      const uint32_t idx = (uint32_t)(w * kSortItems * fc::kWave + j * fc::kWave + lane);
+      k[j] = idx < nvalid ? kt[idx] : ~0u;
+      v[j] = idx < nvalid ? vt[idx] : 0u;
+    }
+    const uint32_t hcount = g.hist[((uint64_t)gr * lo_digits + pass) * kRadix + tid];
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j) {
+      const uint32_t idx = (uint32_t)(w * kSortItems * fc::kWave + j * fc::kWave + lane);
+      rk[j] = wave_digit_rank((k[j] >> shift) & 0xFF, idx < nvalid, lt, s_wcnt[w]);
+    }
+    __syncthreads();
+    const uint32_t t = (uint32_t)tid;  // this thread's digit
+    uint32_t total = 0;
+#pragma unroll
+    for (int ww = 0; ww < kWaves; ++ww) {
+      const uint32_t c = s_wcnt[ww][t];
+      s_wcnt[ww][t] = (uint16_t)total;
+      total += c;
+    }
+    uint64_t* mine = status + (uint64_t)tile * kRadix + t;
+    __hip_atomic_store(mine, pack_status(epoch, tile > t0 ? kFlagAgg : kFlagInc, total), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    s_dstart[t] = (uint16_t)fc::block_excl_sum<uint32_t>(total, s_scan, nullptr);
+    const uint32_t dbase = fc::block_excl_sum<uint32_t>(hcount, s_scan, nullptr);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j) {
+      const uint32_t idx = (uint32_t)(w * kSortItems * fc::kWave + j * fc::kWave + lane);
+      if (idx < nvalid) {
+        const uint32_t d = (k[j] >> shift) & 0xFF;
+        const uint32_t pos = s_dstart[d] + s_wcnt[w][d] + rk[j];
+        s_keys[pos] = k[j];
+        s_vals[pos] = v[j];
+      }
+      if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // or their addresses spill
+    }
+    const uint64_t excl = look_back(status, (int64_t)tile - 1, (int64_t)t0, t, epoch, err);
+    if (tile > t0)
+      __hip_atomic_store(mine, pack_status(epoch, kFlagInc, excl + total), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    s_gbase[t] = dbase + (uint32_t)excl;
+    __syncthreads();
+    for (uint32_t i = (uint32_t)tid; i < nvalid; i += kSortThreads) {
+      const uint32_t key = s_keys[i];
+      const uint32_t d = (key >> shift) & 0xFF;
+      const uint32_t dst = s_gbase[d] + (i - s_dstart[d]);
+      if (dst < size) {  // always true unless a look-back gave up (then err is set)
+        kout[gstart + dst] = key;
+        vout[gstart + dst] = s_vals[i];
+      }
+    }
+    __syncthreads();  // the next tile reuses the LDS
+  }
+}
+
 // ------------------------------------------------------ group bookkeeping --
 
 struct SegFlags {
   bool new_head, old_head, keep;
 };
 
-__device__ __forceinline__ SegFlags seg_flags(const uint64_t* __restrict__ keys, uint32_t U, uint32_t r,
-                                              uint32_t sb, bool round0) {
-  const uint64_t kr = keys[r];
-  SegFlags f;
-  if (r == 0) {
-    f.new_head = true;
-    f.old_head = true;
+// A round's sorted list: round 0's 64-bit keys (one group), later (grp, lo).
+template <bool kRound0>
+struct Sorted {
+  const uint64_t* keys;
+  const uint32_t *grp, *lo;
+};
+
+template <bool kRound0>
+__device__ __forceinline__ SegFlags seg_flags(const Sorted<kRound0>& a, uint32_t U, uint32_t r) {
+  SegFlags f{true, true, false};
+  bool last;
+  if constexpr (kRound0) {
+    const uint64_t kr = a.keys[r];
+    if (r > 0) f.new_head = kr != a.keys[r - 1], f.old_head = false;
+    last = r + 1 == U || a.keys[r + 1] != kr;
   } else {
-    const uint64_t kp = keys[r - 1];
-    f.new_head = kr != kp;
-    f.old_head = round0 ? false : ((kr >> sb) != (kp >> sb));
+    const uint32_t gr = a.grp[r], lr = a.lo[r];
+    if (r > 0) {
+      f.old_head = gr != a.grp[r - 1];
+      f.new_head = f.old_head || lr != a.lo[r - 1];
+    }
+    last = r + 1 == U || a.grp[r + 1] != gr || a.lo[r + 1] != lr;
   }
-  const bool last_of_group = (r + 1 == U) || (keys[r + 1] != kr);
-  f.keep = !(f.new_head && last_of_group);
+  f.keep = !(f.new_head && last);
   return f;
 }
 
 // Per tile: last new-group head, last old-group head, number kept.
-__global__ void __launch_bounds__(kSegThreads) k_seg_partials(const uint64_t* __restrict__ keys, uint32_t U,
-                                                                uint32_t sb, int round0, uint32_t* __restrict__ part_h,
+template <bool kRound0>
+__global__ void __launch_bounds__(kSegThreads) k_seg_partials(Sorted<kRound0> in, uint32_t U,
+                                                                uint32_t* __restrict__ part_h,
                                                                 uint32_t* __restrict__ part_g,
                                                                 uint32_t* __restrict__ part_k) {
   __shared__ uint32_t scratch[kSegThreads / fc::kWave + 1];
@@ -673,7 +1214,7 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_partials(const uint64_t* __
   for (int j = 0; j < kSegItems; ++j) {
     const uint32_t r = r0 + (uint32_t)j * kSegThreads;  // coalesced; max and sum ignore the order
     if (r >= U) break;
-    const SegFlags f = seg_flags(keys, U, r, sb, round0 != 0);
+    const SegFlags f = seg_flags(in, U, r);
     if (f.new_head) mh = r;
     if (f.old_head) mg = r;
     kc += f.keep ? 1u : 0u;
@@ -752,7 +1293,8 @@ __global__ void __launch_bounds__(kScanThreads) k_seg_scan(uint32_t* __restrict_
 }
 
 // Per element: new rank = old group start + (new head index - old head index)
-// in the sorted list; tied suffixes are compacted into vals_next.  A suffix
+// in the sorted list; tied suffixes are compacted into (grp_next, val_next)
+// with their new rank as the group.  A suffix
 // whose group is now a singleton has its final index, so its suffix array
 // entry is written here (sa_out, unless null), in sorted order.  The ranks
 // go to rank[] directly (a random 4-byte write each), or, with pairs, as
@@ -762,16 +1304,15 @@ __global__ void __launch_bounds__(kScanThreads) k_seg_scan(uint32_t* __restrict_
 // ones per step: the running head indexes and the kept count are wave scans
 // carried from step to step, started from the earlier waves' totals and the
 // tile prefix.
-__global__ void __launch_bounds__(kSegThreads) k_seg_apply(const uint64_t* __restrict__ keys,
-                                                             const uint32_t* __restrict__ vals, uint32_t U,
-                                                             uint32_t sb, int round0,
-                                                             const uint32_t* __restrict__ pre_h,
+template <bool kRound0>
+__global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, const uint32_t* __restrict__ vals,
+                                                             uint32_t U, const uint32_t* __restrict__ pre_h,
                                                              const uint32_t* __restrict__ pre_g,
                                                              const uint32_t* __restrict__ pre_k,
                                                              uint32_t* __restrict__ rank,
                                                              uint64_t* __restrict__ pairs,
-                                                             uint32_t* __restrict__ vals_next,
-                                                             uint64_t* __restrict__ hi_next,
+                                                             uint32_t* __restrict__ val_next,
+                                                             uint32_t* __restrict__ grp_next,
                                                              uint32_t* __restrict__ sa_out) {
   constexpr int kWaves = kSegThreads / fc::kWave;
   constexpr uint32_t kPerWave = kSegTile / kWaves;
@@ -779,13 +1320,12 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_apply(const uint64_t* __res
   const int w = (int)threadIdx.x / fc::kWave;
   const uint32_t lane = (uint32_t)fc::lane_id();
   const uint32_t base = blockIdx.x * kSegTile + (uint32_t)w * kPerWave;
-  const bool r0f = round0 != 0;
   // the wave's totals
   uint32_t mh = 0, mg = 0, kc = 0;
   for (int j = 0; j < kSegItems; ++j) {
     const uint32_t r = base + (uint32_t)j * fc::kWave + lane;
     if (r < U) {
-      const SegFlags f = seg_flags(keys, U, r, sb, r0f);
+      const SegFlags f = seg_flags(in, U, r);
       if (f.new_head) mh = r;
       if (f.old_head) mg = r;
       kc += f.keep ? 1u : 0u;
@@ -810,24 +1350,25 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_apply(const uint64_t* __res
     const uint32_t r = base + (uint32_t)j * fc::kWave + lane;
     const bool valid = r < U;
     SegFlags f{false, false, false};
-    if (valid) f = seg_flags(keys, U, r, sb, r0f);
+    if (valid) f = seg_flags(in, U, r);
     uint32_t hr = fc::wave_incl_max<uint32_t>(f.new_head ? r : 0u);
     uint32_t gr = fc::wave_incl_max<uint32_t>(f.old_head ? r : 0u);
     const uint32_t kr = fc::wave_incl_sum_u32(f.keep ? 1u : 0u);
     hr = hr > hh ? hr : hh;
     gr = gr > gg ? gr : gg;
     if (valid) {
-      const uint32_t start = r0f ? 0u : (uint32_t)(keys[r] >> sb);
+      uint32_t start = 0u;
+      if constexpr (!kRound0) start = in.grp[r];
       const uint32_t i = vals[r];
       const uint32_t rk = start + (hr - gr);
       // in the first new group of its old group a suffix keeps its rank (the
       // old group start, already in rank[i]): only round 0 and the later
       // new groups write (a pair rewrites an unchanged rank with itself)
       if (pairs) pairs[r] = ((uint64_t)i << 32) | rk;
-      else if (r0f || hr != gr) rank[i] = rk;
+      else if (kRound0 || hr != gr) rank[i] = rk;
       if (f.keep) {
-        vals_next[out + kr - 1u] = i;
-        if (hi_next) hi_next[out + kr - 1u] = (uint64_t)rk << sb;  // the next round's key, high half
+        val_next[out + kr - 1u] = i;
+        grp_next[out + kr - 1u] = rk;
       }
       else if (sa_out) sa_out[rk] = i;  // a singleton group: rk is the suffix's final index
     }
@@ -878,16 +1419,36 @@ __global__ void __launch_bounds__(256) k_bucket(const uint16_t* __restrict__ tok
   bucket[t] = lo;
 }
 
-// Largest token of a store, for the pair-table precondition (out[0] starts
-// at 0).
+// Largest token of a store (out[0] starts at 0).  Sixteen bytes a lane, and
+// one atomic per workgroup that could raise the result: an atomic per wave of
+// a 4,096-workgroup grid on the one word took 190 us whatever the size.
 __global__ void __launch_bounds__(256) k_max_token(const uint16_t* __restrict__ tok, uint32_t n,
                                                    uint32_t* __restrict__ out) {
+  __shared__ uint32_t scratch[256 / fc::kWave];
   uint32_t mx = 0;
-  for (uint64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    mx = tok[i] > mx ? tok[i] : mx;
-  mx = fc::wave_max(mx);
-  if (fc::lane_id() == 0 && mx) atomicMax(out, mx);
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  const uint64_t id = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  // 16-byte pieces from the first 16-byte boundary; the tokens around them one by one
+  const uint32_t to16 = (uint32_t)((16 - ((uintptr_t)tok & 15)) & 15) / 2;
+  const uint32_t head = to16 < n ? to16 : n;
+  const uint64_t pieces = (n - head) / 8;
+  const uint4* q = (const uint4*)(tok + head);
+  for (uint64_t i = id; i < pieces; i += stride) {
+    const uint4 x = q[i];
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      mx = (w[u] & 0xFFFFu) > mx ? (w[u] & 0xFFFFu) : mx;
+      mx = (w[u] >> 16) > mx ? (w[u] >> 16) : mx;
+    }
+  }
+  const uint64_t rest = head + pieces * 8;  // fewer than eight tokens from here on
+  if (id < head) mx = tok[id] > mx ? tok[id] : mx;
+  if (id < n - rest) mx = tok[rest + id] > mx ? tok[rest + id] : mx;
+  mx = fc::block_max<uint32_t>(mx, scratch);
+  if (threadIdx.x == 0 && mx > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(out, mx);
 }
+constexpr uint32_t kMaxTokenBlocks = 1024;
 
 // Two-token table: suffix-array position r owns the table entries between
 // the previous suffix's pair key (exclusive) and its own (inclusive); keys
@@ -982,11 +1543,12 @@ struct BuildWs {
   uint32_t* hist;
   uint32_t* offsets;
   uint32_t* tickets;
-  uint32_t* misc;  // [0] error flag, [1] next U, [2..9] trivial digit flags, [10] largest token
-  uint64_t* pairs;    // plain build: a round's (suffix, rank) pairs
-  uint32_t* end_of;   // batched build: end of each position's segment
-  uint64_t* seg_off;  // batched build: segment offsets (device copy)
+  uint32_t* misc;      // [0] error flag, [1] tied suffixes, [2..2+kBigCounts) the large groups' counters, [10] largest token
+  uint64_t* pairs;     // plain build: a round's (suffix, rank) pairs
+  uint32_t* seg_bits;  // batched build: a bit per position that starts a segment
+  uint64_t* seg_off;   // batched build: segment offsets (device copy)
 };
+static_assert(2 + kBigCounts <= 10, "misc words");
 
 size_t carve_build(void* p, uint64_t n, BuildWs* w, uint32_t n_seg = 0) {
   fc::Carver c(p);
@@ -998,7 +1560,9 @@ size_t carve_build(void* p, uint64_t n, BuildWs* w, uint32_t n_seg = 0) {
   tmp.keys[1] = c.take<uint64_t>(n);
   tmp.vals[0] = c.take<uint32_t>(n);
   tmp.vals[1] = c.take<uint32_t>(n);
-  tmp.status = c.take<uint64_t>(tiles * kRadix);
+  // a large group's last tile may be short, so the groups' tiles are up to
+  // one per group more than the list's
+  tmp.status = c.take<uint64_t>((tiles + n / (kWin + 1)) * kRadix);
   tmp.part_h = c.take<uint32_t>(seg_tiles);
   tmp.part_g = c.take<uint32_t>(seg_tiles);
   tmp.part_k = c.take<uint32_t>(seg_tiles);
@@ -1006,11 +1570,27 @@ size_t carve_build(void* p, uint64_t n, BuildWs* w, uint32_t n_seg = 0) {
   tmp.offsets = c.take<uint32_t>(kMaxDigits * kRadix);
   tmp.tickets = c.take<uint32_t>(kMaxPasses);
   tmp.misc = c.take<uint32_t>(16);
-  tmp.end_of = n_seg ? c.take<uint32_t>(n) : nullptr;
+  tmp.seg_bits = n_seg ? c.take<uint32_t>(n / 32 + 1) : nullptr;
   tmp.seg_off = n_seg ? c.take<uint64_t>((size_t)n_seg + 1) : nullptr;
   tmp.pairs = n_seg == 0 && n >= kPairRanksMin ? c.take<uint64_t>(n) : nullptr;
   if (w) *w = tmp;
   return c.used + 256;
+}
+
+// The large groups' arrays, in 4 n bytes at p that a round leaves free.  A
+// list of n elements has at most n / (kWin + 1) large groups and as many more
+// tiles than n / kSortTile; their histograms take 2 n bytes of the 4 n.
+// Lists of up to kWin elements have no large group.
+size_t carve_big(void* p, uint64_t n, BigWs* g) {
+  fc::Carver c(p);
+  const uint64_t groups = n / (kWin + 1);
+  g->first_head = c.take<uint32_t>((n + kWin - 1) / kWin);
+  g->start = c.take<uint32_t>(groups);
+  g->size = c.take<uint32_t>(groups);
+  g->tile0 = c.take<uint32_t>(groups);
+  g->tile_group = c.take<uint32_t>((n + kSortTile - 1) / kSortTile + groups);
+  g->hist = c.take<uint32_t>(groups * kMaxLoDigits * kRadix);
+  return c.used;
 }
 
 int bit_length(uint64_t x) {
@@ -1027,26 +1607,17 @@ struct SortState {
   uint32_t ticket = 0;
 };
 
-// LSD radix sort over key bits [shift0, shift0 + key_bits) of kb[src], with
+// LSD radix sort over `digits` 8-bit digits from bit shift0 of kb[src], with
 // vb[src] carried alongside unless vb is null, the passes alternating
-// between the two buffers.  *result is the index (0 or 1) of the buffer
-// that holds the result.
-fc_status radix_sort(BuildWs& w, uint64_t* const kb[2], uint32_t* const vb[2], int src, uint32_t U, int shift0,
-                     int key_bits, SortState& st, hipStream_t stream, int* result) {
-  const int digits = (key_bits + 7) / 8;
-  FC_CHECK_HIP(hipMemsetAsync(w.hist, 0, sizeof(uint32_t) * kMaxDigits * kRadix, stream));
-  const uint32_t hist_blocks = fc::div_up(U, 256) < (uint32_t)kHistBlocks ? fc::div_up(U, 256) : kHistBlocks;
-  hipLaunchKernelGGL(k_hist, dim3(hist_blocks), dim3(256), 0, stream, kb[src], U, shift0, digits, w.hist);
+// between the two buffers; w.hist holds the digits' counts.  *result is the
+// index (0 or 1) of the buffer that holds the result.
+fc_status radix_passes(BuildWs& w, uint64_t* const kb[2], uint32_t* const vb[2], int src, uint32_t U, int shift0,
+                       int digits, SortState& st, hipStream_t stream, int* result) {
+  hipLaunchKernelGGL(k_hist_scan, dim3(digits), dim3(256), 0, stream, w.hist, w.offsets);
   FC_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_hist_scan, dim3(1), dim3(256), 0, stream, w.hist, U, digits, w.offsets, w.misc + 2);
-  FC_CHECK_LAUNCH();
-  uint32_t trivial[kMaxDigits] = {0};
-  FC_CHECK_HIP(hipMemcpyAsync(trivial, w.misc + 2, sizeof(uint32_t) * digits, hipMemcpyDeviceToHost, stream));
-  FC_CHECK_HIP(hipStreamSynchronize(stream));
   int cur = src;
   const uint32_t tiles = fc::div_up(U, kSortTile);
   for (int d = 0; d < digits; ++d) {
-    if (trivial[d]) continue;
     if (st.ticket >= (uint32_t)kMaxPasses) return FC_ERR_UNSUPPORTED;
     ++st.epoch;
     const uint32_t shift = (uint32_t)(shift0 + 8 * d);
@@ -1075,93 +1646,162 @@ struct ExtendArgs {
   int n_old_bits;
 };
 
+// The list of still-tied suffixes between two rounds, and what a round needs.
+struct ListWs {
+  uint32_t* grp[2];
+  uint32_t* val[2];
+  uint32_t* lo;
+  BigWs big;
+};
+
 // Prefix doubling over all n suffixes (n_seg = 0), over the suffixes of
 // n_seg segments at once, each ending at its segment's end (n_seg >= 1,
 // offsets already in w.seg_off), or over the n new suffixes of an extension
 // (ext; leaves their ranks in w.rank and writes no suffix array).
+template <Mode M>
 fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& w, uint32_t* sa_out,
                    hipStream_t stream, const ExtendArgs* ext = nullptr, fc_build_stats* stats = nullptr) {
   const uint32_t N = (uint32_t)n;
   const uint64_t tiles = (n + kSortTile - 1) / kSortTile;
-  FC_CHECK_HIP(hipMemsetAsync(w.status, 0, sizeof(uint64_t) * tiles * kRadix, stream));
+  FC_CHECK_HIP(hipMemsetAsync(w.status, 0, sizeof(uint64_t) * (tiles + n / (kWin + 1)) * kRadix, stream));
   FC_CHECK_HIP(hipMemsetAsync(w.tickets, 0, sizeof(uint32_t) * kMaxPasses, stream));
   FC_CHECK_HIP(hipMemsetAsync(w.misc, 0, sizeof(uint32_t) * 16, stream));
+  FC_CHECK_HIP(hipMemsetAsync(w.hist, 0, sizeof(uint32_t) * kMaxDigits * kRadix, stream));
 
-  // every rank + 1 <= n (an extension's labels: <= the whole text) fits in sb bits
-  const uint32_t sb = (uint32_t)bit_length(ext ? ext->n : n);
+  // every rank + 1 <= n (an extension's labels: <= the whole text) fits in lo_digits bytes
+  const int lo_digits = (bit_length(ext ? ext->n : n) + 7) / 8;
   SortState st;
   uint64_t h;
   int key0_bits;
   int ext_shift = 0;
-  if (ext) {
+  const uint32_t init_blocks = fc::div_up(N, 1024) < (uint32_t)kHistBlocks ? fc::div_up(N, 1024) : kHistBlocks;
+  if (M == Mode::kExtend) {
     const int two = ext->n_old_bits + 34 <= 64;
     ext_shift = two ? 34 : 17;
-    hipLaunchKernelGGL(k_init_keys_ext, dim3(fc::div_up(N, 256)), dim3(256), 0, stream, tokens, N, ext->n,
-                       ext->ins, two, w.keys[0], w.vals[0]);
     h = two ? 2 : 1;
     key0_bits = ext_shift + ext->n_old_bits;
-  } else if (n_seg == 0) {
+    hipLaunchKernelGGL(k_init_keys_ext, dim3(init_blocks), dim3(256), 0, stream, tokens, N, ext->n, ext->ins, two,
+                       (key0_bits + 7) / 8, w.keys[0], w.vals[0], w.hist);
+  } else {
     // token + 1 in tb bits: the largest token decides tb (misc[10] is zero)
-    const uint32_t blocks = fc::div_up(N, 256) < 4096u ? fc::div_up(N, 256) : 4096u;
+    const uint32_t blocks = fc::div_up(N, 2048) < kMaxTokenBlocks ? fc::div_up(N, 2048) : kMaxTokenBlocks;
     hipLaunchKernelGGL(k_max_token, dim3(blocks), dim3(256), 0, stream, tokens, N, w.misc + 10);
     FC_CHECK_LAUNCH();
     uint32_t mx = 0;
     FC_CHECK_HIP(hipMemcpyAsync(&mx, w.misc + 10, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
     FC_CHECK_HIP(hipStreamSynchronize(stream));
     const int tb = bit_length((uint64_t)mx + 1);
-    hipLaunchKernelGGL(k_init_keys, dim3(fc::div_up(N, 256)), dim3(256), 0, stream, tokens, N, tb, w.keys[0],
-                       w.vals[0]);
-    h = 3;
-    key0_bits = 3 * tb;
-  } else {
-    hipLaunchKernelGGL(k_init_keys_seg, dim3(fc::div_up(N, 256)), dim3(256), 0, stream, tokens, N, w.seg_off, n_seg,
-                       w.keys[0], w.vals[0], w.end_of);
-    h = 2;
-    key0_bits = 34 + bit_length(n_seg - 1);
+    if (M == Mode::kPlain) {
+      h = 3;
+      key0_bits = 3 * tb;
+      hipLaunchKernelGGL(k_init_keys, dim3(init_blocks), dim3(256), 0, stream, tokens, N, tb, (key0_bits + 7) / 8,
+                         w.keys[0], w.vals[0], w.hist);
+    } else {
+      const int seg_bits = bit_length(n_seg - 1);
+      const int ntok = seg_bits + 3 * tb <= 64 ? 3 : 2;  // 17-bit tokens and up to 2^30 segments: two always fit
+      h = (uint64_t)ntok;
+      key0_bits = seg_bits + ntok * tb;
+      FC_CHECK_HIP(hipMemsetAsync(w.seg_bits, 0, sizeof(uint32_t) * (n / 32 + 1), stream));
+      hipLaunchKernelGGL(k_seg_starts, dim3(fc::div_up(n_seg, 256)), dim3(256), 0, stream, w.seg_off, n_seg, N,
+                         w.seg_bits);
+      FC_CHECK_LAUNCH();
+      hipLaunchKernelGGL(k_init_keys_seg, dim3(init_blocks), dim3(256), 0, stream, tokens, N, w.seg_off, n_seg, tb,
+                         ntok, (key0_bits + 7) / 8, w.keys[0], w.vals[0], w.hist);
+    }
   }
   FC_CHECK_LAUNCH();
-  uint32_t U = N;
-  int vin = 0;  // buffer holding the suffixes to sort
+  int res = 0;
+  fc_status s = radix_passes(w, w.keys, w.vals, 0, N, 0, (key0_bits + 7) / 8, st, stream, &res);
+  if (s != FC_OK) return s;
+  int sort_passes = (int)st.ticket;
+  if (M == Mode::kExtend) {
+    hipLaunchKernelGGL(k_ins_sorted, dim3(fc::div_up(N, 256)), dim3(256), 0, stream, w.keys[res], N, ext_shift,
+                       ext->ins_sorted);
+    FC_CHECK_LAUNCH();
+  }
+  // The lists live in the sort buffers: round 0's result is in keys[res] and
+  // vals[res], so its tied suffixes go to the other two, and from then on
+  // keys[res] is free as well (lo, and the large groups' arrays).
+  ListWs L;
+  L.grp[0] = (uint32_t*)w.keys[res ^ 1];
+  L.grp[1] = L.grp[0] + n;
+  L.val[0] = w.vals[res ^ 1];
+  L.val[1] = w.vals[res];
+  L.lo = (uint32_t*)w.keys[res];
+  const uint64_t lo_words = (n + 63) & ~(uint64_t)63;  // keeps what follows aligned
+  if (n > (uint64_t)kWin) {
+    if (lo_words * 4 + carve_big(nullptr, n, &L.big) > 8 * n) return FC_ERR_DEVICE;
+    carve_big(L.lo + lo_words, n, &L.big);
+  } else {
+    L.big = BigWs{};
+    L.big.first_head = w.hist;  // the one window of a short list
+  }
+  L.big.count = w.misc + 2;
   // ranks through k_rank_write when the rank array is at least the size of
   // the 256 MB MALL; a smaller one takes the random writes in the MALL
-  const bool pair_ranks = !ext && n_seg == 0 && n >= kPairRanksMin;
+  const bool pair_ranks = M == Mode::kPlain && n >= kPairRanksMin;
+  NextRank nr{w.rank, w.seg_bits, ext ? ext->ins : nullptr, ext ? ext->isa : nullptr,
+              ext ? ext->ins_sorted : nullptr, ext ? ext->n : n, h, N};
+
+  uint32_t U = N;
+  int cur = 1;  // the list a round sorts (round 0: none); the other one takes its tied suffixes
   for (int round = 0;; ++round) {
     if (round >= kMaxRounds) return FC_ERR_DEVICE;
-    if (round > 0) {
-      if (ext)
-        hipLaunchKernelGGL(k_pair_keys_ext, dim3(fc::div_up(U, 256)), dim3(256), 0, stream, w.vals[vin], U, w.rank,
-                           ext->ins, ext->isa, ext->ins_sorted, N, ext->n, h, sb, w.keys[vin]);
-      else if (n_seg == 0)
-        hipLaunchKernelGGL(k_pair_keys, dim3(fc::div_up(U, 256)), dim3(256), 0, stream, w.vals[vin], U, w.rank, N,
-                           h, w.keys[vin]);
-      else
-        hipLaunchKernelGGL(k_pair_keys_seg, dim3(fc::div_up(U, 256)), dim3(256), 0, stream, w.vals[vin], U, w.rank,
-                           w.end_of, h, sb, w.keys[vin]);
-      FC_CHECK_LAUNCH();
-      h *= 2;
-    }
-    int res = vin;
-    fc_status s = radix_sort(w, w.keys, w.vals, vin, U, 0, round == 0 ? key0_bits : (int)(2 * sb), st, stream,
-                             &res);
-    if (s != FC_OK) return s;
-    if (ext && round == 0) {
-      hipLaunchKernelGGL(k_ins_sorted, dim3(fc::div_up(N, 256)), dim3(256), 0, stream, w.keys[res], N, ext_shift,
-                         ext->ins_sorted);
-      FC_CHECK_LAUNCH();
-    }
     const uint32_t seg_tiles = fc::div_up(U, kSegTile);
-    hipLaunchKernelGGL(k_seg_partials, dim3(seg_tiles), dim3(kSegThreads), 0, stream, w.keys[res], U, sb,
-                       round == 0 ? 1 : 0, w.part_h, w.part_g, w.part_k);
+    const Sorted<true> s0{w.keys[res], nullptr, nullptr};
+    const Sorted<false> s1{nullptr, L.grp[cur], L.lo};
+    const uint32_t* sorted_vals = round == 0 ? w.vals[res] : L.val[cur];
+    uint64_t* pairs = pair_ranks ? w.pairs : nullptr;
+    if (round == 0)
+      hipLaunchKernelGGL(k_seg_partials<true>, dim3(seg_tiles), dim3(kSegThreads), 0, stream, s0, U, w.part_h,
+                         w.part_g, w.part_k);
+    else
+      hipLaunchKernelGGL(k_seg_partials<false>, dim3(seg_tiles), dim3(kSegThreads), 0, stream, s1, U, w.part_h,
+                         w.part_g, w.part_k);
     FC_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(kScanThreads), 0, stream, w.part_h, w.part_g, w.part_k, seg_tiles,
                        w.misc + 1);
     FC_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_seg_apply, dim3(seg_tiles), dim3(kSegThreads), 0, stream, w.keys[res], w.vals[res], U, sb,
-                       round == 0 ? 1 : 0, w.part_h, w.part_g, w.part_k, w.rank, pair_ranks ? w.pairs : nullptr,
-                       w.vals[res ^ 1], (ext || n_seg > 0) ? nullptr : w.keys[res ^ 1], ext ? nullptr : sa_out);
+    if (round == 0)
+      hipLaunchKernelGGL(k_seg_apply<true>, dim3(seg_tiles), dim3(kSegThreads), 0, stream, s0, sorted_vals, U,
+                         w.part_h, w.part_g, w.part_k, w.rank, pairs, L.val[cur ^ 1], L.grp[cur ^ 1],
+                         ext ? nullptr : sa_out);
+    else
+      hipLaunchKernelGGL(k_seg_apply<false>, dim3(seg_tiles), dim3(kSegThreads), 0, stream, s1, sorted_vals, U,
+                         w.part_h, w.part_g, w.part_k, w.rank, pairs, L.val[cur ^ 1], L.grp[cur ^ 1],
+                         ext ? nullptr : sa_out);
     FC_CHECK_LAUNCH();
-    uint32_t host_misc[2] = {0, 0};
-    FC_CHECK_HIP(hipMemcpyAsync(host_misc, w.misc, sizeof(uint32_t) * 2, hipMemcpyDeviceToHost, stream));
+    if (pair_ranks) {
+      // the round's ranks, for the next round's keys: the pairs sorted by the
+      // suffix's top kRankSortBits bits (lo's buffer is free now), then
+      // written window by window
+      const int sb = bit_length(n);
+      uint64_t* const pb[2] = {w.pairs, w.keys[res]};
+      const int hb = sb < kRankSortBits ? sb : kRankSortBits;
+      FC_CHECK_HIP(hipMemsetAsync(w.hist, 0, sizeof(uint32_t) * kMaxDigits * kRadix, stream));
+      const uint32_t hist_blocks = fc::div_up(U, 256) < (uint32_t)kHistBlocks ? fc::div_up(U, 256) : kHistBlocks;
+      hipLaunchKernelGGL(k_hist, dim3(hist_blocks), dim3(256), 0, stream, w.pairs, U, 32 + sb - hb, (hb + 7) / 8,
+                         w.hist);
+      FC_CHECK_LAUNCH();
+      int pres = 0;
+      s = radix_passes(w, pb, nullptr, 0, U, 32 + sb - hb, (hb + 7) / 8, st, stream, &pres);
+      if (s != FC_OK) return s;
+      sort_passes += (hb + 7) / 8;
+      const uint32_t per_xcd = fc::div_up(fc::div_up(U, kRankChunk), kXcds);
+      hipLaunchKernelGGL(k_rank_write, dim3(per_xcd * kXcds), dim3(256), 0, stream, pb[pres], U, per_xcd, w.rank);
+      FC_CHECK_LAUNCH();
+    }
+    // the next round's small groups, launched before its size is known on
+    // the host, so that one wait per round tells both the tied suffixes and
+    // the large groups
+    cur ^= 1;
+    nr.h = h;
+    FC_CHECK_HIP(hipMemsetAsync(L.big.count, 0, sizeof(uint32_t) * kBigCounts, stream));
+    hipLaunchKernelGGL(k_sort_small<M>, dim3(fc::div_up(U, kWin)), dim3(kSmallThreads), 0, stream, L.grp[cur],
+                       L.val[cur], L.lo, w.misc + 1, nr, lo_digits, L.big.first_head, L.big.start, L.big.count);
+    FC_CHECK_LAUNCH();
+    uint32_t host_misc[3] = {0, 0, 0};
+    FC_CHECK_HIP(hipMemcpyAsync(host_misc, w.misc, sizeof(uint32_t) * 3, hipMemcpyDeviceToHost, stream));
     FC_CHECK_HIP(hipStreamSynchronize(stream));
     if (host_misc[0]) return FC_ERR_DEVICE;
     if (stats && round < FC_MAX_BUILD_ROUNDS) {
@@ -1169,29 +1809,40 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
       stats->sorted[round] = U;
       stats->unresolved[round] = host_misc[1];
       stats->rounds = round + 1;
-      stats->sort_passes = (int32_t)st.ticket;
-    }
-    if (pair_ranks && host_misc[1] > 0) {
-      // the round's ranks, for the next round's keys: the pairs sorted by the
-      // suffix's top kRankSortBits bits (the other sort buffer is free now),
-      // then written window by window
-      uint64_t* const pb[2] = {w.pairs, w.keys[res]};
-      const int hb = (int)sb < kRankSortBits ? (int)sb : kRankSortBits;
-      int pres = 0;
-      s = radix_sort(w, pb, nullptr, 0, U, 32 + (int)sb - hb, hb, st, stream, &pres);
-      if (s != FC_OK) return s;
-      const uint32_t per_xcd = fc::div_up(fc::div_up(U, kRankChunk), kXcds);
-      hipLaunchKernelGGL(k_rank_write, dim3(per_xcd * kXcds), dim3(256), 0, stream, pb[pres], U, per_xcd, w.rank);
-      FC_CHECK_LAUNCH();
+      stats->sort_passes = sort_passes;
     }
     U = host_misc[1];
-    vin = res ^ 1;
     if (U == 0) break;
+    h *= 2;
+    if (const uint32_t groups = host_misc[2]) {
+      // passes alternate between (lo, val) and the next round's buffers, which
+      // are free now; an odd number starts in those
+      uint32_t* const kb[2] = {L.lo, L.grp[cur ^ 1]};
+      uint32_t* const vb[2] = {L.val[cur], L.val[cur ^ 1]};
+      int from = lo_digits & 1;
+      const uint32_t most = U / kSortTile + groups;  // tiles, at most
+      const uint32_t waves = groups < 4096u ? groups : 4096u;
+      hipLaunchKernelGGL(k_big_plan, dim3(fc::div_up(waves, 4)), dim3(256), 0, stream, L.big, U, lo_digits);
+      FC_CHECK_LAUNCH();
+      const uint32_t kblocks = most < kBigKeysBlocks ? most : kBigKeysBlocks;
+      hipLaunchKernelGGL(k_big_keys<M>, dim3(kblocks), dim3(256), 0, stream, L.big, L.val[cur], nr, lo_digits,
+                         kb[from], from ? vb[1] : nullptr);
+      FC_CHECK_LAUNCH();
+      const uint32_t blocks = most < kBigPassBlocks ? most : kBigPassBlocks;
+      for (int d = 0; d < lo_digits; ++d) {
+        ++st.epoch;
+        hipLaunchKernelGGL(k_big_pass, dim3(blocks), dim3(kSortThreads), 0, stream, L.big, d, lo_digits, kb[from],
+                           vb[from], kb[from ^ 1], vb[from ^ 1], w.status, st.epoch, w.misc);
+        FC_CHECK_LAUNCH();
+        ++sort_passes;
+        from ^= 1;
+      }
+    }
   }
-  if (ext) return FC_OK;
+  if (M == Mode::kExtend) return FC_OK;
   // every suffix array entry was written when its suffix's group became a
   // singleton (k_seg_apply)
-  if (n_seg > 0) {
+  if (M == Mode::kBatched) {
     hipLaunchKernelGGL(k_localize_sa, dim3(fc::div_up(N, 256)), dim3(256), 0, stream, sa_out, N, w.seg_off, n_seg);
     FC_CHECK_LAUNCH();
   }
@@ -1212,7 +1863,7 @@ extern "C" fc_status fc_datastore_build_stats(const uint16_t* tokens, uint64_t n
   (void)hipGetLastError();
   BuildWs w;
   carve_build(ws, n, &w);
-  return build_sa(tokens, n, 0, w, sa_out, stream, nullptr, stats);
+  return build_sa<Mode::kPlain>(tokens, n, 0, w, sa_out, stream, nullptr, stats);
 }
 
 extern "C" fc_status fc_datastore_build(const uint16_t* tokens, uint64_t n, uint32_t* sa_out, void* ws,
@@ -1240,7 +1891,7 @@ extern "C" fc_status fc_datastore_build_batched(const uint16_t* tokens, const ui
   carve_build(ws, n, &w, (uint32_t)n_seg);
   FC_CHECK_HIP(hipMemcpyAsync(w.seg_off, seg_off, sizeof(uint64_t) * ((size_t)n_seg + 1), hipMemcpyHostToDevice,
                               stream));
-  return build_sa(tokens, n, (uint32_t)n_seg, w, sa_out, stream);
+  return build_sa<Mode::kBatched>(tokens, n, (uint32_t)n_seg, w, sa_out, stream);
 }
 
 namespace {
@@ -1337,7 +1988,7 @@ extern "C" fc_status fc_datastore_extend(const uint16_t* tokens, uint64_t n, uin
     ea.ins_sorted = w.ins_sorted;
     ea.n = n;
     ea.n_old_bits = bit_length(n_old);
-    fc_status s = build_sa(tokens, o, 0, w.b, nullptr, stream, &ea);
+    fc_status s = build_sa<Mode::kExtend>(tokens, o, 0, w.b, nullptr, stream, &ea);
     if (s != FC_OK) return s;
     hipLaunchKernelGGL(k_ext_new_out, dim3(fc::div_up(o, 256)), dim3(256), 0, stream, w.b.rank, w.lo[0], o, sa_out);
     FC_CHECK_LAUNCH();
@@ -1387,7 +2038,7 @@ extern "C" fc_status fc_store_prepare_pairs(const uint16_t* tokens, const uint32
   if (n > 0) {
     // precondition: every token < V (pair_out[0] serves as the reduction cell)
     FC_CHECK_HIP(hipMemsetAsync(pair_out, 0, sizeof(uint32_t), stream));
-    const uint32_t blocks = fc::div_up(n, 256) < 4096u ? fc::div_up(n, 256) : 4096u;
+    const uint32_t blocks = fc::div_up(n, 2048) < kMaxTokenBlocks ? fc::div_up(n, 2048) : kMaxTokenBlocks;
     hipLaunchKernelGGL(k_max_token, dim3(blocks), dim3(256), 0, stream, tokens, (uint32_t)n, pair_out);
     FC_CHECK_LAUNCH();
     uint32_t mx = 0;

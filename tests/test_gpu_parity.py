@@ -103,6 +103,36 @@ def test_sa_two_store_workload():
     assert oracle.check_sa(g, sa) == (0, 0)
 
 
+def _tied_groups(sizes, seed: int, vocab: int) -> np.ndarray:
+    """A text in which the 3-token prefix (i + 1, 1, 1) of group i occurs
+    sizes[i] times, each followed by one or two tokens of a small alphabet, so
+    that groups of exactly those sizes are left tied by the first round and
+    stay tied, in parts, for several more."""
+    r = np.random.default_rng(seed)
+    order = r.permutation(np.repeat(np.arange(len(sizes)), sizes))
+    out = []
+    for g in order:
+        out += [g + 1, 1, 1] + list(r.integers(100, 100 + vocab, 1 + int(r.integers(2))))
+    return np.array(out, np.uint16)
+
+
+@pytest.mark.parametrize("sizes", [
+    (2, 3, 47, 48, 49, 50, 63, 64, 65),                         # pairwise comparison up to 48, LDS radix sort beyond
+    (2046, 2, 2047, 3, 2048, 49, 2049, 2050),                   # a workgroup's window, and the first large groups
+    (4095, 4096, 4097, 8191, 8193, 12289),                      # tiles of a large group
+    tuple([700] * 9 + [2049] * 5 + [2] * 40 + [6000, 3, 2500]),  # both kinds side by side
+])
+@pytest.mark.parametrize("vocab", [2, 3000])
+def test_sa_group_size_edges(sizes, vocab):
+    say(f"sa groups {sizes[:8]} vocab={vocab}")
+    t = _tied_groups(sizes, len(sizes), vocab)
+    _sa_case(t)
+    _batched_case(*_concat([t[: len(t) // 3], t, t[:5000]]))
+    k = len(t) // 2
+    t[k - 1] = 0
+    _extend_case(t[:k], t[k:])
+
+
 def test_sa_large_texts_rank_pairs():
     """Stores of 64M suffixes or more take their ranks through sorted
     (suffix, rank) pairs instead of random writes: just past that size, with
