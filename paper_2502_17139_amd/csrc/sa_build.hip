@@ -697,8 +697,8 @@ __global__ void __launch_bounds__(kSortThreads, kVals ? 1 : 4) k_onesweep(const 
 // (small groups 28, keys of the large ones 25, their passes 24); 10M suffixes
 // 3.60 -> 2.83 ms, 64 repositories in one call 8.43 -> 6.04 ms.  The line
 // between the two lies at what one workgroup's LDS holds next to the groups
-// that start before it: about a third of the elements are in larger groups
-// in the first such round of a 10M store, two thirds of a 1B store's.
+// that start before it: in the first such round of a 10M store about half of
+// the elements are in larger groups, in the third a tenth.
 
 constexpr int kWin = 2048;          // list positions whose groups a workgroup sorts
 constexpr int kCap = 2 * kWin;      // a window's last group may end this far
@@ -981,11 +981,12 @@ struct BigWs {
   uint32_t* start;       // per large group: first list position
   uint32_t* size;
   uint32_t* tile0;       // its first tile
+  uint32_t* stat0;       // its first status slot: one per tile but the last, which no tile looks back to
   uint32_t* tile_group;  // per tile: its group
   uint32_t* hist;        // [group][digit place][256]
-  uint32_t* count;       // [0] groups, [1] tiles, [2..2+kMaxLoDigits) tickets of the passes
+  uint32_t* count;       // [0] groups, [1] tiles, [2] status slots, [3..3+kMaxLoDigits) tickets of the passes
 };
-constexpr int kBigCounts = 2 + kMaxLoDigits;
+constexpr int kBigCounts = 3 + kMaxLoDigits;
 
 // One wave per large group: its end is the first group start of a later
 // window (or the list's end); its tiles are numbered consecutively and its
@@ -1012,6 +1013,7 @@ __global__ void __launch_bounds__(256) k_big_plan(BigWs g, uint32_t U, int lo_di
       t0 = atomicAdd(&g.count[1], tiles);
       g.size[i] = e - s;
       g.tile0[i] = t0;
+      g.stat0[i] = atomicAdd(&g.count[2], tiles - 1);
     }
     t0 = (uint32_t)__shfl((int)t0, 0, fc::kWave);
     for (uint32_t t = lane; t < tiles; t += fc::kWave) g.tile_group[t0 + t] = i;
@@ -1098,7 +1100,7 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_big_pass(BigWs g, int pass,
   const uint64_t lt = fc::lanemask_lt();
   for (;;) {
     for (int i = tid; i < kWaves * kRadix; i += kSortThreads) (&s_wcnt[0][0])[i] = 0;
-    if (tid == 0) s_tile = atomicAdd(&g.count[2 + pass], 1u);
+    if (tid == 0) s_tile = atomicAdd(&g.count[3 + pass], 1u);
     __syncthreads();
     const uint32_t tile = uniform(s_tile);
     if (tile >= tiles) return;
@@ -1133,9 +1135,12 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_big_pass(BigWs g, int pass,
       s_wcnt[ww][t] = (uint16_t)total;
       total += c;
     }
-    uint64_t* mine = status + (uint64_t)tile * kRadix + t;
-    __hip_atomic_store(mine, pack_status(epoch, tile > t0 ? kFlagAgg : kFlagInc, total), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t slot0 = uniform(g.stat0[gr]), slot = slot0 + (tile - t0);
+    const bool seen = (uint64_t)(tile - t0 + 1) * kSortTile < size;  // a later tile of the group looks back here
+    uint64_t* mine = status + (uint64_t)slot * kRadix + t;
+    if (seen)
+      __hip_atomic_store(mine, pack_status(epoch, tile > t0 ? kFlagAgg : kFlagInc, total), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
     s_dstart[t] = (uint16_t)fc::block_excl_sum<uint32_t>(total, s_scan, nullptr);
     const uint32_t dbase = fc::block_excl_sum<uint32_t>(hcount, s_scan, nullptr);
     __syncthreads();
@@ -1150,8 +1155,8 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_big_pass(BigWs g, int pass,
       }
       if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // or their addresses spill
     }
-    const uint64_t excl = look_back(status, (int64_t)tile - 1, (int64_t)t0, t, epoch, err);
-    if (tile > t0)
+    const uint64_t excl = look_back(status, (int64_t)slot - 1, (int64_t)slot0, t, epoch, err);
+    if (tile > t0 && seen)
       __hip_atomic_store(mine, pack_status(epoch, kFlagInc, excl + total), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
     s_gbase[t] = dbase + (uint32_t)excl;
@@ -1560,9 +1565,7 @@ size_t carve_build(void* p, uint64_t n, BuildWs* w, uint32_t n_seg = 0) {
   tmp.keys[1] = c.take<uint64_t>(n);
   tmp.vals[0] = c.take<uint32_t>(n);
   tmp.vals[1] = c.take<uint32_t>(n);
-  // a large group's last tile may be short, so the groups' tiles are up to
-  // one per group more than the list's
-  tmp.status = c.take<uint64_t>((tiles + n / (kWin + 1)) * kRadix);
+  tmp.status = c.take<uint64_t>(tiles * kRadix);
   tmp.part_h = c.take<uint32_t>(seg_tiles);
   tmp.part_g = c.take<uint32_t>(seg_tiles);
   tmp.part_k = c.take<uint32_t>(seg_tiles);
@@ -1578,8 +1581,8 @@ size_t carve_build(void* p, uint64_t n, BuildWs* w, uint32_t n_seg = 0) {
 }
 
 // The large groups' arrays, in 4 n bytes at p that a round leaves free.  A
-// list of n elements has at most n / (kWin + 1) large groups and as many more
-// tiles than n / kSortTile; their histograms take 2 n bytes of the 4 n.
+// list of n elements has at most n / (kWin + 1) large groups, n / kWin tiles
+// and n / kSortTile status slots; the histograms take 2 n bytes of the 4 n.
 // Lists of up to kWin elements have no large group.
 size_t carve_big(void* p, uint64_t n, BigWs* g) {
   fc::Carver c(p);
@@ -1588,7 +1591,8 @@ size_t carve_big(void* p, uint64_t n, BigWs* g) {
   g->start = c.take<uint32_t>(groups);
   g->size = c.take<uint32_t>(groups);
   g->tile0 = c.take<uint32_t>(groups);
-  g->tile_group = c.take<uint32_t>((n + kSortTile - 1) / kSortTile + groups);
+  g->stat0 = c.take<uint32_t>(groups);
+  g->tile_group = c.take<uint32_t>(n / kWin);  // ceil(size / kSortTile) < size / kWin for every large group
   g->hist = c.take<uint32_t>(groups * kMaxLoDigits * kRadix);
   return c.used;
 }
@@ -1663,7 +1667,7 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
                    hipStream_t stream, const ExtendArgs* ext = nullptr, fc_build_stats* stats = nullptr) {
   const uint32_t N = (uint32_t)n;
   const uint64_t tiles = (n + kSortTile - 1) / kSortTile;
-  FC_CHECK_HIP(hipMemsetAsync(w.status, 0, sizeof(uint64_t) * (tiles + n / (kWin + 1)) * kRadix, stream));
+  FC_CHECK_HIP(hipMemsetAsync(w.status, 0, sizeof(uint64_t) * tiles * kRadix, stream));
   FC_CHECK_HIP(hipMemsetAsync(w.tickets, 0, sizeof(uint32_t) * kMaxPasses, stream));
   FC_CHECK_HIP(hipMemsetAsync(w.misc, 0, sizeof(uint32_t) * 16, stream));
   FC_CHECK_HIP(hipMemsetAsync(w.hist, 0, sizeof(uint32_t) * kMaxDigits * kRadix, stream));
@@ -1820,7 +1824,7 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
       uint32_t* const kb[2] = {L.lo, L.grp[cur ^ 1]};
       uint32_t* const vb[2] = {L.val[cur], L.val[cur ^ 1]};
       int from = lo_digits & 1;
-      const uint32_t most = U / kSortTile + groups;  // tiles, at most
+      const uint32_t most = U / kWin;  // tiles, at most
       const uint32_t waves = groups < 4096u ? groups : 4096u;
       hipLaunchKernelGGL(k_big_plan, dim3(fc::div_up(waves, 4)), dim3(256), 0, stream, L.big, U, lo_digits);
       FC_CHECK_LAUNCH();
