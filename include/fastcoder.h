@@ -475,6 +475,23 @@ fc_status fc_tree_attention(const uint16_t* q, const uint16_t* k_tree, const uin
                             int32_t R, int32_t H, int32_t Hkv, int32_t D, int32_t Pmax, float rope_base, float* out,
                             hipStream_t stream);
 
+/*
+ * fc_tree_attention with scratch memory, for few trees: with fewer (tree,
+ * head) pairs than the GPU has compute units, each pair's prefix is cut into
+ * parts that run side by side and are put together at the end (the same
+ * arithmetic; the running sums are added part by part).  ws holds at least
+ * fc_tree_attention_workspace_bytes(B, R, H, Pmax) bytes, 16-byte aligned
+ * (FC_ERR_INVALID), its contents on entry do not matter.  That size is 0
+ * where the call runs in one part; with ws NULL or ws_bytes below it the call
+ * runs in one part too, as fc_tree_attention does.
+ */
+size_t fc_tree_attention_workspace_bytes(int32_t B, int32_t R, int32_t H, int32_t Pmax);
+fc_status fc_tree_attention_ws(const uint16_t* q, const uint16_t* k_tree, const uint16_t* v_tree,
+                               const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* prefix_len,
+                               const int32_t* num_nodes, const int32_t* mask, const int32_t* pos_ids, int32_t B,
+                               int32_t R, int32_t H, int32_t Hkv, int32_t D, int32_t Pmax, float rope_base, float* out,
+                               void* ws, size_t ws_bytes, hipStream_t stream);
+
 /* ------------------------------------------------------------------------ */
 /* Decode-trace replay                                                       */
 /* ------------------------------------------------------------------------ */

@@ -38,7 +38,7 @@ EXPORTS = (
     "fc_store_top_bytes", "fc_store_prepare_top",
     "fc_retrieve_workspace_bytes", "fc_retrieve", "fc_build_tree_workspace_bytes", "fc_build_tree",
     "fc_verify_accept", "fc_targets_from_truth", "fc_cache_lds_bytes", "fc_cache_retrieve", "fc_cache_write",
-    "fc_tree_attention", "fc_replay_init", "fc_replay_run", "fc_retrieve_noalloc_max_bytes", "fc_retrieve_noalloc",
+    "fc_tree_attention", "fc_tree_attention_workspace_bytes", "fc_tree_attention_ws", "fc_replay_init", "fc_replay_run", "fc_retrieve_noalloc_max_bytes", "fc_retrieve_noalloc",
     "fc_datastore_build_stats",
 )
 
@@ -158,6 +158,10 @@ def lib() -> ctypes.CDLL:
     L.fc_cache_write.argtypes = [vp, ctypes.c_int64, i32, vp, i32, vp, vp, vp, vp, vp, vp, vp]
     L.fc_tree_attention.restype = ctypes.c_int
     L.fc_tree_attention.argtypes = [vp] * 9 + [i32] * 6 + [ctypes.c_float, vp, vp]
+    L.fc_tree_attention_workspace_bytes.restype = sz
+    L.fc_tree_attention_workspace_bytes.argtypes = [i32] * 4
+    L.fc_tree_attention_ws.restype = ctypes.c_int
+    L.fc_tree_attention_ws.argtypes = [vp] * 9 + [i32] * 6 + [ctypes.c_float, vp, vp, sz, vp]
     L.fc_build_tree_workspace_bytes.restype = sz
     L.fc_build_tree_workspace_bytes.argtypes = [i32]
     L.fc_build_tree.restype = ctypes.c_int
@@ -554,9 +558,16 @@ def fc_tree_attention(q: torch.Tensor, k_tree: torch.Tensor, v_tree: torch.Tenso
     if out is None:
         out = _empty((B, R, H, D), torch.float32, q.device)
     u16 = lambda t: _ptr(t.view(torch.uint16))  # noqa: E731
-    _check("fc_tree_attention", lib().fc_tree_attention(
+    need = int(lib().fc_tree_attention_workspace_bytes(B, R, H, Pmax))
+    ws = None
+    if need > 0:
+        ws = _empty(need, torch.uint8, q.device)
+        if stream is not None:
+            ws.record_stream(stream)  # it is used there, and freed here
+    _check("fc_tree_attention", lib().fc_tree_attention_ws(
         u16(q), u16(k_tree), u16(v_tree), u16(k_cache), u16(v_cache), _ptr(prefix_len), _ptr(tree["num_nodes"]),
-        _ptr(tree["mask"]), _ptr(tree["pos_ids"]), B, R, H, Hkv, D, Pmax, rope_base, _ptr(out), _stream(stream)))
+        _ptr(tree["mask"]), _ptr(tree["pos_ids"]), B, R, H, Hkv, D, Pmax, rope_base, _ptr(out), _ptr(ws), need,
+        _stream(stream)))
     return out
 
 

@@ -25,9 +25,15 @@
 // the score product reads K rows without bank conflicts and the value
 // product takes V^T with the transposing LDS read (ds_read_b64_tr_b16),
 // which hands each lane four keys of one output dim.  The tree's own keys
-// are rotated on the way in, through registers.  Workgroups are numbered so
-// that the query heads sharing a key head run on the same XCD and its L2
-// serves their shared key/value reads.
+// are rotated on the way in, through registers, up to four blocks at once.
+// Workgroups are numbered so that the query heads sharing a key head run on
+// the same XCD and its L2 serves their shared key/value reads.
+//
+// A full batch is bound by HBM (64 trees x 32 heads, 2,048 keys: 490 us, 4.7
+// TB/s of keys and values; 510 before the query rows' loads went ahead of
+// everything else and the tree's blocks were staged together).  A few trees
+// leave CUs idle: their prefixes are cut into parts (part_count), merged by
+// k_tree_merge.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -47,32 +53,36 @@ constexpr int kBlock = 32;                  // keys per block
 constexpr int kRowBytes = kD * 2;           // 256: one key row
 constexpr int kPart = kBlock * kRowBytes;   // 8 KB: a block's keys (or values)
 constexpr int kStage = 2 * kPart;           // keys then values
-constexpr int kStages = 4;                  // ring depth
 constexpr int kDTiles = kD / 16;            // output tiles of 16 dims
 constexpr int kDSteps = kD / 32;            // 32-dim steps of the score product
 constexpr int kDmaWaves = 4;                // waves issuing a block's 16 loads, 4 each
 constexpr int kXcds = 8;
+
+constexpr int kStages = 4;                  // ring depth
+constexpr int kTreeBlocks = 4;              // tree blocks staged at once
+
+// the e-th key of a block that a lane of group lg holds scores of
+__device__ __forceinline__ int key_of(int lg, int e) { return e < 4 ? 4 * lg + e : 16 + 4 * lg + (e - 4); }
 
 __device__ __forceinline__ __bf16 f2bf(float x) { return (__bf16)x; }
 
 // byte offset inside a block part of 16-byte chunk c of row r (swizzled)
 __device__ __forceinline__ uint32_t chunk_at(int r, int c) { return (uint32_t)(r * kRowBytes + ((c ^ (r & 15)) << 4)); }
 
-// sin and cos of the rotary angle position * base^(-2d/D) of the pair (d,
-// d + D/2).  The angle is taken in revolutions and reduced to [0, 1) in
-// double precision, so large positions keep full accuracy; the hardware
-// sine and cosine then take revolutions directly.
-__device__ __forceinline__ void rope_sincos(int pos, int d, double log2_base, float& s, float& c) {
+// sin and cos of the rotary angle position * freq, freq = base^(-2d/D) of
+// the pair (d, d + D/2).  The angle is taken in revolutions and reduced to
+// [0, 1) in double precision, so large positions keep full accuracy; the
+// hardware sine and cosine then take revolutions directly.
+__device__ __forceinline__ void rope_sincos(int pos, double freq, float& s, float& c) {
   constexpr double kInv2Pi = 0.15915494309189533577;
-  const double rev = (double)pos * exp2(-2.0 * (double)d / (double)kD * log2_base) * kInv2Pi;
+  const double rev = (double)pos * freq * kInv2Pi;
   const float f = (float)(rev - floor(rev));
   s = __builtin_amdgcn_sinf(f);
   c = __builtin_amdgcn_cosf(f);
 }
 
-// 8 bf16 (16 bytes) at p as floats.
-__device__ __forceinline__ void load8(const uint16_t* __restrict__ p, float (&v)[8]) {
-  const uint4 u = *(const uint4*)p;
+// 8 bf16 as floats.
+__device__ __forceinline__ void unpack8(const uint4& u, float (&v)[8]) {
   const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -81,14 +91,19 @@ __device__ __forceinline__ void load8(const uint16_t* __restrict__ p, float (&v)
   }
 }
 
-template <int MAXT>
-__global__ void __launch_bounds__(MAXT) k_tree_attn(
+// kSplit: workgroup blockIdx.y of gridDim.y takes an equal share of the
+// prefix's blocks (the last one the tree's rows instead) and leaves its rows'
+// running maxima, weight sums and unnormalised outputs in part_ml and part_o
+// for k_tree_merge.
+template <int MAXT, bool kSplit>
+__global__ void __launch_bounds__(MAXT, kSplit && MAXT == 512 ? 2 : 4) k_tree_attn(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_tree, const uint16_t* __restrict__ v_tree,
     const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ num_nodes, const int32_t* __restrict__ mask,
     const int32_t* __restrict__ pos_ids, int B, int R, int H, int Hkv, int Pmax, double log2_base,
-    float* __restrict__ out) {
+    float* __restrict__ out, float2* __restrict__ part_ml, float* __restrict__ part_o) {
   __shared__ __align__(16) uint8_t s_ring[kStages * kStage];
+  __shared__ double s_freq[kD / 2];  // rotary frequencies: one double-precision power per pair and workgroup
 
   // workgroup -> (tree, head): consecutive ids on one XCD when the count
   // divides evenly, so the heads of one key head share an L2
@@ -98,13 +113,36 @@ __global__ void __launch_bounds__(MAXT) k_tree_attn(
   const int b = lin / H, h = lin - (lin / H) * H;
   const int g_kv = h / (H / Hkv);
   const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
-  const int lane = fc::lane_id(), w = tid / fc::kWave;
+  const int lane = fc::lane_id(), w = __builtin_amdgcn_readfirstlane(tid / fc::kWave);
   const int lg = lane >> 4, lc = lane & 15;  // lane group (0..3), lane column (0..15)
+  // this lane's query row, on its way first
+  const int qr = w * 16 + lc;
+  const bool q_in = qr < R;
+  uint4 q_raw[kDSteps];
+  int q_pos = 0;
+  if (q_in) {
+    const uint16_t* src = q + (((int64_t)b * R + qr) * H + h) * kD + 8 * lg;
+#pragma unroll
+    for (int kc = 0; kc < kDSteps; ++kc) q_raw[kc] = *(const uint4*)(src + 32 * kc);
+    q_pos = pos_ids[(int64_t)b * R + qr];
+  } else {
+#pragma unroll
+    for (int kc = 0; kc < kDSteps; ++kc) q_raw[kc] = make_uint4(0u, 0u, 0u, 0u);
+  }
   // lengths from the device are clamped to the buffers (a malformed tree,
   // num_nodes = -1, has no rows)
   const int P = prefix_len[b] < 0 ? 0 : (prefix_len[b] > Pmax ? Pmax : prefix_len[b]);
   const int n = num_nodes[b] < 0 ? 0 : (num_nodes[b] > R ? R : num_nodes[b]);
   const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)s_ring;
+
+  // this workgroup's prefix blocks [blk0, n_pre) and tree blocks
+  const int n_all = (P + kBlock - 1) / kBlock;
+  const int part = kSplit ? (int)blockIdx.y : 0, parts = kSplit ? (int)gridDim.y - 1 : 1;
+  const int blk0 = kSplit ? (int)((uint32_t)n_all * (uint32_t)part / (uint32_t)parts) : 0;  // n_all < 2^26
+  const int n_pre = !kSplit ? n_all
+                    : part < parts ? (int)((uint32_t)n_all * (uint32_t)(part + 1) / (uint32_t)parts) : blk0;
+  const int n_tree = !kSplit || part == parts ? (n + kBlock - 1) / kBlock : 0;
+  const int key_end = P < n_pre * kBlock ? P : n_pre * kBlock;
 
   // Prefix block loads: load u (0..15) of a block covers rows 4(u%8) ..
   // 4(u%8)+3 of the keys (u < 8) or values; lane L takes row 4(u%8) + L/16
@@ -115,7 +153,7 @@ __global__ void __launch_bounds__(MAXT) k_tree_attn(
   const fc::int32x4 rk = fc::buffer_rsrc(k_cache + ((int64_t)b * Pmax * Hkv + g_kv) * kD, pre_bytes);
   const fc::int32x4 rv = fc::buffer_rsrc(v_cache + ((int64_t)b * Pmax * Hkv + g_kv) * kD, pre_bytes);
   const bool dma_wave = w < kDmaWaves;
-  auto issue_block = [&](int blk) {  // rows past P (also whole blocks past the prefix) read as zeros
+  auto issue_block = [&](int blk) {  // rows past key_end (also whole blocks) read as zeros, from no memory
     if (!dma_wave) return;
     const uint32_t slot = ring + (uint32_t)((blk % kStages) * kStage);
 #pragma unroll
@@ -124,32 +162,35 @@ __global__ void __launch_bounds__(MAXT) k_tree_attn(
       const int r = 4 * (u & 7) + (lane >> 4);
       const int c = (lane & 15) ^ (r & 15);
       const int64_t key = (int64_t)blk * kBlock + r;
-      const uint32_t voff = key < P ? (uint32_t)(key * row_stride + 16 * c) : pre_bytes;
+      const uint32_t voff = key < key_end ? (uint32_t)(key * row_stride + 16 * c) : pre_bytes;
       fc::lds_load16(slot + (u < 8 ? 0u : (uint32_t)kPart) + (uint32_t)(u & 7) * 1024u, voff, u < 8 ? rk : rv);
     }
   };
 
-  // this lane's query row and its rotated dims as the B operand of S^T
-  const int qr = w * 16 + lc;
-  const bool q_in = qr < R;
+  for (int d = tid; d < kD / 2; d += nt) s_freq[d] = exp2(-2.0 * (double)d / (double)kD * log2_base);
+
+  // the first prefix blocks on their way
+#pragma unroll
+  for (int u = 0; u < kStages - 1; ++u) issue_block(blk0 + u);
+  // the frequencies are in LDS; the loads in flight are not waited for
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
+  // the query row's rotated dims as the B operand of S^T
   bf16x8 qf[kDSteps];
   {
     float v[kDSteps][8];
 #pragma unroll
-    for (int kc = 0; kc < kDSteps; ++kc) {
-      if (q_in) load8(q + (((int64_t)b * R + qr) * H + h) * kD + 32 * kc + 8 * lg, v[kc]);
-      else
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[kc][e] = 0.0f;
-    }
-    const int pos = P + (q_in ? pos_ids[(int64_t)b * R + qr] : 0);
+    for (int kc = 0; kc < kDSteps; ++kc) unpack8(q_raw[kc], v[kc]);
+    const int pos = P + q_pos;
 #pragma unroll
     for (int kc = 0; kc < kDSteps / 2; ++kc)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         // dims d and d + D/2 sit in steps kc and kc + 2 of the same lane
         float s, c;
-        rope_sincos(pos, 32 * kc + 8 * lg + e, log2_base, s, c);
+        rope_sincos(pos, s_freq[32 * kc + 8 * lg + e], s, c);
         const float x0 = v[kc][e], x1 = v[kc + 2][e];
         v[kc][e] = x0 * c - x1 * s;
         v[kc + 2][e] = x1 * c + x0 * s;
@@ -167,9 +208,8 @@ __global__ void __launch_bounds__(MAXT) k_tree_attn(
   const float scale = 1.0f / sqrtf((float)kD);
 
   // One block of the two products from the K and V parts at slot_off (a byte
-  // offset in s_ring); `tree` blocks take the mask, prefix blocks only the
-  // prefix bound.
-  auto consume = [&](uint32_t slot_off, int base, int lim, bool tree) {
+  // offset in s_ring); bit e of `allow` admits this lane's e-th key.
+  auto consume = [&](uint32_t slot_off, uint32_t allow) {
     const uint8_t* sk = s_ring + slot_off;
     floatx4 st0 = {0.0f, 0.0f, 0.0f, 0.0f}, st1 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -183,10 +223,7 @@ __global__ void __launch_bounds__(MAXT) k_tree_attn(
     float sv[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int kk = e < 4 ? 4 * lg + e : 16 + 4 * lg + (e - 4);
-      const int j = base + kk;
-      bool ok = j < lim && q_in;
-      if (ok && tree) ok = qr < n && mask[((int64_t)b * R + qr) * R + j] == 1;
+      const bool ok = (allow >> e) & 1u;
       const float raw = e < 4 ? st0[e] : st1[e - 4];
       sv[e] = ok ? raw * scale : -INFINITY;
     }
@@ -228,39 +265,57 @@ __global__ void __launch_bounds__(MAXT) k_tree_attn(
   };
 
   // the cached prefix: a ring of kStages blocks, kStages - 1 in flight
-  const int n_pre = (P + kBlock - 1) / kBlock, n_tree = (n + kBlock - 1) / kBlock;
-#pragma unroll
-  for (int blk = 0; blk < kStages - 1; ++blk) issue_block(blk);
-  for (int blk = 0; blk < n_pre; ++blk) {
+  for (int blk = blk0; blk < n_pre; ++blk) {
     // this wave's loads of block blk are done once at most the loads of the
     // kStages - 2 later blocks (4 each) are outstanding; the barrier makes every
     // wave's visible, and frees the slot the next issue overwrites
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (kStages - 2)) : "memory");
     __syncthreads();
     issue_block(blk + kStages - 1);
-    consume((uint32_t)((blk % kStages) * kStage), blk * kBlock, P, false);
+    uint32_t allow = q_in ? 0xFFu : 0u;
+    if (blk == n_all - 1) {  // the prefix may end inside the block
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (blk * kBlock + key_of(lg, e) >= P) allow &= ~(1u << e);
+    }
+    consume((uint32_t)((blk % kStages) * kStage), allow);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
   // the tree's rows: keys rotated by their positions, values as they are,
-  // staged through registers into slot 0
-  for (int tb = 0; tb < n_tree; ++tb) {
-    const int base = tb * kBlock;
-    uint8_t* sk = s_ring;
-    for (int it = tid; it < kBlock * (kD / 16); it += nt) {
-      const int kk = it / (kD / 16), c = it - kk * (kD / 16);  // key, chunks c and c + D/16
-      const int j = base + kk;
+  // through registers into the ring, kTreeBlocks blocks at a time, so that
+  // their loads and the mask's are waited for once
+  constexpr int kMaskUnroll = kSplit && MAXT == 512 ? kTreeBlocks : 1;  // one part: two workgroups share the registers
+  for (int tb0 = 0; tb0 < n_tree; tb0 += kTreeBlocks) {
+    const int nb = n_tree - tb0 < kTreeBlocks ? n_tree - tb0 : kTreeBlocks;
+    uint32_t allow = 0;  // eight bits per block
+#pragma unroll kMaskUnroll
+    for (int u = 0; u < nb; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int j = (tb0 + u) * kBlock + key_of(lg, e);
+        if (j < n && qr < n && mask[((int64_t)b * R + qr) * R + j] == 1) allow |= 1u << (8 * u + e);
+      }
+    for (int it = tid; it < nb * kBlock * (kD / 16); it += nt) {
+      const int row = it / (kD / 16), c = it - row * (kD / 16);  // key, chunks c and c + D/16
+      const int j = tb0 * kBlock + row;
+      uint8_t* sk = s_ring + (row / kBlock) * kStage;
       float a[8], bb[8];
+      uint4 k0 = make_uint4(0u, 0u, 0u, 0u), k1 = k0, v0 = k0, v1 = k0;
       if (j < n) {
-        const uint16_t* src = k_tree + (((int64_t)b * R + j) * Hkv + g_kv) * kD;
-        load8(src + 8 * c, a);
-        load8(src + kD / 2 + 8 * c, bb);
+        const int64_t src = (((int64_t)b * R + j) * Hkv + g_kv) * kD;
+        k0 = *(const uint4*)(k_tree + src + 8 * c);
+        k1 = *(const uint4*)(k_tree + src + kD / 2 + 8 * c);
+        v0 = *(const uint4*)(v_tree + src + 8 * c);
+        v1 = *(const uint4*)(v_tree + src + kD / 2 + 8 * c);
         const int pos = P + pos_ids[(int64_t)b * R + j];
+        unpack8(k0, a);
+        unpack8(k1, bb);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           float sn, cs;
-          rope_sincos(pos, 8 * c + e, log2_base, sn, cs);
+          rope_sincos(pos, s_freq[8 * c + e], sn, cs);
           const float x0 = a[e], x1 = bb[e];
           a[e] = x0 * cs - x1 * sn;
           bb[e] = x1 * cs + x0 * sn;
@@ -275,24 +330,29 @@ __global__ void __launch_bounds__(MAXT) k_tree_attn(
         pa[e] = f2bf(a[e]);
         pbb[e] = f2bf(bb[e]);
       }
+      const int kk = row % kBlock;
       *(bf16x8*)(sk + chunk_at(kk, c)) = pa;
       *(bf16x8*)(sk + chunk_at(kk, c + kD / 16)) = pbb;
-    }
-    for (int it = tid; it < kBlock * (kD / 8); it += nt) {
-      const int kk = it / (kD / 8), c = it - kk * (kD / 8);
-      const int j = base + kk;
-      uint4 v = make_uint4(0u, 0u, 0u, 0u);
-      if (j < n) v = *(const uint4*)(v_tree + (((int64_t)b * R + j) * Hkv + g_kv) * kD + 8 * c);
-      *(uint4*)(sk + kPart + chunk_at(kk, c)) = v;
+      *(uint4*)(sk + kPart + chunk_at(kk, c)) = v0;
+      *(uint4*)(sk + kPart + chunk_at(kk, c + kD / 16)) = v1;
     }
     __syncthreads();
-    consume(0u, base, n, true);
+    for (int u = 0; u < nb; ++u) consume((uint32_t)(u * kStage), (allow >> (8 * u)) & 0xFFu);
     __syncthreads();
   }
 
   // normalise by the row's total weight (summed over the four lane groups)
   float lt = l_run + __shfl_xor(l_run, 16);
   lt = lt + __shfl_xor(lt, 32);
+  if (kSplit) {
+    if (q_in) {
+      const int64_t row = ((int64_t)(b * H + h) * gridDim.y + blockIdx.y) * R + qr;
+      if (lg == 0) part_ml[row] = make_float2(m_run, lt);
+#pragma unroll
+      for (int t = 0; t < kDTiles; ++t) *(floatx4*)(part_o + row * kD + 16 * t + 4 * lg) = o[t];
+    }
+    return;
+  }
   if (q_in) {
     const bool live = qr < n && lt > 0.0f;
     const float inv = live ? 1.0f / lt : 0.0f;
@@ -305,13 +365,97 @@ __global__ void __launch_bounds__(MAXT) k_tree_attn(
   }
 }
 
+// The parts of a split row put together: out = sum_s e^(m_s - m) o_s / sum_s
+// e^(m_s - m) l_s with m the largest m_s.  32 lanes per (row, head), four dims
+// each, every part's loads issued before any is used; a row at or past
+// num_nodes[b] is 0.
+template <int kMost>
+__global__ void __launch_bounds__(256) k_tree_merge(const float2* __restrict__ part_ml,
+                                                      const float* __restrict__ part_o,
+                                                      const int32_t* __restrict__ num_nodes, int B, int R, int H,
+                                                      int parts, float* __restrict__ out) {
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5;  // (b, row, h)
+  if (i >= (int64_t)B * R * H) return;
+  const int d = 4 * (int)(threadIdx.x & 31);
+  const int h = (int)(i % H), qr = (int)(i / H % R), b = (int)(i / H / R);
+  const int64_t row0 = (int64_t)(b * H + h) * parts * R + qr;
+  float2 ml[kMost];
+  floatx4 o[kMost];
+#pragma unroll
+  for (int s = 0; s < kMost; ++s) {
+    ml[s] = s < parts ? part_ml[row0 + (int64_t)s * R] : make_float2(-INFINITY, 0.0f);
+    o[s] = s < parts ? *(const floatx4*)(part_o + (row0 + (int64_t)s * R) * kD + d) : floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  float m = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < kMost; ++s) m = fmaxf(m, ml[s].x);
+  floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  float l = 0.0f;
+#pragma unroll
+  for (int s = 0; s < kMost; ++s) {
+    const float w = ml[s].x > -INFINITY ? __expf(ml[s].x - m) : 0.0f;  // 0 for a part without an allowed key
+    l += w * ml[s].y;
+    acc += w * o[s];
+  }
+  acc *= qr < num_nodes[b] && l > 0.0f ? 1.0f / l : 0.0f;
+  *(floatx4*)(out + i * kD + d) = acc;
+}
+
+// Workgroups per (tree, head): 1, or parts - 1 for the prefix and one for the
+// tree's rows.  A workgroup walks its prefix at about 1 us per block of 32
+// keys (a chain of LDS reads, products and a softmax step), so with few
+// (tree, head) pairs most of the chip idles while that chain runs.  Parts
+// are added up to a workgroup per CU: past that, two share a CU and gain
+// nothing (1 tree x 32 heads, 3,000 keys: 92 us in one part, 50 in 3, 31 in
+// 5, 24.7 in 8, 35 in 10).  Three parts still pay while the workgroups are all
+// resident, two per CU (128 pairs, 2,048 keys: 71 -> 49 us; 160 pairs, 773
+// keys: 28.9 -> 25.9), and no longer at 256 pairs (73 -> 87).  A part takes two
+// blocks or more, and a prefix under 8 blocks stays whole: the merge costs
+// about 4 us.
+constexpr int kCus = 256;
+constexpr int kMaxParts = 16;
+int part_count(int32_t B, int32_t H, int32_t Pmax) {
+  const int64_t wgs = (int64_t)B * H, blocks = ((int64_t)Pmax + kBlock - 1) / kBlock;
+  if (3 * wgs > 2 * kCus || blocks < 8) return 1;
+  int64_t parts = kCus / wgs;
+  if (parts < 3) parts = 3;
+  if (parts > kMaxParts) parts = kMaxParts;
+  if (parts > blocks / 2 + 1) parts = blocks / 2 + 1;
+  return (int)parts;
+}
+
+size_t carve_parts(void* p, int32_t B, int32_t R, int32_t H, int parts, float2** ml, float** o) {
+  fc::Carver c(p);
+  const size_t rows = (size_t)B * H * parts * R;
+  *ml = c.take<float2>(rows);
+  *o = c.take<float>(rows * kD);
+  return c.used + 256;
+}
+
 }  // namespace
+
+extern "C" size_t fc_tree_attention_workspace_bytes(int32_t B, int32_t R, int32_t H, int32_t Pmax) {
+  if (B < 1 || R < 1 || R > FC_MAX_TREE_ROWS || H < 1 || Pmax < 0) return 0;
+  const int parts = part_count(B, H, Pmax);
+  float2* ml;
+  float* o;
+  return parts > 1 ? carve_parts(nullptr, B, R, H, parts, &ml, &o) : 0;
+}
 
 extern "C" fc_status fc_tree_attention(const uint16_t* q, const uint16_t* k_tree, const uint16_t* v_tree,
                                        const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* prefix_len,
                                        const int32_t* num_nodes, const int32_t* mask, const int32_t* pos_ids,
                                        int32_t B, int32_t R, int32_t H, int32_t Hkv, int32_t D, int32_t Pmax,
                                        float rope_base, float* out, hipStream_t stream) {
+  return fc_tree_attention_ws(q, k_tree, v_tree, k_cache, v_cache, prefix_len, num_nodes, mask, pos_ids, B, R, H, Hkv,
+                              D, Pmax, rope_base, out, nullptr, 0, stream);
+}
+
+extern "C" fc_status fc_tree_attention_ws(const uint16_t* q, const uint16_t* k_tree, const uint16_t* v_tree,
+                                       const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* prefix_len,
+                                       const int32_t* num_nodes, const int32_t* mask, const int32_t* pos_ids,
+                                       int32_t B, int32_t R, int32_t H, int32_t Hkv, int32_t D, int32_t Pmax,
+                                       float rope_base, float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
   if (B < 0 || R < 1 || R > FC_MAX_TREE_ROWS || H < 1 || Hkv < 1 || H % Hkv != 0 || Pmax < 0) return FC_ERR_INVALID;
   if (!(rope_base > 1.0f)) return FC_ERR_INVALID;
   if (D != FC_TREE_ATTN_HEAD_DIM) return FC_ERR_UNSUPPORTED;
@@ -325,16 +469,40 @@ extern "C" fc_status fc_tree_attention(const uint16_t* q, const uint16_t* k_tree
   if ((int64_t)Pmax * Hkv * D * 2 >= (int64_t)1 << 32) return FC_ERR_UNSUPPORTED;
   const int rows_waves = (R + 15) / 16;
   const int waves = rows_waves < 4 ? 4 : rows_waves;  // at least 256 threads stage a block
-  const dim3 grid((uint32_t)B * (uint32_t)H), block(waves * fc::kWave);
+  int parts = part_count(B, H, Pmax);
+  float2* ml = nullptr;
+  float* po = nullptr;
+  if (parts > 1) {
+    if (!ws || ws_bytes < fc_tree_attention_workspace_bytes(B, R, H, Pmax)) {
+      parts = 1;
+    } else {
+      if ((uintptr_t)ws & 15) return FC_ERR_INVALID;
+      carve_parts(ws, B, R, H, parts, &ml, &po);
+    }
+  }
+  const dim3 grid((uint32_t)B * (uint32_t)H, (uint32_t)parts), block(waves * fc::kWave);
   (void)hipGetLastError();
+#define FC_ATTN(T, SPLIT)                                                                                              \
+  hipLaunchKernelGGL((k_tree_attn<T, SPLIT>), grid, block, 0, stream, q, k_tree, v_tree, k_cache, v_cache, prefix_len, \
+                     num_nodes, mask, pos_ids, B, R, H, Hkv, Pmax, log2((double)rope_base), out, ml, po)
   // trees of up to 128 rows (c <= 127) in workgroups of at most 8 waves,
   // which leaves each lane the registers the accumulators need
-  if (waves <= 8)
-    hipLaunchKernelGGL(k_tree_attn<512>, grid, block, 0, stream, q, k_tree, v_tree, k_cache, v_cache, prefix_len,
-                       num_nodes, mask, pos_ids, B, R, H, Hkv, Pmax, log2((double)rope_base), out);
-  else
-    hipLaunchKernelGGL(k_tree_attn<1024>, grid, block, 0, stream, q, k_tree, v_tree, k_cache, v_cache, prefix_len,
-                       num_nodes, mask, pos_ids, B, R, H, Hkv, Pmax, log2((double)rope_base), out);
+  if (waves <= 8 && parts == 1) FC_ATTN(512, false);
+  else if (waves <= 8) FC_ATTN(512, true);
+  else if (parts == 1) FC_ATTN(1024, false);
+  else FC_ATTN(1024, true);
+#undef FC_ATTN
   FC_CHECK_LAUNCH();
+  if (parts > 1) {
+    const dim3 mgrid(fc::div_up((uint64_t)B * R * H * 32, 256));
+    if (parts <= 4)
+      hipLaunchKernelGGL(k_tree_merge<4>, mgrid, dim3(256), 0, stream, ml, po, num_nodes, B, R, H, parts, out);
+    else if (parts <= 8)
+      hipLaunchKernelGGL(k_tree_merge<8>, mgrid, dim3(256), 0, stream, ml, po, num_nodes, B, R, H, parts, out);
+    else
+      hipLaunchKernelGGL(k_tree_merge<kMaxParts>, mgrid, dim3(256), 0, stream, ml, po, num_nodes, B, R, H, parts,
+                         out);
+    FC_CHECK_LAUNCH();
+  }
   return FC_OK;
 }

@@ -1133,3 +1133,53 @@ def test_tree_attention_masks_and_edge_cases():
     err, bound = _tree_attention_case(trees, list(range(0, 24)), 2, 2, [0] * 24, 0, 11, qscale=3.0)
     assert (err[5] == 0).all()
     err, bound = _tree_attention_case(trees, list(range(24, 32)), 2, 1, [4000] * 8, 4000, 12, base=1e6)
+
+
+@pytest.mark.parametrize("R,P,Pmax", [
+    (1, (0, 0), 0), (17, (0, 31), 33), (65, (224, 7), 224), (65, (225, 32), 225), (65, (1000, 3001), 3001),
+    (65, (5, 4096), 4096),
+    (129, (700, 64), 777),
+])
+def test_tree_attention_in_parts_matches_one_part(R, P, Pmax):
+    """Few trees: fc_tree_attention_ws cuts each prefix into parts (some of
+    them empty, where a prefix is far below Pmax); fc_tree_attention and a
+    workspace that is too small run in one.  Both round the same operands to
+    bf16 and add in fp32; a part's weights are taken against its own largest
+    score, so a weight's bf16 rounding (2^-9 relative, 2^-8 between the two) is
+    what may differ: at most 2^-8 max|v|, plus fp32 sums."""
+    rng = np.random.default_rng(R + Pmax)
+    B, H, Hkv, D = 2, 4, 2, fc.FC_TREE_ATTN_HEAD_DIM
+    parent = np.array([[-1] + [int(rng.integers(max(0, i - 3), i)) for i in range(1, R)] for _ in range(B)])
+    mask = np.zeros((B, R, R), np.int32)
+    pos = np.zeros((B, R), np.int32)
+    for b in range(B):
+        for i in range(R):
+            if i:
+                mask[b, i] = mask[b, parent[b, i]]
+                pos[b, i] = pos[b, parent[b, i]] + 1
+            mask[b, i, i] = 1
+    trees = dict(num_nodes=np.array([R, max(1, R - 3)], np.int32), mask=mask, pos_ids=pos)
+    say(f"tree attention in parts R={R} P={P} Pmax={Pmax}")
+    _tree_attention_case(trees, [0, 1], H, Hkv, P, Pmax, R)
+    q, kt, vt = (_bf16(rng, B, R, h, D).cuda() for h in (H, Hkv, Hkv))
+    kc, vc = (_bf16(rng, B, max(Pmax, 1), Hkv, D).cuda() for _ in range(2))
+    t = {f: dev(v) for f, v in trees.items()}
+    Pn = dev(np.asarray(P, np.int32))
+    parts = host(fc.fc_tree_attention(q, kt, vt, kc, vc, Pn, t)).astype(np.float64)
+    L, ptr = fc.lib(), fc._ptr
+    need = L.fc_tree_attention_workspace_bytes(B, R, H, kc.shape[1])
+    assert (need > 0) == (Pmax > 224)  # seven blocks of 32 keys or fewer stay in one part
+    ws = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda")
+    one = torch.full((B, R, H, D), float("nan"), dtype=torch.float32, device="cuda")
+    small = one.clone()
+    args = [ptr(x.view(torch.uint16)) for x in (q, kt, vt, kc, vc)] + [ptr(Pn), ptr(t["num_nodes"]), ptr(t["mask"]),
+                                                                       ptr(t["pos_ids"])]
+    sizes = [B, R, H, Hkv, D, kc.shape[1], 10000.0]
+    assert L.fc_tree_attention(*args, *sizes, ptr(one), fc._stream(None)) == 0
+    assert L.fc_tree_attention_ws(*args, *sizes, ptr(small), ptr(ws), max(need - 1, 0), fc._stream(None)) == 0
+    if need > 0:
+        assert L.fc_tree_attention_ws(*args, *sizes, ptr(one), fc.ctypes.c_void_p(ws.data_ptr() + 4), need,
+                                      fc._stream(None)) == 1
+    torch.cuda.synchronize()
+    assert (host(one) == host(small)).all()
+    assert np.abs(parts - host(one)).max() <= 2.0 ** -8 * max(float(vc.abs().max()), float(vt.abs().max())) + 1e-5
