@@ -22,6 +22,11 @@ __device__ __forceinline__ uint64_t ballot(bool p) { return (uint64_t)__ballot(p
 // hardware takes multi-dword loads at dword alignment).
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
+// The same at any token of a text (two or four words at 2-byte alignment are
+// one load each too).
+typedef uint32_t u32_a2 __attribute__((aligned(2)));
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+
 // ---- DPP wave primitives (32-bit).  Within each row of 16 lanes values move
 // with DPP row shifts (plain VALU ops); rows are combined with readlane.
 // Lanes whose DPP source falls outside the row take the identity explicitly,

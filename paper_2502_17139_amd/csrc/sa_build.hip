@@ -1458,85 +1458,158 @@ constexpr uint32_t kMaxTokenBlocks = 1024;
 // Two-token table: suffix-array position r owns the table entries between
 // the previous suffix's pair key (exclusive) and its own (inclusive); keys
 // never decrease along the suffix array.  r = n owns the rest up to the
-// final entry.  Each wave takes 64 consecutive positions and writes their
-// ranges one after another with all 64 lanes, so long ranges are written
-// in coalesced runs.
-__global__ void __launch_bounds__(256) k_pairs(const uint16_t* __restrict__ tok, const uint32_t* __restrict__ sa,
-                                               uint32_t n, uint32_t V, uint32_t* __restrict__ pair) {
-  const uint64_t base = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) & ~(uint64_t)(fc::kWave - 1);
-  const int lane = fc::lane_id();
-  if (base > n) return;  // whole wave
-  const uint64_t end = (uint64_t)V * (V + 1);
-  auto key = [&](uint64_t rr) -> uint64_t {
-    if (rr >= n) return end;
-    const uint32_t j = sa[rr];
-    const uint64_t t0 = tok[j];
-    const uint64_t u = (uint64_t)j + 1 < n ? (uint64_t)tok[j + 1] + 1 : 0;
-    const uint64_t k = t0 * (V + 1) + u;
-    return k < end ? k : end;  // tokens >= V were rejected before launch
-  };
-  const uint64_t r = base + lane;
-  uint64_t hi = 0, lo = 1;  // empty unless r <= n
-  if (r <= n) {
-    hi = key(r);
-    lo = r == 0 ? 0 : key(r - 1) + 1;
+// final entry.
+struct PairKeys {
+  const uint16_t* __restrict__ tok;
+  const uint32_t* __restrict__ sa;
+  uint32_t n, V;
+  __device__ uint64_t end() const { return (uint64_t)V * (V + 1); }
+  __device__ uint32_t suffix(uint64_t r) const { return r < n ? sa[r] : 0u; }
+  // suffix j's first two tokens in one load (those of the text's last two for the last suffix)
+  __device__ uint32_t two(uint32_t j) const {
+    return *(const fc::u32_a2*)(tok + (j < n - 2 ? j : n - 2));
   }
-  for (int jl = 0; jl < fc::kWave; ++jl) {
-    const uint64_t l2 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(lo >> 32), jl) << 32) |
-                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)lo, jl);
-    const uint64_t h2 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(hi >> 32), jl) << 32) |
-                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)hi, jl);
-    const uint32_t val = (uint32_t)(base + jl);
-    for (uint64_t k = l2 + lane; k <= h2; k += fc::kWave) pair[k] = val;
+  // position r's key; tokens are < V (checked before the launch)
+  __device__ uint64_t key(uint64_t r, uint32_t j, uint32_t t) const {
+    const bool whole = j + 1 < n;
+    const uint64_t t0 = whole ? t & 0xFFFFu : t >> 16;
+    return r < n ? t0 * (V + 1) + (whole ? (t >> 16) + 1u : 0u) : end();
+  }
+};
+
+__device__ __forceinline__ uint64_t readlane64(uint64_t x, int l) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
+}
+
+// The ranges of the lanes whose key differs from the one before, one after
+// another with all 64 lanes, so long ranges are written in coalesced runs.
+// (A first key before ~0: entry 0 on.)
+__device__ __forceinline__ void write_pair_ranges(uint64_t key, uint64_t prev, uint32_t r, bool valid, int lane,
+                                                  uint32_t* __restrict__ pair) {
+  uint64_t heads = fc::ballot(valid && key != prev);
+  while (heads) {
+    const int l = __builtin_ctzll(heads);
+    heads &= heads - 1;
+    const uint64_t from = readlane64(prev, l) + 1, to = readlane64(key, l);
+    const uint32_t val = (uint32_t)__builtin_amdgcn_readlane((int)r, l);
+    for (uint64_t k = from + (uint64_t)lane; k <= to; k += fc::kWave) pair[k] = val;
   }
 }
 
-// Inline-prefix records: one thread per suffix-array position writes
-// {sa[i], T[sa[i]+2 .. sa[i]+32)} as four 16-byte stores (0 past the end).
-// The 60 text bytes come from five aligned 16-byte loads (the 80 bytes from
-// the 16-byte boundary at or below the first token), re-aligned in
-// registers; suffixes whose window would leave the text take token loads.
+// A one-token store: 0 up to its only key (its token, then nothing), 1 after it.
+__global__ void __launch_bounds__(256) k_pairs_one(PairKeys pk, uint32_t* __restrict__ pair) {
+  const uint64_t key = (uint64_t)pk.tok[0] * (pk.V + 1);
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k <= pk.end(); k += stride)
+    pair[k] = k <= key ? 0u : 1u;
+}
+
+// A small store's table (n >= 2): a wave reads 64 consecutive positions.
+__global__ void __launch_bounds__(256) k_pairs(PairKeys pk, uint32_t* __restrict__ pair) {
+  const uint64_t base = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) & ~(uint64_t)(fc::kWave - 1);
+  const int lane = fc::lane_id();
+  if (base > pk.n) return;  // whole wave
+  const uint64_t r = base + (uint64_t)lane, rb = base > 0 ? base - 1 : 0;
+  const uint32_t j = pk.suffix(r), jb = pk.suffix(rb);
+  const uint32_t t = pk.two(j), tb = pk.two(jb);
+  const uint64_t key = pk.key(r, j, t), before = base > 0 ? pk.key(rb, jb, tb) : ~0ull;
+  const uint64_t prev = ((uint64_t)fc::wave_shr1((uint32_t)(key >> 32), (uint32_t)(before >> 32)) << 32) |
+                        fc::wave_shr1((uint32_t)key, (uint32_t)before);
+  write_pair_ranges(key, prev, (uint32_t)r, r <= pk.n, lane, pair);
+}
+
+// A large store's: most neighbours share their pair, and a random 4-byte read
+// of the text moves a whole line, so a wave reads every kPairStep-th of 512
+// positions, and those between two only where they differ.  The groups
+// (p, p + kPairStep] of positions that need it are taken eight at a time.
+// 100M suffixes, 32,256 tokens (a 4.16 GB table): 1.75 ms; 2.55 with every
+// position read once, 3.64 with every position's two tokens read twice and 64
+// steps over ranges, most of them empty, per wave.  Below kPairSampleMin the
+// table's own size decides and 512 positions per wave are too few waves.
+constexpr int kPairStep = 8;
+constexpr uint32_t kPairSpan = fc::kWave * kPairStep;  // positions per wave
+constexpr uint64_t kPairSampleMin = 1ull << 23;        // suffixes
+__global__ void __launch_bounds__(256) k_pairs_sampled(PairKeys pk, uint32_t* __restrict__ pair) {
+  const uint64_t base = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / fc::kWave * kPairSpan;
+  const int lane = fc::lane_id();
+  if (base > pk.n) return;  // whole wave
+  // lane l: the position before its group, base - 1 + 8 l (position -1: ~0); and the wave's last position
+  const uint64_t r0 = base + (uint64_t)(lane * kPairStep), re = base + kPairSpan - 1;
+  const uint32_t j0 = pk.suffix(r0 > 0 ? r0 - 1 : 0), je = pk.suffix(re);
+  const uint32_t t0 = pk.two(j0), te = pk.two(je);
+  const uint64_t k0 = r0 > 0 ? pk.key(r0 - 1, j0, t0) : ~0ull, ke = pk.key(re, je, te);
+  uint64_t k1 = __shfl_down(k0, 1);
+  if (lane == fc::kWave - 1) k1 = ke;
+  uint64_t open = fc::ballot(k0 != k1);  // groups with a head
+  const int x = lane % kPairStep;
+  while (open) {
+    uint64_t rest = open;
+    int g = -1;
+#pragma unroll
+    for (int u = 0; u < fc::kWave / kPairStep; ++u) {
+      if (rest && lane / kPairStep == u) g = __builtin_ctzll(rest);
+      rest &= rest - 1;
+    }
+    open = rest;
+    const uint64_t r = base + (uint64_t)((g < 0 ? 0 : g) * kPairStep + x);
+    uint64_t first = __shfl(k0, g < 0 ? 0 : g), key = __shfl(k1, g < 0 ? 0 : g);  // every lane takes part
+    if (g >= 0 && x < kPairStep - 1) {
+      const uint32_t j = pk.suffix(r);
+      key = pk.key(r, j, pk.two(j));
+    }
+    const uint64_t below = ((uint64_t)fc::wave_shr1((uint32_t)(key >> 32), 0u) << 32) | fc::wave_shr1((uint32_t)key, 0u);
+    write_pair_ranges(key, x == 0 ? first : below, (uint32_t)r, g >= 0 && r <= pk.n, lane, pair);
+  }
+}
+
+// Inline-prefix records {sa[i], T[sa[i]+2 .. sa[i]+32)}: the 64 bytes of text
+// at the suffix with its first two tokens replaced by the suffix's index.
+// Four lanes per record, one 16-byte piece each: the four loads fall on the
+// record's own 64 bytes of text (at the text's 2-byte alignment) and a wave's
+// store covers 1 KB of consecutive records.  Each thread takes kRecRun
+// pieces, their loads issued together; pieces that leave the text are read
+// token by token, 0 past the end.  Bound by the random lines read (about 1.5
+// of 128 bytes a record) next to the 64 bytes written: 100M records 3.52 ms,
+// 7.2 TB/s of both (4.30 with a record per lane, where every load and store
+// touched 64 places; stores marked non-temporal: no change).
+constexpr int kRecRun = 4;
+constexpr uint32_t kRecBlock = 64 * kRecRun;  // records per workgroup
+
 __global__ void __launch_bounds__(256) k_records(const uint16_t* __restrict__ tok, const uint32_t* __restrict__ sa,
                                                  uint32_t n, uint4* __restrict__ rec) {
   static_assert(FC_RECORD_BYTES == 64 && FC_RECORD_TOKENS == 30, "record layout");
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t j = sa[i];
-  uint32_t w[16];
-  w[0] = j;
-  const uintptr_t base = (uintptr_t)tok;
-  const uintptr_t first = base + 2 * ((uint64_t)j + 2);
-  const uintptr_t lo = first & ~(uintptr_t)15;
-  if (lo >= base && lo + 80 <= base + 2 * (uint64_t)n) {
-    uint32_t d[20];
+  const uint32_t piece = threadIdx.x & 3;
+  const uint64_t i0 = (uint64_t)blockIdx.x * kRecBlock + threadIdx.x / 4;
+  uint32_t j[kRecRun];
 #pragma unroll
-    for (int u = 0; u < 5; ++u) {
-      const uint4 v = ((const uint4*)lo)[u];
-      d[4 * u] = v.x;
-      d[4 * u + 1] = v.y;
-      d[4 * u + 2] = v.z;
-      d[4 * u + 3] = v.w;
-    }
-    const uint32_t off = (uint32_t)(first - lo);  // 0, 2, .., 14 bytes
-    const uint32_t q = off >> 2, half = off & 2;
+  for (int u = 0; u < kRecRun; ++u) j[u] = i0 + 64 * u < n ? sa[i0 + 64 * u] : 0u;
+  fc::u32x4_a2 v[kRecRun];
+  const uint32_t last = n < 8 ? 0u : n - 8;  // the last whole piece
+  if (n >= 8) {
 #pragma unroll
-    for (int x = 0; x < FC_RECORD_TOKENS / 2; ++x) {
-      // the dword starting at byte off + 4x: dwords q + x and q + x + 1
-      const uint32_t a0 = q == 0 ? d[x] : q == 1 ? d[x + 1] : q == 2 ? d[x + 2] : d[x + 3];
-      const uint32_t a1 = q == 0 ? d[x + 1] : q == 1 ? d[x + 2] : q == 2 ? d[x + 3] : d[x + 4];
-      w[1 + x] = half ? __builtin_amdgcn_alignbyte(a1, a0, 2) : a0;
-    }
-  } else {
-#pragma unroll
-    for (int x = 0; x < FC_RECORD_TOKENS / 2; ++x) {
-      const uint64_t p = (uint64_t)j + 2 + 2 * x;
-      const uint32_t a = p < n ? tok[p] : 0u;
-      const uint32_t b = p + 1 < n ? tok[p + 1] : 0u;
-      w[1 + x] = a | (b << 16);
+    for (int u = 0; u < kRecRun; ++u) {
+      const uint64_t p = (uint64_t)j[u] + 8 * piece;
+      v[u] = *(const fc::u32x4_a2*)(tok + (p < last ? p : last));
     }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) rec[4 * i + u] = make_uint4(w[4 * u], w[4 * u + 1], w[4 * u + 2], w[4 * u + 3]);
+  for (int u = 0; u < kRecRun; ++u) {
+    const uint64_t i = i0 + 64 * u;
+    if (i >= n) continue;
+    const uint64_t p = (uint64_t)j[u] + 8 * piece;
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    if (n >= 8 && p <= last) {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) w[x] = v[u][x];
+    } else {
+#pragma unroll
+      for (int x = 0; x < 8; ++x)
+        if (p + x < n) w[x / 2] |= (uint32_t)tok[p + x] << (16 * (x & 1));
+    }
+    if (piece == 0) w[0] = j[u];
+    rec[4 * i + piece] = make_uint4(w[0], w[1], w[2], w[3]);
+  }
 }
 
 struct BuildWs {
@@ -2054,9 +2127,13 @@ extern "C" fc_status fc_store_prepare_pairs(const uint16_t* tokens, const uint32
     FC_CHECK_HIP(hipMemsetAsync(pair_out, 0, sizeof(uint32_t) * fc_pair_table_entries(V), stream));
     return FC_OK;
   }
-  const uint64_t threads = n + 1;
-  hipLaunchKernelGGL(k_pairs, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, stream, tokens, sa,
-                     (uint32_t)n, V, pair_out);
+  const PairKeys pk{tokens, sa, (uint32_t)n, V};
+  if (n < 2)
+    hipLaunchKernelGGL(k_pairs_one, dim3(1024), dim3(256), 0, stream, pk, pair_out);
+  else if (n < kPairSampleMin)
+    hipLaunchKernelGGL(k_pairs, dim3(fc::div_up(n + 1, 256)), dim3(256), 0, stream, pk, pair_out);
+  else
+    hipLaunchKernelGGL(k_pairs_sampled, dim3(fc::div_up(n + 1, 4 * kPairSpan)), dim3(256), 0, stream, pk, pair_out);
   FC_CHECK_LAUNCH();
   return FC_OK;
 }
@@ -2100,7 +2177,7 @@ extern "C" fc_status fc_store_prepare_records(const uint16_t* tokens, const uint
   if (n == 0) return FC_OK;
   if (!tokens || !sa || !rec_out || ((uintptr_t)rec_out & (FC_RECORD_BYTES - 1))) return FC_ERR_INVALID;
   (void)hipGetLastError();
-  hipLaunchKernelGGL(k_records, dim3(fc::div_up(n, 256)), dim3(256), 0, stream, tokens, sa, (uint32_t)n,
+  hipLaunchKernelGGL(k_records, dim3(fc::div_up(n, kRecBlock)), dim3(256), 0, stream, tokens, sa, (uint32_t)n,
                      (uint4*)rec_out);
   FC_CHECK_LAUNCH();
   return FC_OK;

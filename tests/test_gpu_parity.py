@@ -325,6 +325,18 @@ def test_pair_table():
         fc.fc_store_prepare_pairs(st.tokens, st.sa, 49)
 
 
+@pytest.mark.parametrize("n,V", [(1 << 23, 50), ((1 << 23) + 1, 3000), ((1 << 23) + 511, 2), ((1 << 23) + 700, 9000)])
+def test_pair_table_sampled(n, V):
+    """Stores from 2^23 suffixes on read only the positions around a change of pair."""
+    say(f"pair table n={n} V={V}")
+    rng = np.random.RandomState(n % 1000)
+    t = (rng.zipf(1.3, n) % V).astype(np.uint16)
+    tokens = dev(t)
+    pair = fc.fc_store_prepare_pairs(tokens, fc.fc_datastore_build(tokens), V)
+    torch.cuda.synchronize()
+    assert (host(pair).astype(np.int64) == _pair_table_expected(t, V)).all()
+
+
 def test_records():
     """Record i = {sa[i], T[sa[i]+2 .. sa[i]+32)} with 0 past the end."""
     for seed, n in enumerate((1, 2, 17, 3000, 70001)):
@@ -340,6 +352,27 @@ def test_records():
         want = padded[idx]
         got = np.stack([rec[:, 1:] & 0xFFFF, rec[:, 1:] >> 16], axis=2).reshape(n, 30)
         assert (got == want).all()
+
+
+@pytest.mark.parametrize("n,V,odd", [(7, 9, 0), (8, 9, 1), (9, 2, 0), (255, 31, 1), (256, 31, 0), (257, 31, 1),
+                                     (1023, 4, 0), (1025, 700, 1), (30011, 1500, 1)])
+def test_tables_around_block_edges(n, V, odd):
+    """Pair table and records where a workgroup's or a wave's share ends, on a
+    text that starts at a 2-byte (odd) or a 4-byte boundary."""
+    say(f"tables n={n} V={V} odd={odd}")
+    t = synth.random_text(90 + n, n, V, 0.05)
+    whole = dev(np.concatenate([t[:odd], t]))
+    tokens = whole[odd:]
+    sa = fc.fc_datastore_build(tokens)
+    pair = fc.fc_store_prepare_pairs(tokens, sa, V)
+    rec = fc.fc_store_prepare_records(tokens, sa)
+    torch.cuda.synchronize()
+    assert (host(pair).astype(np.int64) == _pair_table_expected(t, V)).all()
+    order = oracle.suffix_array(t).astype(np.int64)
+    rec = host(rec).view(np.uint32).reshape(n, 16)
+    padded = np.concatenate([t.astype(np.uint32), np.zeros(32, np.uint32)])[order[:, None] + 2 + np.arange(30)[None, :]]
+    assert (rec[:, 0] == order).all()
+    assert (rec[:, 1:] == (padded[:, 0::2] | (padded[:, 1::2] << 16))).all()
 
 
 # --------------------------------------------------------------- retrieval --
