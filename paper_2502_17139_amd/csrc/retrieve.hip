@@ -14,10 +14,10 @@
 // bucket.  With the store's inline-prefix records the group reads the records
 // at 2G - 1 evenly spaced pivots of its range per round trip (a 2G-ary
 // search: log_2G of the range in dependent round trips), comparing only the
-// tokens the table does not already fix; without them each lane runs a
-// binary search over the suffix-array entries and the text.  The workgroup
-// then keeps, per store, the longest n whose range is non-empty and fills
-// the k slots in store priority order.
+// tokens the table does not already fix; without them it reads pivots of the
+// suffix array and then the text at each (2G-ary, or G-ary in groups of eight
+// lanes and more).  The workgroup then keeps, per store, the longest n whose
+// range is non-empty and fills the k slots in store priority order.
 //
 // k_gather: the kept slots of the whole batch are numbered consecutively and
 // cut into one contiguous piece per workgroup of a grid that is resident at
@@ -45,6 +45,7 @@ constexpr int kSearchWide = 512;      // threads per query for batches of at mos
 constexpr int kSearchWideMaxB = 256;
 constexpr int kSearchWidest = 1024;   // and for batches of at most kSearchWidestMaxB
 constexpr int kSearchWidestMaxB = 128;
+constexpr int kTextWideG = 8;         // lanes per task from which a text search takes one pivot per lane
 constexpr int kGatherThreads = 256;
 constexpr int kScanThreads = 1024;
 constexpr int kOffsetsInLds = 4096;
@@ -132,6 +133,20 @@ __device__ __forceinline__ int rec_cmp(const uint4& h0, const uint4& h1, const R
   return res;
 }
 
+// Suffix j of the text against the pattern: its first 32 bytes are a record's
+// with the second token (a record's are known from the table) in the first
+// word's high half.  Suffixes that end within them are compared token by token.
+__device__ __forceinline__ int text_cmp(const uint16_t* __restrict__ T, uint32_t N, uint32_t j, const uint16_t* q,
+                                        int n, bool two, const RecQuery& r) {
+  if ((uint64_t)j + 16 > N) return cmp_suffix(T, N, j, q, n, 1);
+  const fc::u32x4_a2 a = *(const fc::u32x4_a2*)(T + j);
+  fc::u32x4_a2 b = {0u, 0u, 0u, 0u};
+  if (two) b = *(const fc::u32x4_a2*)(T + j + 8);
+  const int res = rec_cmp(make_uint4(a[0], a[1], a[2], a[3]), make_uint4(b[0], b[1], b[2], b[3]), r);
+  const uint32_t t1 = a[0] >> 16, q1 = q[1];
+  return t1 != q1 ? (t1 < q1 ? -1 : 1) : res;
+}
+
 // Search of query b by the whole workgroup: s_lo / s_hi[s][n_max - n] get
 // the bounds of every tried (store, n) that can still matter; untried
 // entries stay 0.  Only the longest n with an occurrence counts per store,
@@ -140,6 +155,7 @@ __device__ __forceinline__ int rec_cmp(const uint4& h0, const uint4& h1, const R
 // next round trip: those are the short suffixes whose two-token ranges are
 // the largest, and the slowest searches.  Their entries are left partial;
 // the keep step never looks below the longest non-empty n.
+template <bool kText>
 __device__ __forceinline__ void search_query(const StoreArgs& st, int S, const uint16_t* __restrict__ ctx, int b,
                                              int L, int n_max, int n_min, int G, int log2_2g, uint16_t* s_q,
                                              uint32_t (*s_lo)[FC_MAX_NMAX], uint32_t (*s_hi)[FC_MAX_NMAX],
@@ -195,35 +211,9 @@ __device__ __forceinline__ void search_query(const StoreArgs& st, int S, const u
       hi = st.bucket[s][q[0] + 1];
     }
   }
-  const bool kary = act && from < n && lo < hi && from == 2 && st.rec[s] != nullptr;
-  if (act && !kary) {
-    if (from < n && lo < hi) {
-      const uint16_t* T = st.tok[s];
-      const uint32_t* SA = st.sa[s];
-      const uint32_t N = st.n[s];
-      uint32_t mid = lo + ((hi - lo) >> 1);
-      uint32_t j = SA[mid];
-      for (;;) {
-        const uint32_t lmid = lo + ((mid - lo) >> 1);
-        const uint32_t rmid = (mid + 1) + ((hi - mid - 1) >> 1);
-        const uint32_t jl = lo < mid ? SA[lmid] : 0u;
-        const uint32_t jr = mid + 1 < hi ? SA[rmid] : 0u;
-        const int c = cmp_suffix(T, N, j, q, n, from);
-        if (upper ? (c <= 0) : (c < 0)) {
-          lo = mid + 1;
-          mid = rmid;
-          j = jr;
-        } else {
-          hi = mid;
-          mid = lmid;
-          j = jl;
-        }
-        if (lo >= hi) break;
-      }
-    } else if (upper) {
-      lo = hi;  // range already final: its end is the upper bound
-    }
-  }
+  const bool kary = act && from < n && lo < hi;
+  const bool in_rec = kary && (!kText || (from == 2 && st.rec[s] != nullptr));
+  if (act && !kary && upper) lo = hi;  // range already final: its end is the upper bound
   // a task's final bound: recorded, and the second bound of a (store, n)
   // to arrive raises the store's best n when the range is non-empty
   auto finish = [&](uint32_t bound) {
@@ -243,7 +233,16 @@ __device__ __forceinline__ void search_query(const StoreArgs& st, int S, const u
     const bool two = n > 8;  // tokens past offset 7 sit in the record's second quad
     const int gbase = lane - gl;
     const uint64_t gmask = G >= 64 ? ~0ull : ((1ull << G) - 1);
-    const int P = 2 * G - 1;  // pivots per round trip
+    // Pivots per round trip: two per lane in records; one in the text of wide
+    // groups, where a pivot is two dependent reads (suffix array, text) and
+    // the narrowing of a second one is not worth its reads.  The text search
+    // is a chain of such reads: 2 stores of 333 k and 30 M tokens, 1 to 256
+    // queries, 20-22 us a retrieval against 23-43 with a binary search per
+    // task; 1,024 queries 35 against 55; 4 stores, 1,024 queries 44 against 62.
+    const bool one = kText && !in_rec && G >= kTextWideG;
+    const int P = one ? G - 1 : 2 * G - 1;
+    const int log2_p = one ? log2_2g - 1 : log2_2g;
+    const int ga = one ? gl + 1 : 2 * gl + 1;  // this lane's first pivot, 1..P (a wide group's last lane repeats P)
     bool searching = kary;
     // A range spanning two sample strides or more is first searched over the
     // sample: the positions t * FC_TOP_STRIDE in [lo, hi) are t in [ta, tb),
@@ -251,7 +250,7 @@ __device__ __forceinline__ void search_query(const StoreArgs& st, int S, const u
     // within one stride of records.
     uint32_t ta = 0, tb = 0;
     bool in_top = false;
-    if (kary && TP != nullptr) {
+    if (in_rec && TP != nullptr) {
       ta = (uint32_t)(((uint64_t)lo + FC_TOP_STRIDE - 1) / FC_TOP_STRIDE);
       tb = (uint32_t)(((uint64_t)hi + FC_TOP_STRIDE - 1) / FC_TOP_STRIDE);
       in_top = tb > ta + 1;
@@ -262,21 +261,29 @@ __device__ __forceinline__ void search_query(const StoreArgs& st, int S, const u
       if (searching && n < *(volatile int*)&s_best[s]) searching = false;  // a longer n has occurrences
       if (searching) {
         const uint64_t span = chi - clo;
-        const uint32_t pa = clo + (uint32_t)(((uint64_t)(2 * gl + 1) * span) >> log2_2g);
-        const bool vb = 2 * gl + 2 <= P;
-        const uint32_t pb = vb ? clo + (uint32_t)(((uint64_t)(2 * gl + 2) * span) >> log2_2g) : pa;
-        const uint4* Qa = in_top ? TP + 2 * (uint64_t)pa : R + kRecQuads * (uint64_t)pa;
-        const uint4* Qb = in_top ? TP + 2 * (uint64_t)pb : R + kRecQuads * (uint64_t)pb;
-        const uint4 a0 = Qa[0];
-        const uint4 b0 = Qb[0];
-        uint4 a1 = make_uint4(0, 0, 0, 0), b1 = a1;
-        if (two) {
-          a1 = Qa[1];
-          b1 = Qb[1];
+        const bool va = !one || ga <= P, vb = ga + 1 <= P && !one;
+        const uint32_t pa = clo + (uint32_t)(((uint64_t)(va ? ga : P) * span) >> log2_p);
+        const uint32_t pb = vb ? clo + (uint32_t)(((uint64_t)(ga + 1) * span) >> log2_p) : pa;
+        int c1, c2;
+        if (!kText || in_rec) {
+          const uint4* Qa = in_top ? TP + 2 * (uint64_t)pa : R + kRecQuads * (uint64_t)pa;
+          const uint4* Qb = in_top ? TP + 2 * (uint64_t)pb : R + kRecQuads * (uint64_t)pb;
+          const uint4 a0 = Qa[0];
+          const uint4 b0 = Qb[0];
+          uint4 a1 = make_uint4(0, 0, 0, 0), b1 = a1;
+          if (two) {
+            a1 = Qa[1];
+            b1 = Qb[1];
+          }
+          c1 = rec_cmp(a0, a1, rq);
+          c2 = rec_cmp(b0, b1, rq);
+        } else {
+          const uint32_t* SA = st.sa[s];
+          const uint32_t ja = SA[pa], jb = vb ? SA[pb] : ja;
+          c1 = text_cmp(st.tok[s], st.n[s], ja, q, n, two, rq);
+          c2 = vb ? text_cmp(st.tok[s], st.n[s], jb, q, n, two, rq) : c1;
         }
-        const int c1 = rec_cmp(a0, a1, rq);
-        const int c2 = rec_cmp(b0, b1, rq);
-        ca = upper ? c1 <= 0 : c1 < 0;
+        ca = va && (upper ? c1 <= 0 : c1 < 0);
         cb = vb && (upper ? c2 <= 0 : c2 < 0);
       }
       const uint64_t ba = fc::ballot(searching && ca);
@@ -285,8 +292,8 @@ __device__ __forceinline__ void search_query(const StoreArgs& st, int S, const u
         // the pivots before the bound form a prefix of the 2G - 1 pivots
         const int c = __popcll((ba >> gbase) & gmask) + __popcll((bb >> gbase) & gmask);
         const uint64_t span = chi - clo;
-        const uint32_t plo = c > 0 ? clo + (uint32_t)(((uint64_t)c * span) >> log2_2g) + 1 : clo;
-        const uint32_t phi = c < P ? clo + (uint32_t)(((uint64_t)(c + 1) * span) >> log2_2g) : chi;
+        const uint32_t plo = c > 0 ? clo + (uint32_t)(((uint64_t)c * span) >> log2_p) + 1 : clo;
+        const uint32_t phi = c < P ? clo + (uint32_t)(((uint64_t)(c + 1) * span) >> log2_p) : chi;
         clo = plo;
         chi = phi;
         if (clo >= chi && in_top) {
@@ -308,7 +315,7 @@ __device__ __forceinline__ void search_query(const StoreArgs& st, int S, const u
 // One query per workgroup: the 2G-ary search of every (store, n, bound),
 // then the kept ranges (the longest non-empty n per store, store priority
 // order) written to the query's row.
-template <int NT>
+template <int NT, bool kText>
 __global__ void __launch_bounds__(NT) k_search(StoreArgs st, int S, const uint16_t* __restrict__ ctx,
                                                            int L, int n_max, int n_min, int k, int G, int log2_2g,
                                                            const int32_t* __restrict__ rows, int n_rows,
@@ -327,7 +334,7 @@ __global__ void __launch_bounds__(NT) k_search(StoreArgs st, int S, const uint16
   if (row < 0) return;  // skipped query: the whole workgroup leaves
   const int tid = (int)threadIdx.x;
   const int lane = fc::lane_id();
-  search_query(st, S, ctx, b, L, n_max, n_min, G, log2_2g, s_q, s_lo, s_hi, &s_nhi, s_done, s_best);
+  search_query<kText>(st, S, ctx, b, L, n_max, n_min, G, log2_2g, s_q, s_lo, s_hi, &s_nhi, s_done, s_best);
   if (tid < fc::kWave) {
     const int NN = n_max - n_min + 1;
     const int n_hi = s_nhi;
@@ -854,15 +861,17 @@ fc_status retrieve_launch(const StoreArgs& st, int32_t S, const uint16_t* ctx, i
   while (G > 1 && G * tasks > nt) G >>= 1;
   int log2_2g = 1;
   while ((1 << log2_2g) < 2 * G) ++log2_2g;
-  if (widest)
-    hipLaunchKernelGGL(k_search<kSearchWidest>, dim3(B), dim3(kSearchWidest), 0, stream, st, S, ctx, L, p.n_max,
-                       p.n_min, p.k, G, log2_2g, rows, n_rows, match_n, range_lo, range_cnt, taken);
-  else if (wide)
-    hipLaunchKernelGGL(k_search<kSearchWide>, dim3(B), dim3(kSearchWide), 0, stream, st, S, ctx, L, p.n_max, p.n_min,
-                       p.k, G, log2_2g, rows, n_rows, match_n, range_lo, range_cnt, taken);
-  else
-    hipLaunchKernelGGL(k_search<kSearchThreads>, dim3(B), dim3(kSearchThreads), 0, stream, st, S, ctx, L, p.n_max,
-                       p.n_min, p.k, G, log2_2g, rows, n_rows, match_n, range_lo, range_cnt, taken);
+  // every search is one over records: the kernel without the text search (with
+  // it compiled in, 256 queries over records took 0.5 us longer)
+  bool records = true;
+  for (int s = 0; s < S; ++s) records = records && (st.n[s] == 0 || st.rec[s] != nullptr);
+  auto search = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(B), dim3(nt), 0, stream, st, S, ctx, L, p.n_max, p.n_min, p.k, G, log2_2g, rows,
+                       n_rows, match_n, range_lo, range_cnt, taken);
+  };
+  if (widest) records ? search(k_search<kSearchWidest, false>) : search(k_search<kSearchWidest, true>);
+  else if (wide) records ? search(k_search<kSearchWide, false>) : search(k_search<kSearchWide, true>);
+  else records ? search(k_search<kSearchThreads, false>) : search(k_search<kSearchThreads, true>);
   FC_CHECK_LAUNCH();
   if (p.m <= 16) {
     uint32_t* offsets = (uint32_t*)ws;

@@ -653,6 +653,35 @@ def test_fuzz_many_tiny_cases():
     assert cases >= 12000
 
 
+@pytest.mark.parametrize("B,S,pairs", [(1, 1, 0), (3, 4, 1), (128, 2, 0), (129, 3, 1), (256, 2, 0), (257, 2, 1),
+                                       (300, 4, 0)])
+def test_search_without_records(B, S, pairs):
+    """The text search at every width of its groups (16 lanes down to 2), on
+    stores whose matches reach the end of the text, one shorter than the 16
+    tokens a pivot reads, one at an odd address."""
+    say(f"text search B={B} S={S} pairs={pairs}")
+    rng = np.random.default_rng(100 * B + S)
+    texts = [synth.random_text(300 + B + s, n, v, 0.02) for s, (n, v) in enumerate(((9000, 6), (15, 3), (700, 3),
+                                                                                    (20001, 90)))][:S]
+    stores = []
+    for s, t in enumerate(texts):
+        whole = dev(np.concatenate([t[:1], t]))
+        stores.append(fc.Store(whole[1:] if s == 0 else dev(t), pair_vocab=100 if pairs else None))
+    rows = []
+    for b in range(B):
+        t = texts[b % S]
+        j = len(t) - 16 - int(rng.integers(0, 6)) if b % 3 == 0 else int(rng.integers(0, max(1, len(t) - 16)))
+        row = np.ones(16, np.uint16)
+        part = t[max(0, j):max(0, j) + 16]
+        row[16 - len(part):] = part
+        if b % 5 == 4:
+            row[int(rng.integers(0, 12))] = 2
+        rows.append(row)
+    ctx = np.stack(rows)
+    p = dict(n_max=16, n_min=1 if S < 4 else 2, k=40, m=6)
+    compare_retrieve(gpu_pipeline(stores, ctx, p, (1, 1, 1, 1)[:S], 16), oracle.retrieve(texts, ctx, **p))
+
+
 def test_results_do_not_depend_on_batching():
     """The same queries give the same per-query bytes whatever launch shape
     the batch leads to: one batch of 300 (the tree's heaviest-first planning
