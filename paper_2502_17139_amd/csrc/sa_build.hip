@@ -35,10 +35,8 @@
 // positions, 64 at a time), so every load and store of a wave is coalesced
 // except the rank scatter itself, which is indexed by suffix.  Where the
 // rank array outgrows the MALL (64M suffixes or more), a random 4-byte write
-// costs a 32-byte memory write, so the round's (suffix, rank) pairs are
-// written in sorted order instead, sorted by the suffix's top 24 bits
-// (three keys-only passes), and then stored one small window of the rank
-// array after another, each wave's stores falling on a few cache lines.
+// costs a 32-byte memory write, so the new ranks are split into windows of
+// the rank array and put together there (RankParts).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -57,7 +55,6 @@ constexpr int kSegThreads = 256;
 constexpr int kSegItems = 16;
 constexpr int kSegTile = kSegThreads * kSegItems;
 constexpr int kScanThreads = 1024;
-constexpr int kMaxPasses = 1024;  // ticket counters per build
 constexpr int kMaxRounds = 40;
 constexpr int kHistBlocks = 2048;
 constexpr uint32_t kBigKeysBlocks = 2048;
@@ -466,52 +463,6 @@ __global__ void __launch_bounds__(256) k_ext_isa_old(const uint32_t* __restrict_
 
 // ------------------------------------------------------------ histogram ---
 
-__global__ void __launch_bounds__(256) k_hist(const uint64_t* __restrict__ keys, uint32_t U, int shift0,
-                                                int digits, uint32_t* __restrict__ hist) {
-  __shared__ uint32_t s[kMaxDigits][kRadix];
-  for (int i = threadIdx.x; i < kMaxDigits * kRadix; i += blockDim.x) (&s[0][0])[i] = 0;
-  __syncthreads();
-  // 64-bit index: U can come within a grid stride of 2^32.  The keys are in
-  // the previous round's sorted order, so a wave's 64 consecutive keys
-  // mostly share their high digits, in runs: each run of equal digits in
-  // consecutive lanes is counted with one LDS atomic by its first lane
-  // (lanes colliding on one bin would serialise).  Each wave takes kHistRun
-  // runs of 64 consecutive keys per step, their loads issued together.
-  constexpr int kHistRun = 4;
-  const uint64_t wave0 = (uint64_t)blockIdx.x * blockDim.x * kHistRun + (threadIdx.x & ~(uint32_t)(fc::kWave - 1)) * kHistRun;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * kHistRun;
-  for (uint64_t i0 = wave0; i0 < U; i0 += stride) {
-    uint64_t kv[kHistRun];
-#pragma unroll
-    for (int u = 0; u < kHistRun; ++u) {
-      const uint64_t i = i0 + (uint64_t)(u * fc::kWave + fc::lane_id());
-      kv[u] = i < U ? keys[i] : 0ull;
-    }
-#pragma unroll
-    for (int u = 0; u < kHistRun; ++u) {
-      const uint64_t i = i0 + (uint64_t)(u * fc::kWave + fc::lane_id());
-      const bool valid = i < U;
-      const uint64_t k = kv[u];
-      const uint64_t act = fc::ballot(valid);
-      if (act == 0) continue;
-      const uint32_t cnt = (uint32_t)__popcll(act);  // the valid lanes are a prefix
-      const uint32_t lane = (uint32_t)fc::lane_id();
-      for (int d = 0; d < digits; ++d) {
-        const uint32_t dig = (uint32_t)(k >> (shift0 + 8 * d)) & 0xFF;
-        const bool head = valid && dig != fc::wave_shr1(dig, ~0u);
-        const uint64_t after = fc::ballot(head) >> lane >> 1;  // heads above this lane
-        const uint32_t next = after ? lane + 1u + (uint32_t)__builtin_ctzll(after) : cnt;
-        if (head) atomicAdd(&s[d][dig], next - lane);
-      }
-    }
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < digits * kRadix; i += blockDim.x) {
-    uint32_t v = (&s[0][0])[i];
-    if (v) atomicAdd(&hist[i], v);
-  }
-}
-
 // One workgroup of 256 threads per digit: its offsets (exclusive scan).
 __global__ void __launch_bounds__(256) k_hist_scan(const uint32_t* __restrict__ hist,
                                                      uint32_t* __restrict__ offsets) {
@@ -568,10 +519,7 @@ __device__ __forceinline__ uint64_t look_back(const uint64_t* status, int64_t p,
   return excl;
 }
 
-// kVals false: keys only (vin and vout unused), compiled for four waves per
-// SIMD, so four tiles share a CU.
-template <bool kVals>
-__global__ void __launch_bounds__(kSortThreads, kVals ? 1 : 4) k_onesweep(const uint64_t* __restrict__ kin,
+__global__ void __launch_bounds__(kSortThreads) k_onesweep(const uint64_t* __restrict__ kin,
                                                            const uint32_t* __restrict__ vin,
                                                            uint64_t* __restrict__ kout, uint32_t* __restrict__ vout,
                                                            uint32_t U, uint32_t shift,
@@ -587,7 +535,7 @@ __global__ void __launch_bounds__(kSortThreads, kVals ? 1 : 4) k_onesweep(const 
   __shared__ uint32_t s_gbase[kRadix];
   __shared__ uint32_t s_scan[kSortThreads / fc::kWave + 1];
   __shared__ uint64_t s_keys[kSortTile];
-  __shared__ uint32_t s_vals[kVals ? kSortTile : 1];
+  __shared__ uint32_t s_vals[kSortTile];
 
   const int tid = threadIdx.x;
   const int w = (int)uniform((uint32_t)tid / fc::kWave);
@@ -607,7 +555,7 @@ __global__ void __launch_bounds__(kSortThreads, kVals ? 1 : 4) k_onesweep(const 
     const uint32_t idx = (uint32_t)(w * kSortItems * fc::kWave + j * fc::kWave + lane);
     const bool valid = idx < nvalid;
     k[j] = valid ? kin[base + idx] : ~0ull;
-    v[j] = kVals && valid ? vin[base + idx] : 0u;
+    v[j] = valid ? vin[base + idx] : 0u;
   }
   const uint64_t lt = fc::lanemask_lt();
 #pragma unroll
@@ -656,7 +604,7 @@ __global__ void __launch_bounds__(kSortThreads, kVals ? 1 : 4) k_onesweep(const 
       const uint32_t d = (uint32_t)(k[j] >> shift) & 0xFF;
       const uint32_t pos = s_dstart[d] + s_wcnt[w][d] + rk[j];
       s_keys[pos] = k[j];
-      if (kVals) s_vals[pos] = v[j];
+      s_vals[pos] = v[j];
     }
   }
 
@@ -672,7 +620,7 @@ __global__ void __launch_bounds__(kSortThreads, kVals ? 1 : 4) k_onesweep(const 
     const uint32_t dst = s_gbase[d] + (i - s_dstart[d]);
     if (dst < U) {  // always true unless a look-back gave up (then err is set)
       kout[dst] = key;
-      if (kVals) vout[dst] = s_vals[i];
+      vout[dst] = s_vals[i];
     }
   }
 }
@@ -1297,34 +1245,59 @@ __global__ void __launch_bounds__(kScanThreads) k_seg_scan(uint32_t* __restrict_
   if (threadIdx.x == 0) *u_next = ck;
 }
 
+// Where a round's new ranks go when the rank array outgrows the MALL (a
+// random 4-byte write then costs a 32-byte memory write): as (suffix << 32 |
+// rank) pairs into the bucket of the suffix's high bits, then split by lower
+// bits into windows of kRankWin suffixes (k_rank_split), and each window is
+// put together in LDS (k_rank_window).  A suffix occurs once in a round, so a
+// bucket or a window has room for all of its suffixes at its own place in the
+// buffer, [d << shift, (d + 1) << shift), and its elements come in any order:
+// each tile reserves room for its share of a bucket with one atomic, with no
+// histogram and no look-back.  Against sorting the pairs by the suffix's top
+// 24 bits (a histogram and three onesweep passes, then stores that fell on a
+// few lines per wave): 1B suffixes, six rounds: 66 ms (5 counting, 51 sorting, 10
+// storing) -> 35 (13 more in k_seg_apply, 13 splitting, 10 windows).
+struct RankParts {
+  uint64_t* out;
+  uint32_t* cursor;  // elements in each of up to 256 buckets
+  int shift;
+  uint64_t n;        // suffixes, and room in out
+};
+constexpr int kRankWinBits = 14;                 // a window's ranks: 64 KB of LDS, two workgroups per CU
+constexpr uint32_t kRankWin = 1u << kRankWinBits;
+constexpr int kRankSplitMax = 1024;              // windows of a bucket, at most
+constexpr uint64_t kPairRanksMin = 1ull << 26;   // suffixes (4-byte ranks: 256 MB)
+
 // Per element: new rank = old group start + (new head index - old head index)
 // in the sorted list; tied suffixes are compacted into (grp_next, val_next)
 // with their new rank as the group.  A suffix
 // whose group is now a singleton has its final index, so its suffix array
 // entry is written here (sa_out, unless null), in sorted order.  The ranks
-// go to rank[] directly (a random 4-byte write each), or, with pairs, as
-// (suffix << 32 | rank) at the element's own position, for k_rank_write
-// after a sort by suffix.  Wave w of
+// go to rank[] directly (a random 4-byte write each), or, with kParts, into
+// the buckets of RankParts.  Wave w of
 // the tile takes positions [w * 1024, (w + 1) * 1024) of it, 64 consecutive
 // ones per step: the running head indexes and the kept count are wave scans
 // carried from step to step, started from the earlier waves' totals and the
 // tile prefix.
-template <bool kRound0>
+template <bool kRound0, bool kParts>
 __global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, const uint32_t* __restrict__ vals,
                                                              uint32_t U, const uint32_t* __restrict__ pre_h,
                                                              const uint32_t* __restrict__ pre_g,
                                                              const uint32_t* __restrict__ pre_k,
-                                                             uint32_t* __restrict__ rank,
-                                                             uint64_t* __restrict__ pairs,
+                                                             uint32_t* __restrict__ rank, RankParts parts,
                                                              uint32_t* __restrict__ val_next,
                                                              uint32_t* __restrict__ grp_next,
                                                              uint32_t* __restrict__ sa_out) {
   constexpr int kWaves = kSegThreads / fc::kWave;
   constexpr uint32_t kPerWave = kSegTile / kWaves;
   __shared__ uint32_t s_tot[3][kWaves];
+  __shared__ uint32_t s_cnt[kParts ? kRadix : 1], s_start[kParts ? kRadix : 1], s_base[kParts ? kRadix : 1];
+  __shared__ uint32_t s_scan[kWaves + 1];
+  __shared__ uint64_t s_pair[kParts ? kSegTile : 1];
   const int w = (int)threadIdx.x / fc::kWave;
   const uint32_t lane = (uint32_t)fc::lane_id();
   const uint32_t base = blockIdx.x * kSegTile + (uint32_t)w * kPerWave;
+  if (kParts) s_cnt[threadIdx.x] = 0;
   // the wave's totals
   uint32_t mh = 0, mg = 0, kc = 0;
   for (int j = 0; j < kSegItems; ++j) {
@@ -1351,6 +1324,8 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, c
     gg = s_tot[1][v] > gg ? s_tot[1][v] : gg;
     out += s_tot[2][v];
   }
+  uint32_t pi[kParts ? kSegItems : 1], pr[kParts ? kSegItems : 1], pos[kParts ? kSegItems : 1];
+#pragma unroll
   for (int j = 0; j < kSegItems; ++j) {
     const uint32_t r = base + (uint32_t)j * fc::kWave + lane;
     const bool valid = r < U;
@@ -1361,6 +1336,7 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, c
     const uint32_t kr = fc::wave_incl_sum_u32(f.keep ? 1u : 0u);
     hr = hr > hh ? hr : hh;
     gr = gr > gg ? gr : gg;
+    if (kParts) pos[j] = kNone;
     if (valid) {
       uint32_t start = 0u;
       if constexpr (!kRound0) start = in.grp[r];
@@ -1368,9 +1344,16 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, c
       const uint32_t rk = start + (hr - gr);
       // in the first new group of its old group a suffix keeps its rank (the
       // old group start, already in rank[i]): only round 0 and the later
-      // new groups write (a pair rewrites an unchanged rank with itself)
-      if (pairs) pairs[r] = ((uint64_t)i << 32) | rk;
-      else if (kRound0 || hr != gr) rank[i] = rk;
+      // new groups write
+      if (kRound0 || hr != gr) {
+        if (kParts) {
+          pi[j] = i;
+          pr[j] = rk;
+          pos[j] = atomicAdd(&s_cnt[(i >> parts.shift) & (kRadix - 1)], 1u);
+        } else {
+          rank[i] = rk;
+        }
+      }
       if (f.keep) {
         val_next[out + kr - 1u] = i;
         grp_next[out + kr - 1u] = rk;
@@ -1381,32 +1364,127 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, c
     gg = __shfl(gr, fc::kWave - 1);
     out += __shfl(kr, fc::kWave - 1);
   }
-}
-
-// rank[i] = rk for a round's (i << 32 | rk) pairs, sorted by the high bits
-// of i so that each run of equal high bits covers one window of the rank
-// array (256 bytes at 1G suffixes), and a wave's 64 stores fall on a few
-// cache lines.  Workgroup w takes chunk (w % 8) * per_xcd + w / 8 of
-// kRankChunk pairs: workgroups are dealt to the eight XCDs in turn, so each
-// XCD writes one contiguous eighth of the sorted pairs, and a line is
-// assembled in one L2 rather than written back in pieces from several.
-constexpr int kRankChunk = 4096;
-constexpr int kXcds = 8;
-constexpr int kRankSortBits = 24;  // high bits of the suffix index sorted on
-constexpr uint64_t kPairRanksMin = 1ull << 26;  // suffixes (4-byte ranks: 256 MB)
-__global__ void __launch_bounds__(256) k_rank_write(const uint64_t* __restrict__ pairs, uint32_t U,
-                                                    uint32_t per_xcd, uint32_t* __restrict__ rank) {
-  const uint32_t c = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-  const uint64_t b = (uint64_t)c * kRankChunk;
-  if (b >= U) return;
-#pragma unroll 4
-  for (int j = 0; j < kRankChunk / 256; ++j) {
-    const uint64_t r = b + (uint64_t)j * 256 + threadIdx.x;
-    if (r < U) {
-      const uint64_t p = pairs[r];
-      rank[p >> 32] = (uint32_t)p;
+  if constexpr (kParts) {
+    __syncthreads();
+    const uint32_t t = threadIdx.x, mine = s_cnt[t];  // this thread's bucket
+    const uint32_t got = mine ? atomicAdd(&parts.cursor[t], mine) : 0u;
+    uint32_t all;
+    s_start[t] = fc::block_excl_sum<uint32_t>(mine, s_scan, &all);
+    s_base[t] = got;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSegItems; ++j)
+      if (pos[j] != kNone) s_pair[s_start[(pi[j] >> parts.shift) & (kRadix - 1)] + pos[j]] = ((uint64_t)pi[j] << 32) | pr[j];
+    __syncthreads();
+    for (uint32_t x = threadIdx.x; x < all; x += kSegThreads) {
+      const uint64_t p = s_pair[x];
+      const uint32_t d = ((uint32_t)(p >> 32) >> parts.shift) & (kRadix - 1);
+      const uint64_t at = ((uint64_t)d << parts.shift) + s_base[d] + (x - s_start[d]);
+      if (at < parts.n) parts.out[at] = p;  // always true unless a look-back gave up (then err is set)
     }
   }
+}
+
+// Bucket blockIdx.x % buckets (its elements: cursor[bucket]) into its windows,
+// tile after tile; the workgroups of one bucket are on one XCD, whose L2 puts
+// a window's lines together.
+constexpr int kSplitThreads = 512;
+constexpr int kSplitItems = 16;
+constexpr uint32_t kSplitTile = kSplitThreads * kSplitItems;
+__global__ void __launch_bounds__(kSplitThreads) k_rank_split(RankParts from, uint32_t buckets,
+                                                               uint64_t* __restrict__ out,
+                                                               uint32_t* __restrict__ win_count) {
+  __shared__ uint32_t s_cnt[kRankSplitMax], s_start[kRankSplitMax], s_base[kRankSplitMax];
+  __shared__ uint32_t s_scan[kSplitThreads / fc::kWave + 1];
+  __shared__ uint64_t s_pair[kSplitTile];
+  const uint32_t d = blockIdx.x % buckets;
+  const uint64_t d0 = (uint64_t)d << from.shift;
+  const uint64_t room = from.n - d0 < (1ull << from.shift) ? from.n - d0 : 1ull << from.shift;
+  const uint32_t got = uniform(from.cursor[d]), count = got < room ? got : (uint32_t)room;
+  const int splits = 1 << (from.shift - kRankWinBits);
+  const uint64_t* __restrict__ src = from.out + d0;
+  uint32_t* const wc = win_count + ((uint64_t)d << (from.shift - kRankWinBits));
+  constexpr int kPer = kRankSplitMax / kSplitThreads;
+  for (uint64_t t0 = (uint64_t)(blockIdx.x / buckets) * kSplitTile; t0 < count;
+       t0 += (uint64_t)(gridDim.x / buckets) * kSplitTile) {
+    for (int i = (int)threadIdx.x; i < kRankSplitMax; i += kSplitThreads) s_cnt[i] = 0;
+    __syncthreads();
+    uint64_t p[kSplitItems];
+    uint32_t pos[kSplitItems];
+#pragma unroll
+    for (int j = 0; j < kSplitItems; ++j) {
+      const uint64_t i = t0 + (uint64_t)(j * kSplitThreads) + threadIdx.x;
+      p[j] = i < count ? src[i] : 0ull;
+    }
+#pragma unroll
+    for (int j = 0; j < kSplitItems; ++j) {
+      const uint64_t i = t0 + (uint64_t)(j * kSplitThreads) + threadIdx.x;
+      const uint32_t sub = (uint32_t)(p[j] >> (32 + kRankWinBits)) & (uint32_t)(splits - 1);
+      pos[j] = i < count ? atomicAdd(&s_cnt[sub], 1u) : kNone;
+    }
+    __syncthreads();
+    uint32_t c[kPer], sum = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int sub = (int)threadIdx.x * kPer + u;
+      c[u] = s_cnt[sub];  // 0 past the bucket's windows
+      s_base[sub] = c[u] ? atomicAdd(&wc[sub], c[u]) : 0u;
+      sum += c[u];
+    }
+    uint32_t all;
+    uint32_t run = fc::block_excl_sum<uint32_t>(sum, s_scan, &all);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      s_start[(int)threadIdx.x * kPer + u] = run;
+      run += c[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSplitItems; ++j)
+      if (pos[j] != kNone) s_pair[s_start[(uint32_t)(p[j] >> (32 + kRankWinBits)) & (uint32_t)(splits - 1)] + pos[j]] = p[j];
+    __syncthreads();
+    for (uint32_t x = threadIdx.x; x < all; x += kSplitThreads) {
+      const uint64_t q = s_pair[x];
+      const uint32_t win = (uint32_t)(q >> (32 + kRankWinBits)), sub = win & (uint32_t)(splits - 1);
+      const uint64_t at = ((uint64_t)win << kRankWinBits) + s_base[sub] + (x - s_start[sub]);
+      if (at < from.n) out[at] = q;  // always (as above)
+    }
+    __syncthreads();  // the next tile reuses the LDS
+  }
+}
+
+// Window blockIdx.x of the rank array.  One that changes in part is read
+// first; one that changes in few places takes the stores directly (they fall
+// on 64 KB).
+__global__ void __launch_bounds__(kSplitThreads) k_rank_window(const uint64_t* __restrict__ pairs,
+                                                               const uint32_t* __restrict__ win_count, uint64_t n,
+                                                               uint32_t* __restrict__ rank) {
+  __shared__ uint32_t s_rank[kRankWin];
+  const uint64_t w0 = (uint64_t)blockIdx.x << kRankWinBits;
+  const uint32_t size = n - w0 < kRankWin ? (uint32_t)(n - w0) : kRankWin;
+  const uint32_t got = uniform(win_count[blockIdx.x]), count = got < size ? got : size;
+  const uint64_t* __restrict__ src = pairs + w0;
+  uint32_t* const dst = rank + w0;
+  if (count <= size / 8) {
+    for (uint32_t i = threadIdx.x; i < count; i += kSplitThreads) {
+      const uint64_t p = src[i];
+      if ((p >> 32) < n) rank[p >> 32] = (uint32_t)p;
+    }
+    return;
+  }
+  if (count < size) {
+#pragma unroll 8
+    for (uint32_t i = threadIdx.x; i < size; i += kSplitThreads) s_rank[i] = dst[i];
+    __syncthreads();
+  }
+#pragma unroll 8
+  for (uint32_t i = threadIdx.x; i < count; i += kSplitThreads) {
+    const uint64_t p = src[i];
+    s_rank[(uint32_t)(p >> 32) & (kRankWin - 1)] = (uint32_t)p;
+  }
+  __syncthreads();
+#pragma unroll 8
+  for (uint32_t i = threadIdx.x; i < size; i += kSplitThreads) dst[i] = s_rank[i];
 }
 
 // ------------------------------------------------------- first-token table --
@@ -1644,7 +1722,7 @@ size_t carve_build(void* p, uint64_t n, BuildWs* w, uint32_t n_seg = 0) {
   tmp.part_k = c.take<uint32_t>(seg_tiles);
   tmp.hist = c.take<uint32_t>(kMaxDigits * kRadix);
   tmp.offsets = c.take<uint32_t>(kMaxDigits * kRadix);
-  tmp.tickets = c.take<uint32_t>(kMaxPasses);
+  tmp.tickets = c.take<uint32_t>(kMaxDigits);
   tmp.misc = c.take<uint32_t>(16);
   tmp.seg_bits = n_seg ? c.take<uint32_t>(n / 32 + 1) : nullptr;
   tmp.seg_off = n_seg ? c.take<uint64_t>((size_t)n_seg + 1) : nullptr;
@@ -1679,35 +1757,21 @@ int bit_length(uint64_t x) {
   return b;
 }
 
-struct SortState {
-  uint32_t epoch = 0;
-  uint32_t ticket = 0;
-};
-
-// LSD radix sort over `digits` 8-bit digits from bit shift0 of kb[src], with
-// vb[src] carried alongside unless vb is null, the passes alternating
-// between the two buffers; w.hist holds the digits' counts.  *result is the
-// index (0 or 1) of the buffer that holds the result.
-fc_status radix_passes(BuildWs& w, uint64_t* const kb[2], uint32_t* const vb[2], int src, uint32_t U, int shift0,
-                       int digits, SortState& st, hipStream_t stream, int* result) {
+// LSD radix sort of round 0's keys over `digits` 8-bit digits, the suffixes
+// carried alongside, the passes alternating between the two buffers; w.hist
+// holds the digits' counts.  *result is the index (0 or 1) of the buffers that
+// hold the result.
+fc_status radix_passes(BuildWs& w, uint32_t U, int digits, uint32_t& epoch, hipStream_t stream, int* result) {
   hipLaunchKernelGGL(k_hist_scan, dim3(digits), dim3(256), 0, stream, w.hist, w.offsets);
   FC_CHECK_LAUNCH();
-  int cur = src;
+  int cur = 0;
   const uint32_t tiles = fc::div_up(U, kSortTile);
   for (int d = 0; d < digits; ++d) {
-    if (st.ticket >= (uint32_t)kMaxPasses) return FC_ERR_UNSUPPORTED;
-    ++st.epoch;
-    const uint32_t shift = (uint32_t)(shift0 + 8 * d);
-    if (vb)
-      hipLaunchKernelGGL(k_onesweep<true>, dim3(tiles), dim3(kSortThreads), 0, stream, kb[cur], vb[cur],
-                         kb[cur ^ 1], vb[cur ^ 1], U, shift, w.offsets + d * kRadix, w.status, w.tickets + st.ticket,
-                         st.epoch, w.misc);
-    else
-      hipLaunchKernelGGL(k_onesweep<false>, dim3(tiles), dim3(kSortThreads), 0, stream, kb[cur], nullptr,
-                         kb[cur ^ 1], nullptr, U, shift, w.offsets + d * kRadix, w.status, w.tickets + st.ticket,
-                         st.epoch, w.misc);
+    ++epoch;
+    hipLaunchKernelGGL(k_onesweep, dim3(tiles), dim3(kSortThreads), 0, stream, w.keys[cur], w.vals[cur],
+                       w.keys[cur ^ 1], w.vals[cur ^ 1], U, (uint32_t)(8 * d), w.offsets + d * kRadix, w.status,
+                       w.tickets + d, epoch, w.misc);
     FC_CHECK_LAUNCH();
-    ++st.ticket;
     cur ^= 1;
   }
   *result = cur;
@@ -1741,13 +1805,13 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
   const uint32_t N = (uint32_t)n;
   const uint64_t tiles = (n + kSortTile - 1) / kSortTile;
   FC_CHECK_HIP(hipMemsetAsync(w.status, 0, sizeof(uint64_t) * tiles * kRadix, stream));
-  FC_CHECK_HIP(hipMemsetAsync(w.tickets, 0, sizeof(uint32_t) * kMaxPasses, stream));
+  FC_CHECK_HIP(hipMemsetAsync(w.tickets, 0, sizeof(uint32_t) * kMaxDigits, stream));
   FC_CHECK_HIP(hipMemsetAsync(w.misc, 0, sizeof(uint32_t) * 16, stream));
   FC_CHECK_HIP(hipMemsetAsync(w.hist, 0, sizeof(uint32_t) * kMaxDigits * kRadix, stream));
 
   // every rank + 1 <= n (an extension's labels: <= the whole text) fits in lo_digits bytes
   const int lo_digits = (bit_length(ext ? ext->n : n) + 7) / 8;
-  SortState st;
+  uint32_t epoch = 0;  // of the status words: one per pass
   uint64_t h;
   int key0_bits;
   int ext_shift = 0;
@@ -1788,9 +1852,9 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
   }
   FC_CHECK_LAUNCH();
   int res = 0;
-  fc_status s = radix_passes(w, w.keys, w.vals, 0, N, 0, (key0_bits + 7) / 8, st, stream, &res);
+  const fc_status s = radix_passes(w, N, (key0_bits + 7) / 8, epoch, stream, &res);
   if (s != FC_OK) return s;
-  int sort_passes = (int)st.ticket;
+  int sort_passes = (key0_bits + 7) / 8;
   if (M == Mode::kExtend) {
     hipLaunchKernelGGL(k_ins_sorted, dim3(fc::div_up(N, 256)), dim3(256), 0, stream, w.keys[res], N, ext_shift,
                        ext->ins_sorted);
@@ -1814,8 +1878,8 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
     L.big.first_head = w.hist;  // the one window of a short list
   }
   L.big.count = w.misc + 2;
-  // ranks through k_rank_write when the rank array is at least the size of
-  // the 256 MB MALL; a smaller one takes the random writes in the MALL
+  // ranks through RankParts when the rank array is at least the size of the
+  // 256 MB MALL; a smaller one takes the random writes in the MALL
   const bool pair_ranks = M == Mode::kPlain && n >= kPairRanksMin;
   NextRank nr{w.rank, w.seg_bits, ext ? ext->ins : nullptr, ext ? ext->isa : nullptr,
               ext ? ext->ins_sorted : nullptr, ext ? ext->n : n, h, N};
@@ -1828,7 +1892,6 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
     const Sorted<true> s0{w.keys[res], nullptr, nullptr};
     const Sorted<false> s1{nullptr, L.grp[cur], L.lo};
     const uint32_t* sorted_vals = round == 0 ? w.vals[res] : L.val[cur];
-    uint64_t* pairs = pair_ranks ? w.pairs : nullptr;
     if (round == 0)
       hipLaunchKernelGGL(k_seg_partials<true>, dim3(seg_tiles), dim3(kSegThreads), 0, stream, s0, U, w.part_h,
                          w.part_g, w.part_k);
@@ -1839,33 +1902,41 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
     hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(kScanThreads), 0, stream, w.part_h, w.part_g, w.part_k, seg_tiles,
                        w.misc + 1);
     FC_CHECK_LAUNCH();
-    if (round == 0)
-      hipLaunchKernelGGL(k_seg_apply<true>, dim3(seg_tiles), dim3(kSegThreads), 0, stream, s0, sorted_vals, U,
-                         w.part_h, w.part_g, w.part_k, w.rank, pairs, L.val[cur ^ 1], L.grp[cur ^ 1],
-                         ext ? nullptr : sa_out);
-    else
-      hipLaunchKernelGGL(k_seg_apply<false>, dim3(seg_tiles), dim3(kSegThreads), 0, stream, s1, sorted_vals, U,
-                         w.part_h, w.part_g, w.part_k, w.rank, pairs, L.val[cur ^ 1], L.grp[cur ^ 1],
-                         ext ? nullptr : sa_out);
-    FC_CHECK_LAUNCH();
     if (pair_ranks) {
-      // the round's ranks, for the next round's keys: the pairs sorted by the
-      // suffix's top kRankSortBits bits (lo's buffer is free now), then
-      // written window by window
-      const int sb = bit_length(n);
-      uint64_t* const pb[2] = {w.pairs, w.keys[res]};
-      const int hb = sb < kRankSortBits ? sb : kRankSortBits;
-      FC_CHECK_HIP(hipMemsetAsync(w.hist, 0, sizeof(uint32_t) * kMaxDigits * kRadix, stream));
-      const uint32_t hist_blocks = fc::div_up(U, 256) < (uint32_t)kHistBlocks ? fc::div_up(U, 256) : kHistBlocks;
-      hipLaunchKernelGGL(k_hist, dim3(hist_blocks), dim3(256), 0, stream, w.pairs, U, 32 + sb - hb, (hb + 7) / 8,
-                         w.hist);
+      // w.hist is free after the radix passes, the tile partials after k_seg_apply, lo's buffer until k_sort_small
+      const int bits = bit_length(n - 1);
+      const RankParts parts{w.pairs, w.hist, bits > 8 + kRankWinBits ? bits - 8 : kRankWinBits, n};
+      const uint32_t buckets = (uint32_t)(((n - 1) >> parts.shift) + 1);  // <= 256
+      const uint32_t windows = (uint32_t)((n + kRankWin - 1) >> kRankWinBits);
+      FC_CHECK_HIP(hipMemsetAsync(w.hist, 0, sizeof(uint32_t) * kRadix, stream));
+      if (round == 0)
+        hipLaunchKernelGGL((k_seg_apply<true, true>), dim3(seg_tiles), dim3(kSegThreads), 0, stream, s0, sorted_vals,
+                           U, w.part_h, w.part_g, w.part_k, w.rank, parts, L.val[cur ^ 1], L.grp[cur ^ 1], sa_out);
+      else
+        hipLaunchKernelGGL((k_seg_apply<false, true>), dim3(seg_tiles), dim3(kSegThreads), 0, stream, s1, sorted_vals,
+                           U, w.part_h, w.part_g, w.part_k, w.rank, parts, L.val[cur ^ 1], L.grp[cur ^ 1], sa_out);
       FC_CHECK_LAUNCH();
-      int pres = 0;
-      s = radix_passes(w, pb, nullptr, 0, U, 32 + sb - hb, (hb + 7) / 8, st, stream, &pres);
-      if (s != FC_OK) return s;
-      sort_passes += (hb + 7) / 8;
-      const uint32_t per_xcd = fc::div_up(fc::div_up(U, kRankChunk), kXcds);
-      hipLaunchKernelGGL(k_rank_write, dim3(per_xcd * kXcds), dim3(256), 0, stream, pb[pres], U, per_xcd, w.rank);
+      uint32_t* const win_count = w.part_h;  // a tile of the partials is smaller than a window
+      static_assert((uint32_t)kSegTile <= kRankWin, "window counters fit the tile partials");
+      FC_CHECK_HIP(hipMemsetAsync(win_count, 0, sizeof(uint32_t) * windows, stream));
+      // enough workgroups per bucket for its tiles when the elements are spread evenly, up to a few per CU in all
+      const uint32_t want = fc::div_up(U, kSplitTile * buckets), most = fc::div_up(2048, buckets);
+      hipLaunchKernelGGL(k_rank_split, dim3(buckets * (want < most ? want : most)), dim3(kSplitThreads), 0, stream,
+                         parts, buckets, w.keys[res], win_count);
+      FC_CHECK_LAUNCH();
+      hipLaunchKernelGGL(k_rank_window, dim3(windows), dim3(kSplitThreads), 0, stream, w.keys[res], win_count, n,
+                         w.rank);
+      FC_CHECK_LAUNCH();
+    } else {
+      const RankParts none{nullptr, nullptr, 0, 0};
+      if (round == 0)
+        hipLaunchKernelGGL((k_seg_apply<true, false>), dim3(seg_tiles), dim3(kSegThreads), 0, stream, s0, sorted_vals,
+                           U, w.part_h, w.part_g, w.part_k, w.rank, none, L.val[cur ^ 1], L.grp[cur ^ 1],
+                           ext ? nullptr : sa_out);
+      else
+        hipLaunchKernelGGL((k_seg_apply<false, false>), dim3(seg_tiles), dim3(kSegThreads), 0, stream, s1, sorted_vals,
+                           U, w.part_h, w.part_g, w.part_k, w.rank, none, L.val[cur ^ 1], L.grp[cur ^ 1],
+                           ext ? nullptr : sa_out);
       FC_CHECK_LAUNCH();
     }
     // the next round's small groups, launched before its size is known on
@@ -1907,9 +1978,9 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
       FC_CHECK_LAUNCH();
       const uint32_t blocks = most < kBigPassBlocks ? most : kBigPassBlocks;
       for (int d = 0; d < lo_digits; ++d) {
-        ++st.epoch;
+        ++epoch;
         hipLaunchKernelGGL(k_big_pass, dim3(blocks), dim3(kSortThreads), 0, stream, L.big, d, lo_digits, kb[from],
-                           vb[from], kb[from ^ 1], vb[from ^ 1], w.status, st.epoch, w.misc);
+                           vb[from], kb[from ^ 1], vb[from ^ 1], w.status, epoch, w.misc);
         FC_CHECK_LAUNCH();
         ++sort_passes;
         from ^= 1;
