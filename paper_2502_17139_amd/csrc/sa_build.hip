@@ -1124,10 +1124,6 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_big_pass(BigWs g, int pass,
 
 // ------------------------------------------------------ group bookkeeping --
 
-struct SegFlags {
-  bool new_head, old_head, keep;
-};
-
 // A round's sorted list: round 0's 64-bit keys (one group), later (grp, lo).
 template <bool kRound0>
 struct Sorted {
@@ -1135,25 +1131,86 @@ struct Sorted {
   const uint32_t *grp, *lo;
 };
 
+// The heads among a wave's kSegItems * 64 consecutive positions from `base`,
+// a bit per position, in scalar registers: every element is loaded once (the
+// one before it comes from the lane below), and what follows from the heads -
+// an element's group start, the elements kept before it - is a bit search or
+// a population count instead of a scan over the lanes.  With the tile passes
+// reading each element's neighbours from memory again and scanning the heads
+// step by step over the lanes, all rounds of a 1B build took 46 + 8 ms
+// (k_seg_apply, k_seg_partials) against 23 + 3.6; of a 10M build 653 + 116
+// against 458 + 69 us.
 template <bool kRound0>
-__device__ __forceinline__ SegFlags seg_flags(const Sorted<kRound0>& a, uint32_t U, uint32_t r) {
-  SegFlags f{true, true, false};
-  bool last;
-  if constexpr (kRound0) {
-    const uint64_t kr = a.keys[r];
-    if (r > 0) f.new_head = kr != a.keys[r - 1], f.old_head = false;
-    last = r + 1 == U || a.keys[r + 1] != kr;
-  } else {
-    const uint32_t gr = a.grp[r], lr = a.lo[r];
-    if (r > 0) {
-      f.old_head = gr != a.grp[r - 1];
-      f.new_head = f.old_head || lr != a.lo[r - 1];
-    }
-    last = r + 1 == U || a.grp[r + 1] != gr || a.lo[r + 1] != lr;
+struct WaveHeads {
+  uint32_t U, base;
+  uint64_t nu[kSegItems + 1];    // new-group heads, and every position from U on; [kSegItems]: the next position
+  uint64_t old[kSegItems];       // old-group heads
+  uint32_t grp[kRound0 ? 1 : kSegItems];
+
+  // a step's positions below U
+  __device__ uint64_t valid(int j) const {
+    const uint64_t x0 = (uint64_t)base + (uint32_t)(j * fc::kWave);
+    return x0 >= U ? 0ull : U - x0 >= 64 ? ~0ull : (1ull << (U - x0)) - 1;
   }
-  f.keep = !(f.new_head && last);
-  return f;
-}
+  __device__ void load(const Sorted<kRound0>& in, uint32_t U_, uint32_t base_, uint32_t lane) {
+    U = U_;
+    base = base_;
+    const uint64_t end = (uint64_t)base + kSegItems * fc::kWave;
+    uint32_t k0[kSegItems], k1[kSegItems];  // round 0: the key's halves; later: lo, grp
+#pragma unroll
+    for (int j = 0; j < kSegItems; ++j) {
+      const uint64_t r = (uint64_t)base + (uint32_t)(j * fc::kWave) + lane;
+      if constexpr (kRound0) {
+        const uint64_t k = r < U ? in.keys[r] : 0ull;
+        k0[j] = (uint32_t)k;
+        k1[j] = (uint32_t)(k >> 32);
+      } else {
+        k0[j] = r < U ? in.lo[r] : 0u;
+        k1[j] = r < U ? in.grp[r] : 0u;
+        grp[j] = k1[j];
+      }
+    }
+    uint32_t c0 = 0, c1 = 0, e0 = 0, e1 = 0;  // the elements before and after the wave's
+    if (base > 0 && base <= U) at(in, base - 1, c0, c1);
+    if (end < U) at(in, end, e0, e1);
+#pragma unroll
+    for (int j = 0; j < kSegItems; ++j) {
+      const uint64_t x0 = (uint64_t)base + (uint32_t)(j * fc::kWave);
+      const bool first = x0 + lane == 0;
+      const uint32_t p0 = fc::wave_shr1(k0[j], c0), p1 = fc::wave_shr1(k1[j], c1);
+      nu[j] = fc::ballot(first || k0[j] != p0 || k1[j] != p1) | ~valid(j);
+      old[j] = (kRound0 ? fc::ballot(first) : fc::ballot(first || k1[j] != p1)) & valid(j);
+      c0 = (uint32_t)__builtin_amdgcn_readlane((int)k0[j], fc::kWave - 1);
+      c1 = (uint32_t)__builtin_amdgcn_readlane((int)k1[j], fc::kWave - 1);
+    }
+    nu[kSegItems] = end >= U || e0 != c0 || e1 != c1 ? 1ull : 0ull;
+  }
+  static __device__ void at(const Sorted<kRound0>& in, uint64_t r, uint32_t& a, uint32_t& b) {
+    if constexpr (kRound0) {
+      a = uniform((uint32_t)in.keys[r]);
+      b = uniform((uint32_t)(in.keys[r] >> 32));
+    } else {
+      a = uniform(in.lo[r]);
+      b = uniform(in.grp[r]);
+    }
+  }
+  // still tied: not a head right before another head
+  __device__ uint64_t keep(int j) const { return valid(j) & ~(nu[j] & ((nu[j] >> 1) | (nu[j + 1] << 63))); }
+  // last position of a step's mask (base + 64 j ..), or `before`
+  static __device__ uint32_t last(uint64_t mask, uint32_t x0, uint32_t before) {
+    return mask ? x0 + 63u - (uint32_t)__builtin_clzll(mask) : before;
+  }
+  // the wave's last new and old heads (0: none) and its kept elements
+  __device__ void totals(uint32_t& h, uint32_t& g, uint32_t& k) const {
+    h = g = k = 0;
+#pragma unroll
+    for (int j = 0; j < kSegItems; ++j) {
+      h = last(nu[j] & valid(j), base + (uint32_t)(j * fc::kWave), h);
+      g = last(old[j], base + (uint32_t)(j * fc::kWave), g);
+      k += (uint32_t)__popcll(keep(j));
+    }
+  }
+};
 
 // Per tile: last new-group head, last old-group head, number kept.
 template <bool kRound0>
@@ -1161,24 +1218,31 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_partials(Sorted<kRound0> in
                                                                 uint32_t* __restrict__ part_h,
                                                                 uint32_t* __restrict__ part_g,
                                                                 uint32_t* __restrict__ part_k) {
-  __shared__ uint32_t scratch[kSegThreads / fc::kWave + 1];
-  const uint32_t r0 = blockIdx.x * kSegTile + threadIdx.x;
-  uint32_t mh = 0, mg = 0, kc = 0;
-  for (int j = 0; j < kSegItems; ++j) {
-    const uint32_t r = r0 + (uint32_t)j * kSegThreads;  // coalesced; max and sum ignore the order
-    if (r >= U) break;
-    const SegFlags f = seg_flags(in, U, r);
-    if (f.new_head) mh = r;
-    if (f.old_head) mg = r;
-    kc += f.keep ? 1u : 0u;
+  constexpr int kWaves = kSegThreads / fc::kWave;
+  __shared__ uint32_t s_tot[3][kWaves];
+  const int w = (int)uniform(threadIdx.x / fc::kWave);
+  const uint32_t lane = (uint32_t)fc::lane_id();
+  const uint32_t base = blockIdx.x * kSegTile + (uint32_t)(w * kSegItems * fc::kWave);
+  WaveHeads<kRound0> hd;
+  hd.load(in, U, base, lane);
+  uint32_t h, g, k;
+  hd.totals(h, g, k);
+  if (lane == 0) {
+    s_tot[0][w] = h;
+    s_tot[1][w] = g;
+    s_tot[2][w] = k;
   }
-  mh = fc::block_max<uint32_t>(mh, scratch);
-  mg = fc::block_max<uint32_t>(mg, scratch);
-  kc = fc::block_sum<uint32_t>(kc, scratch);
+  __syncthreads();
   if (threadIdx.x == 0) {
-    part_h[blockIdx.x] = mh;
-    part_g[blockIdx.x] = mg;
-    part_k[blockIdx.x] = kc;
+    h = g = k = 0;
+    for (int v = 0; v < kWaves; ++v) {
+      h = s_tot[0][v] > h ? s_tot[0][v] : h;
+      g = s_tot[1][v] > g ? s_tot[1][v] : g;
+      k += s_tot[2][v];
+    }
+    part_h[blockIdx.x] = h;
+    part_g[blockIdx.x] = g;
+    part_k[blockIdx.x] = k;
   }
 }
 
@@ -1276,9 +1340,8 @@ constexpr uint64_t kPairRanksMin = 1ull << 26;   // suffixes (4-byte ranks: 256 
 // go to rank[] directly (a random 4-byte write each), or, with kParts, into
 // the buckets of RankParts.  Wave w of
 // the tile takes positions [w * 1024, (w + 1) * 1024) of it, 64 consecutive
-// ones per step: the running head indexes and the kept count are wave scans
-// carried from step to step, started from the earlier waves' totals and the
-// tile prefix.
+// ones per step: the running head indexes and the kept count are carried from
+// step to step, started from the earlier waves' totals and the tile prefix.
 template <bool kRound0, bool kParts>
 __global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, const uint32_t* __restrict__ vals,
                                                              uint32_t U, const uint32_t* __restrict__ pre_h,
@@ -1294,75 +1357,71 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, c
   __shared__ uint32_t s_cnt[kParts ? kRadix : 1], s_start[kParts ? kRadix : 1], s_base[kParts ? kRadix : 1];
   __shared__ uint32_t s_scan[kWaves + 1];
   __shared__ uint64_t s_pair[kParts ? kSegTile : 1];
-  const int w = (int)threadIdx.x / fc::kWave;
+  const int w = (int)uniform(threadIdx.x / fc::kWave);
   const uint32_t lane = (uint32_t)fc::lane_id();
   const uint32_t base = blockIdx.x * kSegTile + (uint32_t)w * kPerWave;
   if (kParts) s_cnt[threadIdx.x] = 0;
-  // the wave's totals
-  uint32_t mh = 0, mg = 0, kc = 0;
+  uint32_t val[kSegItems];
+#pragma unroll
   for (int j = 0; j < kSegItems; ++j) {
-    const uint32_t r = base + (uint32_t)j * fc::kWave + lane;
-    if (r < U) {
-      const SegFlags f = seg_flags(in, U, r);
-      if (f.new_head) mh = r;
-      if (f.old_head) mg = r;
-      kc += f.keep ? 1u : 0u;
-    }
+    const uint64_t r = (uint64_t)base + (uint32_t)(j * fc::kWave) + lane;
+    val[j] = r < U ? vals[r] : 0u;
   }
-  mh = fc::wave_max<uint32_t>(mh);
-  mg = fc::wave_max<uint32_t>(mg);
-  kc = fc::wave_sum<uint32_t>(kc);
+  WaveHeads<kRound0> hd;
+  hd.load(in, U, base, lane);
+  uint32_t mh, mg, kc;
+  hd.totals(mh, mg, kc);
   if (lane == 0) {
     s_tot[0][w] = mh;
     s_tot[1][w] = mg;
     s_tot[2][w] = kc;
   }
   __syncthreads();
+  // running over the earlier tiles, the earlier waves and the wave's steps:
+  // the last new and old heads, the kept elements
   uint32_t hh = pre_h[blockIdx.x], gg = pre_g[blockIdx.x], out = pre_k[blockIdx.x];
   for (int v = 0; v < w; ++v) {
     hh = s_tot[0][v] > hh ? s_tot[0][v] : hh;
     gg = s_tot[1][v] > gg ? s_tot[1][v] : gg;
     out += s_tot[2][v];
   }
-  uint32_t pi[kParts ? kSegItems : 1], pr[kParts ? kSegItems : 1], pos[kParts ? kSegItems : 1];
+  hh = uniform(hh);
+  gg = uniform(gg);
+  out = uniform(out);
+  const uint64_t lt = fc::lanemask_lt(), le = lt | (1ull << lane);
+  uint32_t pr[kParts ? kSegItems : 1], pos[kParts ? kSegItems : 1];
 #pragma unroll
   for (int j = 0; j < kSegItems; ++j) {
-    const uint32_t r = base + (uint32_t)j * fc::kWave + lane;
-    const bool valid = r < U;
-    SegFlags f{false, false, false};
-    if (valid) f = seg_flags(in, U, r);
-    uint32_t hr = fc::wave_incl_max<uint32_t>(f.new_head ? r : 0u);
-    uint32_t gr = fc::wave_incl_max<uint32_t>(f.old_head ? r : 0u);
-    const uint32_t kr = fc::wave_incl_sum_u32(f.keep ? 1u : 0u);
-    hr = hr > hh ? hr : hh;
-    gr = gr > gg ? gr : gg;
+    const uint32_t x0 = base + (uint32_t)(j * fc::kWave);
+    const uint64_t nu = hd.nu[j] & hd.valid(j), keep = hd.keep(j);
+    const uint32_t hr = hd.last(nu & le, x0, hh), gr = hd.last(hd.old[j] & le, x0, gg);
+    const uint32_t kr = (uint32_t)__popcll(keep & lt);
     if (kParts) pos[j] = kNone;
-    if (valid) {
+    if ((hd.valid(j) >> lane) & 1) {
       uint32_t start = 0u;
-      if constexpr (!kRound0) start = in.grp[r];
-      const uint32_t i = vals[r];
+      if constexpr (!kRound0) start = hd.grp[j];
+      const uint32_t i = val[j];
       const uint32_t rk = start + (hr - gr);
       // in the first new group of its old group a suffix keeps its rank (the
       // old group start, already in rank[i]): only round 0 and the later
       // new groups write
       if (kRound0 || hr != gr) {
         if (kParts) {
-          pi[j] = i;
           pr[j] = rk;
           pos[j] = atomicAdd(&s_cnt[(i >> parts.shift) & (kRadix - 1)], 1u);
         } else {
           rank[i] = rk;
         }
       }
-      if (f.keep) {
-        val_next[out + kr - 1u] = i;
-        grp_next[out + kr - 1u] = rk;
+      if ((keep >> lane) & 1) {
+        val_next[out + kr] = i;
+        grp_next[out + kr] = rk;
       }
       else if (sa_out) sa_out[rk] = i;  // a singleton group: rk is the suffix's final index
     }
-    hh = __shfl(hr, fc::kWave - 1);
-    gg = __shfl(gr, fc::kWave - 1);
-    out += __shfl(kr, fc::kWave - 1);
+    hh = hd.last(nu, x0, hh);
+    gg = hd.last(hd.old[j], x0, gg);
+    out += (uint32_t)__popcll(keep);
   }
   if constexpr (kParts) {
     __syncthreads();
@@ -1374,7 +1433,8 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, c
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kSegItems; ++j)
-      if (pos[j] != kNone) s_pair[s_start[(pi[j] >> parts.shift) & (kRadix - 1)] + pos[j]] = ((uint64_t)pi[j] << 32) | pr[j];
+      if (pos[j] != kNone)
+        s_pair[s_start[(val[j] >> parts.shift) & (kRadix - 1)] + pos[j]] = ((uint64_t)val[j] << 32) | pr[j];
     __syncthreads();
     for (uint32_t x = threadIdx.x; x < all; x += kSegThreads) {
       const uint64_t p = s_pair[x];
