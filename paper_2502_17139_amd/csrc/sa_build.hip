@@ -519,6 +519,25 @@ __device__ __forceinline__ uint64_t look_back(const uint64_t* status, int64_t p,
   return excl;
 }
 
+// Stable rank of each wave's elements inside their digit: the elements of the
+// wave with the same digit before this lane's; wcnt counts the wave's digits
+// (zeroed before).  Every lane counts.
+__device__ __forceinline__ uint32_t wave_digit_rank(uint32_t d, uint16_t* wcnt) {
+  uint32_t lo = ~0u, hi = ~0u;  // the lanes with this lane's digit
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);  // the bit, in all 32
+    const uint64_t ones = fc::ballot(mine != 0);
+    lo &= ~((uint32_t)ones ^ mine);
+    hi &= ~((uint32_t)(ones >> 32) ^ mine);
+  }
+  const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+  const uint32_t old = wcnt[d];
+  if (below == 0) wcnt[d] = (uint16_t)(old + (uint32_t)(__popc(lo) + __popc(hi)));
+  __builtin_amdgcn_sched_barrier(0);  // one element after another: interleaved, their masks spill
+  return old + below;
+}
+
 __global__ void __launch_bounds__(kSortThreads) k_onesweep(const uint64_t* __restrict__ kin,
                                                            const uint32_t* __restrict__ vin,
                                                            uint64_t* __restrict__ kout, uint32_t* __restrict__ vout,
@@ -557,24 +576,10 @@ __global__ void __launch_bounds__(kSortThreads) k_onesweep(const uint64_t* __res
     k[j] = valid ? kin[base + idx] : ~0ull;
     v[j] = valid ? vin[base + idx] : 0u;
   }
-  const uint64_t lt = fc::lanemask_lt();
+  // what lies past the last tile's end has digit 255 and comes last: it counts
+  // nowhere but behind the tile's own elements
 #pragma unroll
-  for (int j = 0; j < kSortItems; ++j) {
-    const uint32_t idx = (uint32_t)(w * kSortItems * fc::kWave + j * fc::kWave + lane);
-    const bool valid = idx < nvalid;
-    const uint32_t d = (uint32_t)(k[j] >> shift) & 0xFF;
-    uint64_t peers = fc::ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t ones = fc::ballot(valid && bit);
-      peers &= bit ? ones : ~ones;
-    }
-    const uint32_t below = (uint32_t)__popcll(peers & lt);
-    const uint32_t old = s_wcnt[w][d];
-    if (valid && below == 0) s_wcnt[w][d] = (uint16_t)(old + (uint32_t)__popcll(peers));
-    rk[j] = old + below;
-  }
+  for (int j = 0; j < kSortItems; ++j) rk[j] = wave_digit_rank((uint32_t)(k[j] >> shift) & 0xFF, s_wcnt[w]);
   __syncthreads();
 
   // Per digit: offsets of each wave's elements, tile count, tile-local start.
@@ -655,24 +660,6 @@ constexpr int kSmallItems = kCap / kSmallThreads;
 constexpr uint32_t kCountMax = 48;  // groups up to this size are ranked by comparing all pairs
 constexpr int kMaxLoDigits = 4;
 constexpr uint32_t kNone = 0xFFFFFFFFu;
-
-// Stable rank of each wave's elements inside their digit: rk[j] = elements of
-// the wave with the same digit before element j of this lane; wcnt counts
-// the wave's digits (zeroed before).
-__device__ __forceinline__ uint32_t wave_digit_rank(uint32_t d, bool valid, uint64_t lt, uint16_t* wcnt) {
-  uint64_t peers = fc::ballot(valid);
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const bool bit = (d >> b) & 1u;
-    const uint64_t ones = fc::ballot(valid && bit);
-    peers &= bit ? ones : ~ones;
-  }
-  const uint32_t below = (uint32_t)__popcll(peers & lt);
-  const uint32_t old = wcnt[d];
-  if (valid && below == 0) wcnt[d] = (uint16_t)(old + (uint32_t)__popcll(peers));
-  __builtin_amdgcn_sched_barrier(0);  // one element after another: interleaved, their masks spill
-  return old + below;
-}
 
 // Window b takes the groups that start at list positions [b kWin, (b+1) kWin).
 // All but the last one end inside the window or right after it; the last one
@@ -864,7 +851,6 @@ __global__ void __launch_bounds__(kSmallThreads, 4) k_sort_small(const uint32_t*
   }
   const int items = (int)((nl + kSmallThreads - 1) / kSmallThreads);  // per lane; a wave's elements are contiguous
   const uint32_t cbase = (uint32_t)(w * items * fc::kWave);
-  const uint64_t lt = fc::lanemask_lt();
   const int passes = lo_digits + (nrg > 1 ? 1 : 0);
   uint32_t a[kSmallItems], b[kSmallItems], rk[kSmallItems];
   for (int ps = 0; ps < passes; ++ps) {
@@ -880,8 +866,9 @@ __global__ void __launch_bounds__(kSmallThreads, 4) k_sort_small(const uint32_t*
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
       if (j < items) {
-        const uint32_t d = ps < lo_digits ? (a[j] >> (8 * ps)) & 0xFF : b[j] >> 16;
-        rk[j] = wave_digit_rank(d, cbase + (uint32_t)(j * fc::kWave) + lane < nl, lt, s_wcnt[w]) | (d << 16);
+        const bool valid = cbase + (uint32_t)(j * fc::kWave) + lane < nl;  // the others: last, behind all (as above)
+        const uint32_t d = !valid ? 255u : ps < lo_digits ? (a[j] >> (8 * ps)) & 0xFF : b[j] >> 16;
+        rk[j] = wave_digit_rank(d, s_wcnt[w]) | (d << 16);
       }
     }
     __syncthreads();
@@ -1045,7 +1032,6 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_big_pass(BigWs g, int pass,
   const int lane = fc::lane_id();
   const uint32_t tiles = g.count[1];
   const uint32_t shift = (uint32_t)(8 * pass);
-  const uint64_t lt = fc::lanemask_lt();
   for (;;) {
     for (int i = tid; i < kWaves * kRadix; i += kSortThreads) (&s_wcnt[0][0])[i] = 0;
     if (tid == 0) s_tile = atomicAdd(&g.count[3 + pass], 1u);
@@ -1069,11 +1055,9 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_big_pass(BigWs g, int pass,
       v[j] = idx < nvalid ? vt[idx] : 0u;
     }
     const uint32_t hcount = g.hist[((uint64_t)gr * lo_digits + pass) * kRadix + tid];
+    // (past a group's end: digit 255, behind the tile's own elements)
 #pragma unroll
-    for (int j = 0; j < kSortItems; ++j) {
-      const uint32_t idx = (uint32_t)(w * kSortItems * fc::kWave + j * fc::kWave + lane);
-      rk[j] = wave_digit_rank((k[j] >> shift) & 0xFF, idx < nvalid, lt, s_wcnt[w]);
-    }
+    for (int j = 0; j < kSortItems; ++j) rk[j] = wave_digit_rank((k[j] >> shift) & 0xFF, s_wcnt[w]);
     __syncthreads();
     const uint32_t t = (uint32_t)tid;  // this thread's digit
     uint32_t total = 0;
