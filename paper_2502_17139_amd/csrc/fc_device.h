@@ -25,6 +25,7 @@ typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 // The same at any token of a text (two or four words at 2-byte alignment are
 // one load each too).
 typedef uint32_t u32_a2 __attribute__((aligned(2)));
+typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 
 // ---- DPP wave primitives (32-bit).  Within each row of 16 lanes values move

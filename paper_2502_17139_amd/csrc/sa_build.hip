@@ -63,6 +63,8 @@ constexpr uint32_t kSpinLimit = 1u << 22;
 constexpr int kLookWindow = 2;  // earlier tiles examined per look-back step (with the counts
                                 // published early, wider windows only add loads)
 
+enum class Mode { kPlain, kBatched, kExtend };
+
 constexpr uint64_t kFlagAgg = 1ull << 46;
 constexpr uint64_t kFlagInc = 2ull << 46;
 constexpr uint64_t kFlagMask = 3ull << 46;
@@ -100,26 +102,6 @@ struct LdsHist {
   }
 };
 
-// Round 0's keys and their digit histogram in one pass (a histogram pass of
-// its own reads the 8-byte keys once more: 3.5 of 7.6 ms at 1B suffixes).
-__global__ void __launch_bounds__(256) k_init_keys(const uint16_t* __restrict__ tok, uint32_t n, int tb,
-                                                     int digits, uint64_t* __restrict__ keys,
-                                                     uint32_t* __restrict__ vals, uint32_t* __restrict__ hist) {
-  __shared__ uint32_t s_hist[kMaxDigits][kRadix];
-  const LdsHist lh{s_hist};
-  lh.zero();
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t a = (uint64_t)tok[i] + 1;
-    const uint64_t b = (i + 1 < n) ? (uint64_t)tok[i + 1] + 1 : 0;
-    const uint64_t c = (i + 2 < n) ? (uint64_t)tok[i + 2] + 1 : 0;
-    const uint64_t key = (a << (2 * tb)) | (b << tb) | c;
-    keys[i] = key;
-    vals[i] = (uint32_t)i;
-    lh.add(key, digits);
-  }
-  lh.flush(digits, hist);
-}
-
 // Batched build: position i belongs to the segment r with off[r] <= i <
 // off[r+1] (the last r with off[r] <= i, so empty segments are skipped).
 __device__ __forceinline__ uint32_t segment_of(const uint64_t* __restrict__ off, uint32_t R, uint64_t i) {
@@ -129,28 +111,6 @@ __device__ __forceinline__ uint32_t segment_of(const uint64_t* __restrict__ off,
     if (off[mid] <= i) lo = mid; else hi = mid - 1;
   }
   return lo;
-}
-
-// Round 0 of a batched build: key = (segment, first `ntok` tokens as token+1
-// in tb bits, 0 past the segment's end), so suffixes of different segments
-// never share a group and every suffix ends at its own segment's end.
-__global__ void __launch_bounds__(256) k_init_keys_seg(const uint16_t* __restrict__ tok, uint32_t n,
-                                                         const uint64_t* __restrict__ off, uint32_t R, int tb,
-                                                         int ntok, int digits, uint64_t* __restrict__ keys,
-                                                         uint32_t* __restrict__ vals, uint32_t* __restrict__ hist) {
-  __shared__ uint32_t s_hist[kMaxDigits][kRadix];
-  const LdsHist lh{s_hist};
-  lh.zero();
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint32_t r = segment_of(off, R, i);
-    const uint64_t end = off[r + 1];
-    uint64_t key = r;
-    for (int x = 0; x < ntok; ++x) key = (key << tb) | (i + x < end ? (uint64_t)tok[i + x] + 1 : 0ull);
-    keys[i] = key;
-    vals[i] = (uint32_t)i;
-    lh.add(key, digits);
-  }
-  lh.flush(digits, hist);
 }
 
 // One bit per position that starts a segment (bits zeroed before).
@@ -310,30 +270,6 @@ __global__ void __launch_bounds__(256) k_ext_fix(const uint32_t* __restrict__ do
   olo[p] = ohi[p] = nlo[p];
 }
 
-// Ordering the new suffixes: prefix doubling as in the plain build, over the
-// o new positions only, with ins(p) as the most significant field of round
-// 0's key.  A new suffix's group label is ins(p) + rank[p] and an old
-// suffix's is its final index isa + (new suffixes with ins <= isa): both are
-// positions in the final array's order, so the rank of whatever follows the
-// first h tokens can be either kind.
-__global__ void __launch_bounds__(256) k_init_keys_ext(const uint16_t* __restrict__ tok, uint32_t o, uint64_t n,
-                                                         const uint32_t* __restrict__ ins, int two, int digits,
-                                                         uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                         uint32_t* __restrict__ hist) {
-  __shared__ uint32_t s_hist[kMaxDigits][kRadix];
-  const LdsHist lh{s_hist};
-  lh.zero();
-  for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < o; p += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t a = (uint64_t)tok[p] + 1;
-    const uint64_t b = (p + 1 < n) ? (uint64_t)tok[p + 1] + 1 : 0;
-    const uint64_t key = two ? (((uint64_t)ins[p] << 34) | (a << 17) | b) : (((uint64_t)ins[p] << 17) | a);
-    keys[p] = key;
-    vals[p] = (uint32_t)p;
-    lh.add(key, digits);
-  }
-  lh.flush(digits, hist);
-}
-
 __global__ void __launch_bounds__(256) k_ins_sorted(const uint64_t* __restrict__ keys, uint32_t o, int shift,
                                                       uint32_t* __restrict__ out) {
   const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -351,7 +287,6 @@ __device__ __forceinline__ uint32_t count_le(const uint32_t* __restrict__ s, uin
 }
 
 // The second half of a round's key: what the label of the position h on is.
-enum class Mode { kPlain, kBatched, kExtend };
 struct NextRank {
   const uint32_t* rank;
   const uint32_t* seg_bits;    // batched: a bit per position that starts a segment
@@ -461,6 +396,110 @@ __global__ void __launch_bounds__(256) k_ext_isa_old(const uint32_t* __restrict_
   isa_out[q + o] = j + (o ? count_new_le(ins_sorted, coarse, j) : 0u);
 }
 
+// --------------------------------------------------------- round 0's keys --
+
+
+// Round 0's keys, made from the text where they are needed: once for their
+// digit histogram and once in the first digit pass.  (Written out once, 12
+// bytes a suffix, and read back by the first pass, 1B suffixes took 3.9 ms
+// before and as long in that pass; now 1.9.)
+//   plain: the first three tokens, as token + 1 in tb bits, 0 past the end.
+//   batched: (segment, first ntok tokens, 0 past the segment's end), so
+//     suffixes of different segments never share a group and every suffix
+//     ends at its own segment's end.
+//   extension: the n new positions, with ins(p) as the most significant field
+//     and one or two tokens in 17 bits after it.  A new suffix's group label
+//     is ins(p) + rank[p] and an old suffix's is its final index isa + (new
+//     suffixes with ins <= isa): both are positions in the final array's
+//     order, so the rank of whatever follows the first h tokens can be either
+//     kind.
+template <Mode M>
+struct FirstKeys {
+  const uint16_t* __restrict__ tok;
+  uint64_t n;     // tokens of the text
+  int tb, ntok;
+  const uint64_t* __restrict__ off;  // batched: R segments
+  uint32_t R;
+  const uint32_t* __restrict__ ins;  // extension
+
+  // The keys of a wave's kItems * 64 positions from `first` on, below `count`
+  // (the others: ~0).  Away from the text's end, and inside one segment, all
+  // loads are issued together.
+  template <int kItems>
+  __device__ void wave_keys(uint64_t first, uint32_t count, uint32_t lane, uint64_t (&k)[kItems]) const {
+    const uint64_t last = first + kItems * fc::kWave - 1;
+    uint32_t r = 0;
+    uint64_t end = n;
+    if constexpr (M == Mode::kBatched) {
+      if (first < count) {
+        r = uniform(segment_of(off, R, first));
+        end = off[r + 1];
+      }
+    }
+    if (last < count && last < end && last + 4 <= n) {
+      fc::u32x2_a2 w[kItems];
+#pragma unroll
+      for (int j = 0; j < kItems; ++j) w[j] = *(const fc::u32x2_a2*)(tok + first + (uint32_t)(j * fc::kWave) + lane);
+#pragma unroll
+      for (int j = 0; j < kItems; ++j) {
+        const uint64_t i = first + (uint32_t)(j * fc::kWave) + lane;
+        k[j] = key(i, r, (w[j][0] & 0xFFFFu) + 1, i + 1 < end ? (w[j][0] >> 16) + 1 : 0,
+                   i + 2 < end ? (w[j][1] & 0xFFFFu) + 1 : 0);
+      }
+      return;
+    }
+#pragma unroll 1
+    for (int j = 0; j < kItems; ++j) {
+      const uint64_t i = first + (uint32_t)(j * fc::kWave) + lane;
+      uint64_t x = ~0ull;
+      if (i < count) {
+        if constexpr (M == Mode::kBatched)
+          while (i >= end) end = off[++r + 1];
+        x = key(i, r, (uint32_t)tok[i] + 1, i + 1 < end ? (uint32_t)tok[i + 1] + 1 : 0,
+                i + 2 < end ? (uint32_t)tok[i + 2] + 1 : 0);
+      }
+      set(k, j, x);
+    }
+  }
+  // k[j] = x with j known at run time only: registers cannot be indexed
+  template <int kItems>
+  static __device__ void set(uint64_t (&k)[kItems], int j, uint64_t x) {
+#pragma unroll
+    for (int u = 0; u < kItems; ++u) k[u] = u == j ? x : k[u];
+  }
+  // position i of segment r, tokens as token + 1
+  __device__ uint64_t key(uint64_t i, uint32_t r, uint32_t a, uint32_t b, uint32_t c) const {
+    if constexpr (M == Mode::kPlain) return ((uint64_t)a << (2 * tb)) | ((uint64_t)b << tb) | c;
+    if constexpr (M == Mode::kBatched) {
+      const uint64_t two = ((((uint64_t)r << tb) | a) << tb) | b;
+      return ntok == 3 ? (two << tb) | c : two;
+    }
+    return ntok == 2 ? ((uint64_t)ins[i] << 34) | ((uint64_t)a << 17) | b : ((uint64_t)ins[i] << 17) | a;
+  }
+};
+
+// The keys' digit histogram.
+template <Mode M>
+__global__ void __launch_bounds__(256) k_first_hist(FirstKeys<M> fk, uint32_t count, int digits,
+                                                     uint32_t* __restrict__ hist) {
+  __shared__ uint32_t s_hist[kMaxDigits][kRadix];
+  const LdsHist lh{s_hist};
+  lh.zero();
+  const uint32_t lane = (uint32_t)fc::lane_id();
+  constexpr int kItems = 4;
+  constexpr uint32_t kSpan = kItems * fc::kWave;
+  const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x / fc::kWave);
+  for (uint64_t x = (uint64_t)blockIdx.x * (blockDim.x / fc::kWave) + uniform(threadIdx.x / fc::kWave); x * kSpan < count;
+       x += waves) {
+    uint64_t k[kItems];
+    fk.template wave_keys<kItems>(x * kSpan, count, lane, k);
+#pragma unroll
+    for (int j = 0; j < kItems; ++j)
+      if (x * kSpan + (uint32_t)(j * fc::kWave) + lane < count) lh.add(k[j], digits);
+  }
+  lh.flush(digits, hist);
+}
+
 // ------------------------------------------------------------ histogram ---
 
 // One workgroup of 256 threads per digit: its offsets (exclusive scan).
@@ -538,7 +577,9 @@ __device__ __forceinline__ uint32_t wave_digit_rank(uint32_t d, uint16_t* wcnt) 
   return old + below;
 }
 
-__global__ void __launch_bounds__(kSortThreads) k_onesweep(const uint64_t* __restrict__ kin,
+// kFirst: the pass that makes the keys (kin and vin unused).
+template <Mode M, bool kFirst>
+__global__ void __launch_bounds__(kSortThreads) k_onesweep(FirstKeys<M> fk, const uint64_t* __restrict__ kin,
                                                            const uint32_t* __restrict__ vin,
                                                            uint64_t* __restrict__ kout, uint32_t* __restrict__ vout,
                                                            uint32_t U, uint32_t shift,
@@ -569,12 +610,18 @@ __global__ void __launch_bounds__(kSortThreads) k_onesweep(const uint64_t* __res
   uint64_t k[kSortItems];
   uint32_t v[kSortItems];
   uint32_t rk[kSortItems];
+  if constexpr (kFirst)
+    fk.template wave_keys<kSortItems>(base + (uint32_t)(w * kSortItems * fc::kWave), U, (uint32_t)lane, k);
 #pragma unroll
   for (int j = 0; j < kSortItems; ++j) {
     const uint32_t idx = (uint32_t)(w * kSortItems * fc::kWave + j * fc::kWave + lane);
     const bool valid = idx < nvalid;
-    k[j] = valid ? kin[base + idx] : ~0ull;
-    v[j] = valid ? vin[base + idx] : 0u;
+    if constexpr (kFirst) {
+      v[j] = (uint32_t)(base + idx);
+    } else {
+      k[j] = valid ? kin[base + idx] : ~0ull;
+      v[j] = valid ? vin[base + idx] : 0u;
+    }
   }
   // what lies past the last tile's end has digit 255 and comes last: it counts
   // nowhere but behind the tile's own elements
@@ -1805,16 +1852,24 @@ int bit_length(uint64_t x) {
 // carried alongside, the passes alternating between the two buffers; w.hist
 // holds the digits' counts.  *result is the index (0 or 1) of the buffers that
 // hold the result.
-fc_status radix_passes(BuildWs& w, uint32_t U, int digits, uint32_t& epoch, hipStream_t stream, int* result) {
+template <Mode M>
+fc_status radix_passes(BuildWs& w, const FirstKeys<M>& fk, uint32_t U, int digits, uint32_t& epoch,
+                       hipStream_t stream, int* result) {
+  const uint32_t hist_blocks = fc::div_up(U, 1024) < (uint32_t)kHistBlocks ? fc::div_up(U, 1024) : kHistBlocks;
+  hipLaunchKernelGGL(k_first_hist<M>, dim3(hist_blocks), dim3(256), 0, stream, fk, U, digits, w.hist);
+  FC_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_hist_scan, dim3(digits), dim3(256), 0, stream, w.hist, w.offsets);
   FC_CHECK_LAUNCH();
   int cur = 0;
   const uint32_t tiles = fc::div_up(U, kSortTile);
   for (int d = 0; d < digits; ++d) {
     ++epoch;
-    hipLaunchKernelGGL(k_onesweep, dim3(tiles), dim3(kSortThreads), 0, stream, w.keys[cur], w.vals[cur],
-                       w.keys[cur ^ 1], w.vals[cur ^ 1], U, (uint32_t)(8 * d), w.offsets + d * kRadix, w.status,
-                       w.tickets + d, epoch, w.misc);
+    auto pass = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kSortThreads), 0, stream, fk, w.keys[cur], w.vals[cur],
+                         w.keys[cur ^ 1], w.vals[cur ^ 1], U, (uint32_t)(8 * d), w.offsets + d * kRadix, w.status,
+                         w.tickets + d, epoch, w.misc);
+    };
+    d == 0 ? pass(k_onesweep<M, true>) : pass(k_onesweep<M, false>);
     FC_CHECK_LAUNCH();
     cur ^= 1;
   }
@@ -1856,17 +1911,13 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
   // every rank + 1 <= n (an extension's labels: <= the whole text) fits in lo_digits bytes
   const int lo_digits = (bit_length(ext ? ext->n : n) + 7) / 8;
   uint32_t epoch = 0;  // of the status words: one per pass
-  uint64_t h;
   int key0_bits;
   int ext_shift = 0;
-  const uint32_t init_blocks = fc::div_up(N, 1024) < (uint32_t)kHistBlocks ? fc::div_up(N, 1024) : kHistBlocks;
+  FirstKeys<M> fk{tokens, ext ? ext->n : n, 17, 3, w.seg_off, n_seg, ext ? ext->ins : nullptr};
   if (M == Mode::kExtend) {
-    const int two = ext->n_old_bits + 34 <= 64;
-    ext_shift = two ? 34 : 17;
-    h = two ? 2 : 1;
+    fk.ntok = ext->n_old_bits + 34 <= 64 ? 2 : 1;
+    ext_shift = 17 * fk.ntok;
     key0_bits = ext_shift + ext->n_old_bits;
-    hipLaunchKernelGGL(k_init_keys_ext, dim3(init_blocks), dim3(256), 0, stream, tokens, N, ext->n, ext->ins, two,
-                       (key0_bits + 7) / 8, w.keys[0], w.vals[0], w.hist);
   } else {
     // token + 1 in tb bits: the largest token decides tb (misc[10] is zero)
     const uint32_t blocks = fc::div_up(N, 2048) < kMaxTokenBlocks ? fc::div_up(N, 2048) : kMaxTokenBlocks;
@@ -1875,28 +1926,20 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
     uint32_t mx = 0;
     FC_CHECK_HIP(hipMemcpyAsync(&mx, w.misc + 10, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
     FC_CHECK_HIP(hipStreamSynchronize(stream));
-    const int tb = bit_length((uint64_t)mx + 1);
-    if (M == Mode::kPlain) {
-      h = 3;
-      key0_bits = 3 * tb;
-      hipLaunchKernelGGL(k_init_keys, dim3(init_blocks), dim3(256), 0, stream, tokens, N, tb, (key0_bits + 7) / 8,
-                         w.keys[0], w.vals[0], w.hist);
-    } else {
-      const int seg_bits = bit_length(n_seg - 1);
-      const int ntok = seg_bits + 3 * tb <= 64 ? 3 : 2;  // 17-bit tokens and up to 2^30 segments: two always fit
-      h = (uint64_t)ntok;
-      key0_bits = seg_bits + ntok * tb;
+    fk.tb = bit_length((uint64_t)mx + 1);
+    const int seg_bits = M == Mode::kBatched ? bit_length(n_seg - 1) : 0;
+    if (M == Mode::kBatched) {
+      fk.ntok = seg_bits + 3 * fk.tb <= 64 ? 3 : 2;  // 17-bit tokens and up to 2^30 segments: two always fit
       FC_CHECK_HIP(hipMemsetAsync(w.seg_bits, 0, sizeof(uint32_t) * (n / 32 + 1), stream));
       hipLaunchKernelGGL(k_seg_starts, dim3(fc::div_up(n_seg, 256)), dim3(256), 0, stream, w.seg_off, n_seg, N,
                          w.seg_bits);
       FC_CHECK_LAUNCH();
-      hipLaunchKernelGGL(k_init_keys_seg, dim3(init_blocks), dim3(256), 0, stream, tokens, N, w.seg_off, n_seg, tb,
-                         ntok, (key0_bits + 7) / 8, w.keys[0], w.vals[0], w.hist);
     }
+    key0_bits = seg_bits + fk.ntok * fk.tb;
   }
-  FC_CHECK_LAUNCH();
+  uint64_t h = (uint64_t)fk.ntok;
   int res = 0;
-  const fc_status s = radix_passes(w, N, (key0_bits + 7) / 8, epoch, stream, &res);
+  const fc_status s = radix_passes<M>(w, fk, N, (key0_bits + 7) / 8, epoch, stream, &res);
   if (s != FC_OK) return s;
   int sort_passes = (key0_bits + 7) / 8;
   if (M == Mode::kExtend) {
