@@ -70,8 +70,11 @@ class FcRetrieveParams(ctypes.Structure):
     _fields_ = [("n_max", ctypes.c_int32), ("n_min", ctypes.c_int32), ("k", ctypes.c_int32), ("m", ctypes.c_int32)]
 
 
+_Alpha = ctypes.c_uint32 * FC_MAX_SOURCES
+
+
 class FcTreeParams(ctypes.Structure):
-    _fields_ = [("c", ctypes.c_int32), ("alpha", ctypes.c_uint32 * FC_MAX_SOURCES)]
+    _fields_ = [("c", ctypes.c_int32), ("alpha", _Alpha)]
 
 
 _P = ctypes.c_void_p
@@ -183,14 +186,38 @@ def _check(fn: str, code: int) -> None:
         raise FcError(fn, code, lib().fc_status_string(code).decode())
 
 
-def _ptr(t: torch.Tensor | None) -> ctypes.c_void_p:
+def _ptr(t: torch.Tensor | None):
+    """Device address of a contiguous device tensor (None: null)."""
     if t is None:
-        return ctypes.c_void_p(0)
+        return None
     if not t.is_cuda:
         raise ValueError("device tensor expected")
     if not t.is_contiguous():
         raise ValueError("contiguous tensor expected")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _ptrs(tensors) -> list:
+    """_ptr of each tensor.  One sequence is decoded in a few microseconds of
+    kernels, so a call's host work is what it waits for: the checks of its
+    dozen tensors run in one loop each (three calls of a drafting step: 45 us
+    with a function call per tensor and check, 34 now)."""
+    ptrs = []
+    for t in tensors:
+        if not t.is_cuda:
+            raise ValueError("device tensor expected")
+        if not t.is_contiguous():
+            raise ValueError("contiguous tensor expected")
+        ptrs.append(t.data_ptr())
+    return ptrs
+
+
+def _refuse(name: str, t: torch.Tensor | None, dtype, shape):
+    if t is None:
+        raise ValueError(f"{name} is required")
+    if t.dtype != dtype:
+        raise ValueError(f"{name} must be {dtype}, not {t.dtype}")
+    raise ValueError(f"{name} must have shape {tuple(int(x) for x in shape)}, not {tuple(t.shape)}")
 
 
 def _expect(name: str, t: torch.Tensor | None, dtype, shape=None, optional: bool = False) -> None:
@@ -199,30 +226,31 @@ def _expect(name: str, t: torch.Tensor | None, dtype, shape=None, optional: bool
     if t is None:
         if optional:
             return
-        raise ValueError(f"{name} is required")
-    if t.dtype != dtype:
-        raise ValueError(f"{name} must be {dtype}, not {t.dtype}")
-    if shape is not None and t.shape != shape:
-        raise ValueError(f"{name} must have shape {tuple(int(x) for x in shape)}, not {tuple(t.shape)}")
+        _refuse(name, t, dtype, shape)
+    if t.dtype != dtype or (shape is not None and t.shape != shape):
+        _refuse(name, t, dtype, shape)
 
 
-def _expect_outputs(out: dict, fields, shapes: dict, dtypes: dict) -> None:
-    for f in fields:
-        _expect(f, out.get(f), dtypes[f], shapes[f])
+def _expect_all(names, tensors, dtypes, shapes) -> None:
+    """_expect of each tensor."""
+    for name, t, dtype, shape in zip(names, tensors, dtypes, shapes):
+        if t is None or t.dtype != dtype or t.shape != shape:
+            _refuse(name, t, dtype, shape)
 
 
-_RETRIEVE_DTYPES = dict(match_n=torch.int32, range_lo=torch.uint32, range_cnt=torch.uint32, taken=torch.int32,
-                        cont_pos=torch.uint32, cont_src=torch.uint8, cont_len=torch.uint8, cont_tok=torch.uint16)
+_RETRIEVE_DTYPES = (torch.int32, torch.uint32, torch.uint32, torch.int32, torch.uint32, torch.uint8, torch.uint8,
+                    torch.uint16)
 
 
-def _retrieve_shapes(n_rows: int, S: int, k: int, m: int) -> dict:
-    return dict(match_n=(n_rows, S), range_lo=(n_rows, S), range_cnt=(n_rows, S), taken=(n_rows, S),
-                cont_pos=(n_rows, k), cont_src=(n_rows, k), cont_len=(n_rows, k), cont_tok=(n_rows, k, m))
+def _retrieve_shapes(n_rows: int, S: int, k: int, m: int) -> tuple:
+    per_store, slots = (n_rows, S), (n_rows, k)
+    return (per_store, per_store, per_store, per_store, slots, slots, slots, (n_rows, k, m))
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())  # torch.cuda.current_stream().cuda_stream
 
 
 def _empty(shape, dtype, device) -> torch.Tensor:
@@ -442,14 +470,15 @@ def fc_retrieve(stores, ctx: torch.Tensor, n_max: int = 16, n_min: int = 2, k: i
     n_rows = out["taken"].shape[0] if "taken" in out else B
     if rows is None and n_rows != B:
         raise ValueError("without a row map the outputs need one row per query")
-    _expect_outputs(out, RETRIEVE_FIELDS, _retrieve_shapes(n_rows, S, k, m), _RETRIEVE_DTYPES)
+    results = [out.get(f) for f in RETRIEVE_FIELDS]
+    _expect_all(RETRIEVE_FIELDS, results, _RETRIEVE_DTYPES, _retrieve_shapes(n_rows, S, k, m))
     _expect("rows", rows, torch.int32, (B,), optional=True)
     _expect("workspace", workspace, torch.uint8, optional=True)
     need = int(lib().fc_retrieve_workspace_bytes(B, S, p))
     if workspace is None and need > 0:
         workspace = _empty(need, torch.uint8, ctx.device)
     _check("fc_retrieve", lib().fc_retrieve(
-        views, S, _ptr(ctx), B, L, p, *[_ptr(out[f]) for f in RETRIEVE_FIELDS], _ptr(rows), n_rows,
+        views, S, _ptr(ctx), B, L, p, *_ptrs(results), _ptr(rows), n_rows,
         _ptr(workspace), 0 if workspace is None else workspace.numel(), _stream(stream)))
     return out
 
@@ -474,10 +503,11 @@ def fc_retrieve_noalloc(stores, ctx: torch.Tensor, n_max: int = 16, n_min: int =
     n_rows = out["taken"].shape[0] if "taken" in out else B
     if rows is None and n_rows != B:
         raise ValueError("without a row map the outputs need one row per query")
-    _expect_outputs(out, RETRIEVE_FIELDS, _retrieve_shapes(n_rows, S, k, m), _RETRIEVE_DTYPES)
+    results = [out.get(f) for f in RETRIEVE_FIELDS]
+    _expect_all(RETRIEVE_FIELDS, results, _RETRIEVE_DTYPES, _retrieve_shapes(n_rows, S, k, m))
     _expect("rows", rows, torch.int32, (B,), optional=True)
     _check("fc_retrieve_noalloc", lib().fc_retrieve_noalloc(
-        views, S, _ptr(ctx), B, L, p, *[_ptr(out[f]) for f in RETRIEVE_FIELDS], _ptr(rows), n_rows,
+        views, S, _ptr(ctx), B, L, p, *_ptrs(results), _ptr(rows), n_rows,
         _stream(stream)))
     return out
 
@@ -506,11 +536,12 @@ def fc_cache_retrieve(texts: torch.Tensor, text_len: torch.Tensor, ctx: torch.Te
     n_rows = out["taken"].shape[0] if "taken" in out else B
     if rows is None and n_rows != B:
         raise ValueError("without a row map the outputs need one row per query")
-    _expect_outputs(out, RETRIEVE_FIELDS, _retrieve_shapes(n_rows, 1, k, m), _RETRIEVE_DTYPES)
+    results = [out.get(f) for f in RETRIEVE_FIELDS]
+    _expect_all(RETRIEVE_FIELDS, results, _RETRIEVE_DTYPES, _retrieve_shapes(n_rows, 1, k, m))
     _expect("rows", rows, torch.int32, (B,), optional=True)
     _check("fc_cache_retrieve", lib().fc_cache_retrieve(
         _ptr(texts), stride, n_texts, _ptr(text_len), _ptr(text_row), _ptr(ctx), B, L,
-        FcRetrieveParams(n_max, n_min, k, m), *[_ptr(out[f]) for f in RETRIEVE_FIELDS], _ptr(rows),
+        FcRetrieveParams(n_max, n_min, k, m), *_ptrs(results), _ptr(rows),
         out["taken"].shape[0], _stream(stream)))
     return out
 
@@ -574,6 +605,7 @@ def fc_tree_attention(q: torch.Tensor, k_tree: torch.Tensor, v_tree: torch.Tenso
 # ----------------------------------------------------------------- tree ----
 
 TREE_FIELDS = ("num_nodes", "node_tok", "parent", "weight", "pos_ids", "mask")
+_TREE_DTYPES = (torch.int32, torch.int32, torch.int32, torch.uint32, torch.int32, torch.int32)
 
 
 def tree_outputs(B: int, c: int, device) -> dict:
@@ -606,20 +638,19 @@ def fc_build_tree(taken: torch.Tensor, cont_len: torch.Tensor, cont_tok: torch.T
     a = list(alpha)[:S]
     if len(a) != S:
         raise ValueError("need one alpha per store")
-    tp = FcTreeParams(c, (ctypes.c_uint32 * FC_MAX_SOURCES)(*(a + [0] * (FC_MAX_SOURCES - S))))
+    tp = FcTreeParams(c, _Alpha(*a))  # 0 for the stores past S
     if out is None:
         out = tree_outputs(B, c, ctx.device)
     R = c + 1
-    _expect_outputs(out, TREE_FIELDS, dict(num_nodes=(B,), node_tok=(B, R), parent=(B, R), weight=(B, R),
-                                           pos_ids=(B, R), mask=(B, R, R)),
-                    dict(num_nodes=torch.int32, node_tok=torch.int32, parent=torch.int32, weight=torch.uint32,
-                         pos_ids=torch.int32, mask=torch.int32))
+    rows_of = (B, R)
+    results = [out.get(f) for f in TREE_FIELDS]
+    _expect_all(TREE_FIELDS, results, _TREE_DTYPES, ((B,), rows_of, rows_of, rows_of, rows_of, (B, R, R)))
     need = fc_build_tree_workspace_bytes(B)
     if workspace is None and need > 0:
         workspace = _empty(need, torch.uint8, ctx.device)
     _check("fc_build_tree", lib().fc_build_tree(
         _ptr(taken), _ptr(cont_len), _ptr(cont_tok), _ptr(ctx), B, L, S, k, m, tp,
-        *[_ptr(out[f]) for f in TREE_FIELDS], _ptr(rows), n_rows, _ptr(workspace),
+        *_ptrs(results), _ptr(rows), n_rows, _ptr(workspace),
         0 if workspace is None else workspace.numel(), _stream(stream)))
     return out
 
@@ -627,6 +658,7 @@ def fc_build_tree(taken: torch.Tensor, cont_len: torch.Tensor, cont_tok: torch.T
 # ----------------------------------------------------------- acceptance ----
 
 ACCEPT_FIELDS = ("accept_len", "accept_tok", "last_node")
+_VERIFY_FIELDS = ("num_nodes", "node_tok", "parent", "pos_ids")
 
 
 def accept_outputs(B: int, m: int, device) -> dict:
@@ -637,18 +669,15 @@ def accept_outputs(B: int, m: int, device) -> dict:
 def fc_verify_accept(tree: dict, target: torch.Tensor, m: int = 10, out: dict | None = None, stream=None) -> dict:
     """Longest accepted root path against per-row target tokens ([B][c+1])."""
     B, R = tree["node_tok"].shape
-    _expect("num_nodes", tree["num_nodes"], torch.int32, (B,))
-    for f in ("node_tok", "parent", "pos_ids"):
-        _expect(f, tree[f], torch.int32, (B, R))
+    nodes = [tree[f] for f in _VERIFY_FIELDS]
+    _expect_all(_VERIFY_FIELDS, nodes, (torch.int32,) * 4, ((B,), (B, R), (B, R), (B, R)))
     _expect("target", target, torch.int32, (B, R))
-    if out is not None:
-        _expect_outputs(out, ACCEPT_FIELDS, dict(accept_len=(B,), accept_tok=(B, m + 1), last_node=(B,)),
-                        dict(accept_len=torch.int32, accept_tok=torch.int32, last_node=torch.int32))
     if out is None:
         out = accept_outputs(B, m, target.device)
+    results = [out.get(f) for f in ACCEPT_FIELDS]
+    _expect_all(ACCEPT_FIELDS, results, (torch.int32,) * 3, ((B,), (B, m + 1), (B,)))
     _check("fc_verify_accept", lib().fc_verify_accept(
-        _ptr(tree["num_nodes"]), _ptr(tree["node_tok"]), _ptr(tree["parent"]), _ptr(tree["pos_ids"]),
-        _ptr(target), B, R - 1, m, *[_ptr(out[f]) for f in ACCEPT_FIELDS], _stream(stream)))
+        *_ptrs(nodes), _ptr(target), B, R - 1, m, *_ptrs(results), _stream(stream)))
     return out
 
 
