@@ -1159,7 +1159,13 @@ constexpr int kFlatWideMaxB = 256;
 template <int MAXM>
 constexpr int flat_rows() { return MAXM <= 10 ? 5 : 4; }
 constexpr int kFlatShortCap = 256;  // short strings a query may keep in LDS
-constexpr int kFlatList = 2048;     // shared trie nodes (two strings or more) listed in LDS
+// Shared trie nodes (two strings or more) listed in LDS, at least; as many more
+// as LDS has room for without costing a resident workgroup (flat_list).  A
+// query with more of them than the list holds walks its trie five times
+// instead, and one such query sets its batch's time: 2,433 shared nodes of
+// 5,000 strings 51.8 us against 25 for queries a little smaller (1,024-thread
+// workgroups 39.6 against 21).
+constexpr int kFlatList = 2048;
 
 struct FlatLayout {
   size_t perm, lm, A, sstr, slen, sidx, sh_key, sh_w, total;
@@ -1177,7 +1183,8 @@ __host__ __device__ inline bool flat_masks(int k, int maxm, bool with_A) {
 // maxm: the instantiation's row width (rows of maxm/2 32-bit words);
 // cap: short strings held; with_A: alpha prefix sums (stores of different
 // weights); S > 2: the short strings' merged order needs its own index.
-__host__ __device__ inline FlatLayout flat_layout(int k, int maxm, int cap, int S, bool with_A) {
+__host__ __device__ inline FlatLayout flat_layout(int k, int maxm, int cap, int S, bool with_A,
+                                                          int list = kFlatList) {
   FlatLayout t;
   size_t o = 0;
   t.perm = o;  // k uint16: merged position -> slot
@@ -1197,9 +1204,9 @@ __host__ __device__ inline FlatLayout flat_layout(int k, int maxm, int cap, int 
   t.sidx = o;  // cap uint16: short merged order -> LDS row
   if (S > 2) o = align_up(o + (size_t)cap * 2, 16);
   t.sh_key = o;  // shared trie nodes in (position, depth) order: position << 5 | depth
-  o = align_up(o + (size_t)kFlatList * 4, 16);
+  o = align_up(o + (size_t)list * 4, 16);
   t.sh_w = o;  // their weights (16 bits when no weight can exceed them)
-  o = align_up(o + (size_t)kFlatList * (with_A ? 4 : 2), 16);
+  o = align_up(o + (size_t)list * (with_A ? 4 : 2), 16);
   t.total = o;
   return t;
 }
@@ -1376,7 +1383,7 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
                                                             const uint8_t* __restrict__ cont_len,
                                                             const uint16_t* __restrict__ cont_tok,
                                                             const uint16_t* __restrict__ ctx, int L, int S, int k,
-                                                            int m, int c, Alpha alpha, int cap, int words,
+                                                            int m, int c, Alpha alpha, int cap, int list, int words,
                                                             const int32_t* __restrict__ order, int self_plan, int B,
                                                             const int32_t* __restrict__ rows, int n_rows,
                                                             int32_t* __restrict__ num_nodes,
@@ -1545,7 +1552,7 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
     return;
   }
 
-  const FlatLayout lay = flat_layout(k, MAXM, cap, S, !NARROW);
+  const FlatLayout lay = flat_layout(k, MAXM, cap, S, !NARROW, list);
   uint16_t* perm = (uint16_t*)(smem + lay.perm);
   LMT* lm = (LMT*)(smem + lay.lm);
   uint32_t* A = (uint32_t*)(smem + lay.A);
@@ -1902,7 +1909,7 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
       n_tot = tot3[1];
       sh_tot = tot3[2];
     }
-    const bool listed = sh_tot <= (uint32_t)kFlatList;
+    const bool listed = sh_tot <= (uint32_t)list;
 
     // The walk's set-up, done once and only when a walk is needed: the next
     // head per depth after each chunk, and the alpha prefix sums of stores
@@ -2455,6 +2462,17 @@ fc_status launch_fast(const int32_t* taken, const uint8_t* cont_len, const uint1
   return FC_OK;
 }
 
+// Entries of the list of shared nodes: a list of k strings of m tokens has at
+// most k m / 2 shared nodes, `room` bytes of LDS are there for the layout.
+constexpr size_t kLdsStep = 1280;  // LDS is allocated in pieces of this size
+int flat_list(int k, int m, int maxm, int cap, int S, bool with_A, size_t room) {
+  const size_t least = flat_layout(k, maxm, cap, S, with_A).total;
+  if (least >= room) return kFlatList;
+  const size_t most = (size_t)k * (size_t)m / 2, fit = kFlatList + (room - least) / (with_A ? 8 : 6);
+  const size_t list = (most < fit ? most : fit) & ~(size_t)15;  // whole 16-byte pieces: no padding on top
+  return list > (size_t)kFlatList ? (int)list : kFlatList;
+}
+
 // The flat path when its layout fits (with as many short strings as a query
 // can have, or else as many as fit, the rest of the queries going to the
 // full-LDS kernel through a list); returns FC_ERR_UNSUPPORTED when it does
@@ -2473,8 +2491,7 @@ fc_status launch_flat(const int32_t* taken, const uint8_t* cont_len, const uint1
   // typical batches a second store's list holds a few strings)
   int cap = worst_short < kFlatShortCap ? worst_short : kFlatShortCap;
   while (cap > 0 && flat_layout(k, MAXM, cap, S, !NARROW).total > budget) cap = cap * 7 / 8;
-  const FlatLayout lay = flat_layout(k, MAXM, cap, S, !NARROW);
-  if (lay.total > budget) return FC_ERR_UNSUPPORTED;
+  if (flat_layout(k, MAXM, cap, S, !NARROW).total > budget) return FC_ERR_UNSUPPORTED;
   // with two stores a query's short list past the cap is searched in place;
   // with more, such queries go to the full-LDS kernel
   const bool defer = S > 2 && cap < worst_short;
@@ -2495,16 +2512,25 @@ fc_status launch_flat(const int32_t* taken, const uint8_t* cont_len, const uint1
   // a small batch leaves CUs idle: each query gets a workgroup twice as wide
   bool wide = false;
   if constexpr (MAXM == 10) {
-    wide = !plan && B <= kFlatWideMaxB && lay.total + dv.wide_static[NARROW ? 1 : 0] <= (size_t)dv.max_lds;
-    if (wide)
-      hipLaunchKernelGGL((k_tree_flat<MAXM, NARROW, kFlatWide>), dim3(B), dim3(kFlatWide), lay.total, stream, taken,
-                         cont_len, cont_tok, ctx, L, S, k, m, t.c, a, cap, words, nullptr, self_plan, B, rows, n_rows,
-                         num_nodes, node_tok, parent, weight, pos_ids, mask);
+    const size_t wstat = dv.wide_static[NARROW ? 1 : 0];
+    wide = !plan && B <= kFlatWideMaxB && flat_layout(k, MAXM, cap, S, !NARROW).total + wstat <= (size_t)dv.max_lds;
+    if (wide) {  // one per CU, by its registers
+      const int list = flat_list(k, m, MAXM, cap, S, !NARROW, (size_t)dv.max_lds - wstat);
+      hipLaunchKernelGGL((k_tree_flat<MAXM, NARROW, kFlatWide>), dim3(B), dim3(kFlatWide),
+                         flat_layout(k, MAXM, cap, S, !NARROW, list).total, stream, taken, cont_len, cont_tok, ctx, L,
+                         S, k, m, t.c, a, cap, list, words, nullptr, self_plan, B, rows, n_rows, num_nodes, node_tok,
+                         parent, weight, pos_ids, mask);
+    }
   }
-  if (!wide)
-    hipLaunchKernelGGL((k_tree_flat<MAXM, NARROW>), dim3(B), dim3(kFlatThreads), lay.total, stream, taken, cont_len,
-                       cont_tok, ctx, L, S, k, m, t.c, a, cap, words, plan ? order : nullptr, self_plan, B, rows,
-                       n_rows, num_nodes, node_tok, parent, weight, pos_ids, mask);
+  if (!wide) {
+    // the workgroups that a CU's registers hold: three of up to 80, two of up to 128
+    const size_t share = ((size_t)dv.max_lds / (MAXM == 10 ? 3 : 2)) / kLdsStep * kLdsStep;
+    const int list = flat_list(k, m, MAXM, cap, S, !NARROW, share > stat ? share - stat : 0);
+    hipLaunchKernelGGL((k_tree_flat<MAXM, NARROW>), dim3(B), dim3(kFlatThreads),
+                       flat_layout(k, MAXM, cap, S, !NARROW, list).total, stream, taken, cont_len, cont_tok, ctx, L,
+                       S, k, m, t.c, a, cap, list, words, plan ? order : nullptr, self_plan, B, rows, n_rows,
+                       num_nodes, node_tok, parent, weight, pos_ids, mask);
+  }
   FC_CHECK_LAUNCH();
   if (defer) {
     hipLaunchKernelGGL((k_tree_fast<1024, MAXM, NARROW>), dim3(B), dim3(1024), full.total, stream, taken, cont_len,
