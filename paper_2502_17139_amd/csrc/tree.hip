@@ -1172,13 +1172,10 @@ struct FlatLayout {
 };
 
 // Head bits (one 64-bit word per 64 merged positions and depth, positions
-// 0..T) need every weight to be one store weight times a run length and one
-// byte per position's (LCP, length); at most kHeadWords words per depth.
+// 0..T), at most kHeadWords words per depth.
 constexpr int kHeadWords = 192;
 __host__ __device__ inline int head_words(int T) { return (T + 1 + 63) / 64; }
-__host__ __device__ inline bool flat_masks(int k, int maxm, bool with_A) {
-  return !with_A && maxm <= 15 && head_words(k) <= kHeadWords;
-}
+__host__ __device__ inline bool flat_masks(int k) { return head_words(k) <= kHeadWords; }
 
 // maxm: the instantiation's row width (rows of maxm/2 32-bit words);
 // cap: short strings held; with_A: alpha prefix sums (stores of different
@@ -1195,7 +1192,7 @@ __host__ __device__ inline FlatLayout flat_layout(int k, int maxm, int cap, int 
   if (with_A) o = align_up(o + (size_t)(k + 1) * 4, 16);
   t.sstr = o;  // cap rows of maxm/2 words; later the head bits, then the kept tail nodes
   const size_t rows = (size_t)cap * maxm * 2, tails = (size_t)FC_MAX_TREE_ROWS * 4;
-  const size_t heads = flat_masks(k, maxm, with_A) ? (size_t)maxm * head_words(k) * 8 : 0;
+  const size_t heads = flat_masks(k) ? (size_t)maxm * head_words(k) * 8 : 0;
   size_t region = rows > tails ? rows : tails;
   region = region > heads ? region : heads;
   o = align_up(o + region, 16);
@@ -1861,35 +1858,40 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
       ntail += li > lo_t ? (uint32_t)(li - lo_t) : 0u;
       l_after = l;
     }
-    // With one store weight, shared node (q, d) weighs alpha times the
-    // distance from q to the next head of depth d (the next position whose
-    // LCP is below d, or T).  Per depth, one bit per position says whether
-    // it is a head (positions T and past are), so a node's weight is a bit
-    // search instead of the chunk walk below ("direct").  A head word is
-    // built by one thread from 64 (LCP, length) bytes, four at a time: with
-    // the LCP in a byte's low nibble, adding 16 - d sets the byte's bit 4
-    // exactly when LCP >= d.
+    // Shared node (q, d) weighs what the strings from q to the next head of
+    // depth d weigh (the next position whose LCP is below d, or T): alpha
+    // times the distance with one store weight, else a difference of prefix
+    // sums.  Per depth, one bit per position says whether it is a head
+    // (positions T and past are), so a node's weight is a bit search instead
+    // of the chunk walk below ("direct").  A head word is built by one thread
+    // from 64 packed (LCP, length), a 32-bit word of them at a time: with the
+    // LCP in a field's low half, adding 2^kSh - d sets bit kSh exactly when
+    // LCP >= d.
     const int nwd = head_words(T);
-    const bool direct = alpha_flat && flat_masks(k, MAXM, !NARROW) && m <= MAXM;
+    const bool direct = flat_masks(k) && m <= MAXM;
     uint64_t* heads = (uint64_t*)(smem + lay.sstr);
     if (direct) {
       if (tid < MAXM * (kHeadWords / 64)) (&s_nzw[0][0])[tid] = 0ull;
       __syncthreads();
+      constexpr int kPerWord = 4 / (int)sizeof(LMT);  // positions per 32-bit word
+      constexpr uint32_t kOnes = sizeof(LMT) == 1 ? 0x01010101u : 0x00010001u;
       for (int x = tid; x < m * nwd; x += NT) {
         // consecutive threads take the depths of one word: same LDS bytes
         const int wd = x / m, d = x - (x / m) * m + 1;
         const uint4* src = (const uint4*)(lm + wd * 64);
-        const uint32_t add = (uint32_t)(16 - d) * 0x01010101u;
+        const uint32_t add = ((1u << kSh) - (uint32_t)d) * kOnes;
         uint64_t hb = 0;
 #pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) {
+        for (int c4 = 0; c4 < 16 / kPerWord; ++c4) {
           const uint4 v = src[c4];
           const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const uint32_t ge = (((wv[u] & 0x0F0F0F0Fu) + add) >> 4) & 0x01010101u;  // bit 8i: LCP_i >= d
-            const uint32_t nib = (ge | (ge >> 7) | (ge >> 14) | (ge >> 21)) & 0xFu;
-            hb |= (uint64_t)(~nib & 0xFu) << (16 * c4 + 4 * u);
+            // bit i of each field: LCP_i >= d
+            const uint32_t ge = (((wv[u] & (kLo * kOnes)) + add) >> kSh) & kOnes;
+            const uint32_t nib = sizeof(LMT) == 1 ? (ge | (ge >> 7) | (ge >> 14) | (ge >> 21)) & 0xFu
+                                                  : (ge | (ge >> 15)) & 0x3u;
+            hb |= (uint64_t)(~nib & ((1u << kPerWord) - 1u)) << (4 * kPerWord * c4 + kPerWord * u);
           }
         }
         const int past = T - wd * 64;  // positions at or past T are heads
@@ -1915,7 +1917,18 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
     // head per depth after each chunk, and the alpha prefix sums of stores
     // of different weights.
     uint16_t nh[MAXM + 1];
-    bool walk_ready = false;
+    bool walk_ready = false, sums_ready = false;
+    auto prepare_sums = [&]() {  // stores of different weights
+      if (alpha_flat || sums_ready) return;
+      sums_ready = true;
+      uint32_t run = a_ex;
+      for (int p = p0; p < p1; ++p) {
+        A[p] = run;
+        run += alpha_of(alpha, store_of(perm[p]));
+      }
+      if (tid == 0) A[T] = a_tot;
+      __syncthreads();
+    };
     auto prepare_walk = [&]() {
       if (walk_ready) return;
       walk_ready = true;
@@ -1954,15 +1967,7 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
         const uint32_t x = s_wsuf[w][d];
         if (d <= m && x < nh[d]) nh[d] = (uint16_t)x;
       }
-      if (!alpha_flat) {
-        uint32_t run = a_ex;
-        for (int p = p0; p < p1; ++p) {
-          A[p] = run;
-          run += alpha_of(alpha, store_of(perm[p]));
-        }
-        if (tid == 0) A[T] = a_tot;
-        __syncthreads();
-      }
+      prepare_sums();
     };
     // The own nodes of the chunk, right to left and deepest first (the
     // reverse of (p, d) order), with their weights: node (q, d) covers the
@@ -2022,6 +2027,7 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
         if (Wt != 1u && Wt != 2u && Wt < 256u) atomicAdd(&s_hist[Wt], n);
       };
       if (direct && listed) {
+        prepare_sums();
         uint32_t o = sh_ex;
         uint32_t x = p0 < p1 ? (uint32_t)lm[p0] : 0u;
         for (int q = p0; q < p1; ++q) {
@@ -2029,9 +2035,10 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
           const int l = (int)(x & kLo), ml = (int)(x >> kSh), ln = (int)(xn & kLo);
           const int hi = ml < ln ? ml : ln;
           for (int d = l + 1; d <= hi; ++d) sh_key[o++] = ((uint32_t)q << 5) | (uint32_t)d;
+          if (!alpha_flat && ml > (l > ln ? l : ln)) count(A[q + 1] - A[q], (uint32_t)(ml - (l > ln ? l : ln)));
           x = xn;
         }
-        count(a0, ntail);
+        if (alpha_flat) count(a0, ntail);
         __syncthreads();
         // (q, d) with d <= lcp(q + 1): the next head of depth d is past q + 1
         for (uint32_t e = (uint32_t)tid; e < sh_tot; e += NT) {
@@ -2056,7 +2063,7 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
             }
             nxt = (j2 << 6) + __builtin_ctzll(hd[j2]);
           }
-          const uint32_t Wt = a0 * (uint32_t)(nxt - q);
+          const uint32_t Wt = alpha_flat ? a0 * (uint32_t)(nxt - q) : A[nxt] - A[q];
           sh_w[e] = (SWT)Wt;
           count(Wt, 1u);
         }
@@ -2162,9 +2169,10 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
     //    one scan gives every kept node its row.  With one store weight and
     //    W* equal to it, every shared node is kept (its weight is at least
     //    twice that) and so are the first take_eq tail nodes in (p, d)
-    //    order; the two ordered lists are merged by binary search.
-    //    Otherwise (a list that did not fit) the chunks count their kept
-    //    nodes in a walk and emit them in order.
+    //    order; the two ordered lists are merged by binary search.  With
+    //    stores of different weights and a W* among those the chunks count
+    //    their kept nodes and emit them in order.  A list that did not fit
+    //    takes the walk for that.
     uint32_t tail_max = a0;
 #pragma unroll
     for (int u = 1; u < FC_MAX_SOURCES; ++u)
@@ -2241,6 +2249,46 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
         }
       }
       nsel = (int)(need < (uint32_t)c ? need : (uint32_t)c);
+    } else if (listed && need > 0) {
+      // stores of different weights and W* no more than the largest: the
+      // chunk's nodes in order, shared ones with their listed weights, tails
+      // with their string's
+      prepare_sums();
+      auto in_order = [&](auto&& node) {
+        uint32_t at = sh_ex;
+        uint32_t x = p0 < p1 ? (uint32_t)lm[p0] : 0u;
+        for (int q = p0; q < p1; ++q) {
+          const uint32_t xn = q + 1 < T ? (uint32_t)lm[q + 1] : 0u;
+          const int l = (int)(x & kLo), ml = (int)(x >> kSh), ln = (int)(xn & kLo);
+          const int hi = ml < ln ? ml : ln;
+          for (int d = l + 1; d <= hi; ++d) node(q, d, d, (uint32_t)sh_w[at++]);
+          const int lo_t = l > ln ? l : ln;
+          if (ml > lo_t) node(q, lo_t + 1, ml, alpha_flat ? a0 : A[q + 1] - A[q]);
+          x = xn;
+        }
+      };
+      uint32_t gt = 0, eq = 0;
+      in_order([&](int, int lo, int hi, uint32_t Wt) {
+        gt += Wt > wstar ? (uint32_t)(hi - lo + 1) : 0u;
+        eq += Wt == wstar ? (uint32_t)(hi - lo + 1) : 0u;
+      });
+      uint32_t gt_ex, eq_ex, gt_tot, eq_tot;
+      Scan2<NT>::run(gt, eq, s_x, s_y, &gt_ex, &eq_ex, &gt_tot, &eq_tot);
+      uint32_t row = 1 + gt_ex + (eq_ex < take_eq ? eq_ex : take_eq);
+      if (gt > 0 || (eq > 0 && eq_ex < take_eq))
+        in_order([&](int q, int lo, int hi, uint32_t Wt) {
+          if (Wt < wstar) return;
+          for (int d = lo; d <= hi; ++d) {
+            if (Wt == wstar && eq_ex++ >= take_eq) return;
+            if (row < (uint32_t)FC_MAX_TREE_ROWS) {
+              s_sel_p[row] = (uint16_t)q;
+              s_sel_d[row] = (uint8_t)d;
+              s_sel_w[row] = Wt;
+            }
+            ++row;
+          }
+        });
+      nsel = (int)need;
     } else {
       uint32_t gt = 0, eq = 0;
       prepare_walk();
@@ -2523,8 +2571,12 @@ fc_status launch_flat(const int32_t* taken, const uint8_t* cont_len, const uint1
     }
   }
   if (!wide) {
-    // the workgroups that a CU's registers hold: three of up to 80, two of up to 128
-    const size_t share = ((size_t)dv.max_lds / (MAXM == 10 ? 3 : 2)) / kLdsStep * kLdsStep;
+    // as many workgroups per CU as its registers hold (three of up to 80, two
+    // of up to 128) and their LDS without a longer list
+    const size_t one = flat_layout(k, MAXM, cap, S, !NARROW).total + stat;
+    size_t groups = MAXM == 10 ? 3 : 2;
+    while (groups > 1 && one > (size_t)dv.max_lds / groups) --groups;
+    const size_t share = (size_t)dv.max_lds / groups / kLdsStep * kLdsStep;
     const int list = flat_list(k, m, MAXM, cap, S, !NARROW, share > stat ? share - stat : 0);
     hipLaunchKernelGGL((k_tree_flat<MAXM, NARROW>), dim3(B), dim3(kFlatThreads),
                        flat_layout(k, MAXM, cap, S, !NARROW, list).total, stream, taken, cont_len, cont_tok, ctx, L,

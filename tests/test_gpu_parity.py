@@ -682,6 +682,43 @@ def test_search_without_records(B, S, pairs):
     compare_retrieve(gpu_pipeline(stores, ctx, p, (1, 1, 1, 1)[:S], 16), oracle.retrieve(texts, ctx, **p))
 
 
+@pytest.mark.parametrize("m,alpha,B", [(10, (1, 1), 2), (10, (2, 1), 2), (10, (1, 1), 260), (10, (3, 1), 260),
+                                       (16, (1, 1), 2), (16, (1, 2), 2), (15, (2, 1), 2), (7, (0, 1), 2),
+                                       (16, (200, 7), 2), (10, (300, 300), 2)])
+def test_tree_node_weights(m, alpha, B):
+    """Tries with few to very many shared nodes (lists that fit in LDS, that
+    only fit in what it has left, and that do not fit), small and large W*,
+    and W* among the store weights, whatever the weights and the row width."""
+    say(f"tree node weights m={m} alpha={alpha} B={B}")
+    rng = np.random.default_rng(m * 100 + B)
+    k = 5000
+    taken = np.zeros((B, 2), np.int32)
+    lens, toks = np.zeros((B, k), np.uint8), np.zeros((B, k, m), np.uint16)
+    # kept slots per store, vocabulary, chance that a token is the store's usual one, shortest row
+    shapes = [(4700, 300, 2, 0.5, m), (1500, 60, 3, 0.5, 0), (4990, 10, 500, 0.55, m), (900, 0, 4, 0.3, 1),
+              (40, 9, 900, 0.0, 0), (4000, 1000, 30, 0.85, m - 2), (3, 2, 50, 0.5, 0), (0, 5000, 12, 0.6, m)]
+    for b in range(B):
+        n0, n1, v, usual, shortest = shapes[b % len(shapes)] if B > 2 else shapes[(2 * m + 5 * b) % len(shapes)]
+        taken[b] = n0, n1
+        at = 0
+        for n in (n0, n1):
+            if n == 0:
+                continue
+            x = rng.integers(1, v + 1, (n, m))
+            x[rng.random((n, m)) < usual] = 1
+            ln = rng.integers(shortest, m + 1, n)
+            x[np.arange(m)[None, :] >= ln[:, None]] = 0
+            order = np.lexsort(x.T[::-1])
+            lens[b, at:at + n], toks[b, at:at + n] = ln[order], x[order]
+            at += n
+    ctx = np.full((B, 4), 7, np.uint16)
+    t = fc.fc_build_tree(dev(taken), dev(lens), dev(toks), dev(ctx), c=64, alpha=alpha)
+    torch.cuda.synchronize()
+    rows = list(range(min(B, len(shapes))))
+    o = oracle.build_tree(taken[rows], lens[rows], toks[rows], ctx[rows], c=64, alpha=alpha)
+    compare_tree({f: host(x) for f, x in t.items()}, o, rows)
+
+
 def test_results_do_not_depend_on_batching():
     """The same queries give the same per-query bytes whatever launch shape
     the batch leads to: one batch of 300 (the tree's heaviest-first planning
