@@ -19,9 +19,8 @@
 //   and sa[rank[i]] = i is written in that round (in sorted order, so at
 //   nearly sequential addresses).
 //
-// Round 0 and the rank pairs below are sorted by a global digit histogram
-// followed by one "onesweep" pass per 8-bit digit (Adinets and Merrill 2022):
-// a workgroup takes a tile of 4,096 keys (its tile id from an atomic ticket,
+// Round 0's keys are sorted by a global digit histogram followed by one
+// "onesweep" pass per 8-bit digit (Adinets and Merrill 2022): a workgroup takes a tile of 4,096 keys (its tile id from an atomic ticket,
 // so tiles start in order), ranks them stably inside the tile with wave
 // ballots, publishes per-digit tile counts and resolves its global offsets by
 // decoupled look-back over the earlier tiles, stages the tile in LDS in digit
@@ -693,8 +692,8 @@ __global__ void __launch_bounds__(kSortThreads) k_onesweep(FirstKeys<M> fk, cons
 //    and counts each group's digits, k_big_pass is a onesweep pass whose
 //    look-back ends at the group's first tile.
 // At 1B suffixes this replaced 48 passes over (8-byte key, suffix) elements
-// and their key and histogram kernels, 159 ms of a 305 ms build, by 77 ms
-// (small groups 28, keys of the large ones 25, their passes 24); 10M suffixes
+// and their key and histogram kernels, 159 ms of a 305 ms build, by 67 ms
+// (small groups 28, keys of the large ones 22, their passes 17); 10M suffixes
 // 3.60 -> 2.83 ms, 64 repositories in one call 8.43 -> 6.04 ms.  The line
 // between the two lies at what one workgroup's LDS holds next to the groups
 // that start before it: in the first such round of a 10M store about half of
@@ -1877,7 +1876,7 @@ fc_status radix_passes(BuildWs& w, const FirstKeys<M>& fk, uint32_t U, int digit
   return FC_OK;
 }
 
-// The new suffixes of an extension (see k_init_keys_ext).
+// The new suffixes of an extension (see FirstKeys).
 struct ExtendArgs {
   const uint32_t* ins;  // per new position
   const uint32_t* isa;  // inverse of the old suffix array
