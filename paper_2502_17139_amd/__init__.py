@@ -27,6 +27,7 @@ FC_BUCKETS = 65537
 FC_MAX_CACHE_TOKENS = 16384
 FC_TREE_ATTN_HEAD_DIM = 128
 
+FC_ERR_WORKSPACE = 2
 STATUS = {0: "FC_OK", 1: "FC_ERR_INVALID", 2: "FC_ERR_WORKSPACE", 3: "FC_ERR_DEVICE", 4: "FC_ERR_UNSUPPORTED"}
 
 # Names of every entry point the header declares.
@@ -38,8 +39,8 @@ EXPORTS = (
     "fc_store_top_bytes", "fc_store_prepare_top",
     "fc_retrieve_workspace_bytes", "fc_retrieve", "fc_build_tree_workspace_bytes", "fc_build_tree",
     "fc_verify_accept", "fc_targets_from_truth", "fc_cache_lds_bytes", "fc_cache_retrieve", "fc_cache_write",
-    "fc_tree_attention", "fc_tree_attention_workspace_bytes", "fc_tree_attention_ws", "fc_replay_init", "fc_replay_run", "fc_retrieve_noalloc_max_bytes", "fc_retrieve_noalloc",
-    "fc_datastore_build_stats",
+    "fc_tree_attention", "fc_tree_attention_workspace_bytes", "fc_tree_attention_ws", "fc_replay_init",
+    "fc_replay_run", "fc_retrieve_noalloc_max_bytes", "fc_retrieve_noalloc", "fc_datastore_build_stats",
 )
 
 
@@ -255,6 +256,19 @@ def _stream(stream) -> int:
 
 def _empty(shape, dtype, device) -> torch.Tensor:
     return torch.empty(shape, dtype=dtype, device=device)
+
+
+def _scratch(size: int, device, stream) -> torch.Tensor:
+    """A call's own scratch memory, from the allocator's pool of the stream
+    that uses it: a block of another stream's pool may still be in use there
+    when this call's kernels write it, and is handed out again there while
+    they run."""
+    if stream is None:
+        return _empty(size, torch.uint8, device)
+    if not isinstance(stream, torch.cuda.Stream):  # anything with a raw stream
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+    with torch.cuda.stream(stream):
+        return _empty(size, torch.uint8, device)
 
 
 # ---------------------------------------------------------------- index ----
@@ -567,12 +581,21 @@ def fc_cache_write(texts: torch.Tensor, text_len: torch.Tensor, dst_row: torch.T
 
 # ------------------------------------------------------- tree attention ----
 
+def fc_tree_attention_workspace_bytes(B: int, R: int, H: int, Pmax: int) -> int:
+    return int(lib().fc_tree_attention_workspace_bytes(B, R, H, Pmax))
+
+
 def fc_tree_attention(q: torch.Tensor, k_tree: torch.Tensor, v_tree: torch.Tensor, k_cache: torch.Tensor,
                       v_cache: torch.Tensor, prefix_len: torch.Tensor, tree: dict, rope_base: float = 10000.0,
-                      out: torch.Tensor | None = None, stream=None) -> torch.Tensor:
+                      out: torch.Tensor | None = None, stream=None,
+                      workspace: torch.Tensor | None = None) -> torch.Tensor:
     """Tree attention (bf16 q [B][R][H][D], k/v_tree [B][R][Hkv][D],
     k/v_cache [B][Pmax][Hkv][D]) with the tree's num_nodes, mask and pos_ids;
-    returns fp32 [B][R][H][D]."""
+    returns fp32 [B][R][H][D].  Few trees need scratch memory
+    (fc_tree_attention_workspace_bytes; 16-byte aligned): the caller's
+    workspace, or else this call's own.  A program that captures the call into
+    a graph without torch's own graph pool passes a workspace, which has to
+    outlive the graph."""
     for t in (q, k_tree, v_tree, k_cache, v_cache):
         if t.dtype != torch.bfloat16 or t.dim() != 4:
             raise ValueError("q, k_tree, v_tree, k_cache, v_cache must be 4-D bfloat16")
@@ -589,15 +612,16 @@ def fc_tree_attention(q: torch.Tensor, k_tree: torch.Tensor, v_tree: torch.Tenso
     if out is None:
         out = _empty((B, R, H, D), torch.float32, q.device)
     u16 = lambda t: _ptr(t.view(torch.uint16))  # noqa: E731
-    need = int(lib().fc_tree_attention_workspace_bytes(B, R, H, Pmax))
-    ws = None
-    if need > 0:
-        ws = _empty(need, torch.uint8, q.device)
-        if stream is not None:
-            ws.record_stream(stream)  # it is used there, and freed here
+    need = fc_tree_attention_workspace_bytes(B, R, H, Pmax)
+    _expect("workspace", workspace, torch.uint8, optional=True)
+    if workspace is None and need > 0:
+        workspace = _scratch(need, q.device, stream)
+    size = 0 if workspace is None else workspace.numel()
+    if size < need:  # the library would run in one part; here a workspace that is too small is a mistake
+        _check("fc_tree_attention", FC_ERR_WORKSPACE)
     _check("fc_tree_attention", lib().fc_tree_attention_ws(
         u16(q), u16(k_tree), u16(v_tree), u16(k_cache), u16(v_cache), _ptr(prefix_len), _ptr(tree["num_nodes"]),
-        _ptr(tree["mask"]), _ptr(tree["pos_ids"]), B, R, H, Hkv, D, Pmax, rope_base, _ptr(out), _ptr(ws), need,
+        _ptr(tree["mask"]), _ptr(tree["pos_ids"]), B, R, H, Hkv, D, Pmax, rope_base, _ptr(out), _ptr(workspace), size,
         _stream(stream)))
     return out
 

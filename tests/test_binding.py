@@ -81,3 +81,82 @@ def test_cache_write_refuses_mismatched_segments():
     with pytest.raises(ValueError, match="dst_off"):
         fc.fc_cache_write(texts, tl, i32(3), i32(2), i32(3), torch.zeros(3, dtype=torch.int64), i32(3),
                           torch.zeros(5, dtype=torch.uint16))
+
+
+class _Stream:
+    cuda_stream = 7
+
+
+class _Scratch:
+    """Stands in for the GPU: records, for each buffer the binding makes, the
+    stream whose pool it came from, and what the library was handed."""
+
+    def __init__(self, monkeypatch, need):
+        self.stream, self.made, self.calls = None, [], []
+        rec = self
+
+        class Lib:
+            def __getattr__(self, name):
+                if name.endswith("_bytes"):
+                    return lambda *a: need
+                return lambda *a: rec.calls.append((name, a)) or 0
+
+        class on_stream:
+            def __init__(self, s):
+                self.s = s
+
+            def __enter__(self):
+                self.before, rec.stream = rec.stream, self.s.cuda_stream
+
+            def __exit__(self, *_):
+                rec.stream = self.before
+
+        def empty(shape, dtype, device):
+            t = torch.empty(shape, dtype=dtype)
+            rec.made.append((rec.stream, t.numel(), t.data_ptr()))
+            return t
+
+        monkeypatch.setattr(fc, "lib", lambda: Lib())
+        monkeypatch.setattr(fc, "_empty", empty)
+        monkeypatch.setattr(fc, "_ptr", lambda t: None if t is None else t.data_ptr())
+        monkeypatch.setattr(fc, "_ptrs", lambda ts: [t.data_ptr() for t in ts])
+        monkeypatch.setattr(fc, "_stream", lambda s: 0 if s is None else s.cuda_stream)
+        monkeypatch.setattr(torch.cuda, "Stream", _Stream)
+        monkeypatch.setattr(torch.cuda, "stream", on_stream)
+
+
+def _attention_args(B=1, R=5, H=4, Hkv=2, D=128, P=300):
+    z = lambda *s: torch.zeros(s, dtype=torch.bfloat16)  # noqa: E731
+    return dict(q=z(B, R, H, D), k_tree=z(B, R, Hkv, D), v_tree=z(B, R, Hkv, D), k_cache=z(B, P, Hkv, D),
+                v_cache=z(B, P, Hkv, D), prefix_len=torch.zeros(B, dtype=torch.int32),
+                tree=fc.tree_outputs(B, R - 1, "cpu"), out=torch.zeros((B, R, H, D)))
+
+
+@pytest.mark.parametrize("stream", [None, _Stream()])
+def test_tree_attention_scratch_comes_from_the_stream_it_is_used_on(monkeypatch, stream):
+    args = _attention_args()
+    gpu = _Scratch(monkeypatch, 4096)
+    fc.fc_tree_attention(**args, stream=stream)
+    where = None if stream is None else stream.cuda_stream
+    assert [(s, n) for s, n, _ in gpu.made] == [(where, 4096)]
+    (name, a), = gpu.calls
+    assert name == "fc_tree_attention_ws" and a[-3:] == (gpu.made[0][2], 4096, where or 0)
+
+
+def test_tree_attention_takes_the_callers_workspace(monkeypatch):
+    args = _attention_args()
+    gpu = _Scratch(monkeypatch, 4096)
+    ws = torch.zeros(5000, dtype=torch.uint8)
+    fc.fc_tree_attention(**args, workspace=ws)
+    assert not gpu.made and gpu.calls[0][1][-3:] == (ws.data_ptr(), 5000, 0)
+    with pytest.raises(ValueError, match="workspace"):
+        fc.fc_tree_attention(**args, workspace=ws.to(torch.int32))
+
+
+def test_tree_attention_refuses_a_small_workspace(monkeypatch):
+    args = _attention_args()
+    gpu = _Scratch(monkeypatch, 4096)
+    monkeypatch.setattr(fc, "_check", lambda fn, code: (_ for _ in ()).throw(RuntimeError(code)) if code else None)
+    with pytest.raises(RuntimeError, match="2"):
+        fc.fc_tree_attention(**args, workspace=torch.zeros(4095, dtype=torch.uint8))
+    assert not gpu.calls

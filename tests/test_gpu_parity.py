@@ -1282,3 +1282,39 @@ def test_tree_attention_in_parts_matches_one_part(R, P, Pmax):
     torch.cuda.synchronize()
     assert (host(one) == host(small)).all()
     assert np.abs(parts - host(one)).max() <= 2.0 ** -8 * max(float(vc.abs().max()), float(vt.abs().max())) + 1e-5
+
+
+def test_tree_attention_on_another_stream():
+    """A call on a side stream while the current stream still reads a block it
+    has freed, of the size of the call's scratch: the block is not the call's
+    (a copy queued behind a long product still finds its contents), and the
+    call's result is that of a quiet GPU, of a given workspace, and of every
+    repeat."""
+    B, R, H, Hkv, D, Pn = 1, 65, 32, 8, fc.FC_TREE_ATTN_HEAD_DIM, 3000
+    rng = np.random.default_rng(8)
+    q, kt, vt = (_bf16(rng, B, R, h, D).cuda() for h in (H, Hkv, Hkv))
+    kc, vc = (_bf16(rng, B, Pn, Hkv, D).cuda() for _ in range(2))
+    tree = dict(num_nodes=dev(np.array([R], np.int32)), mask=dev(np.tril(np.ones((B, R, R), np.int32))),
+                pos_ids=dev(np.arange(R, dtype=np.int32)[None] % 10))
+    plen = dev(np.array([Pn], np.int32))
+    need = fc.fc_tree_attention_workspace_bytes(B, R, H, Pn)
+    assert need > 0
+    say("attention on a side stream")
+    want = fc.fc_tree_attention(q, kt, vt, kc, vc, plen, tree)
+    ws = torch.empty(need + 48, dtype=torch.uint8, device="cuda")
+    assert torch.equal(want, fc.fc_tree_attention(q, kt, vt, kc, vc, plen, tree, workspace=ws))
+    with pytest.raises(fc.FcError):
+        fc.fc_tree_attention(q, kt, vt, kc, vc, plen, tree, workspace=ws[: need - 16])
+    side = torch.cuda.Stream()
+    a = torch.rand(6144, 6144, device="cuda")
+    out, seen = torch.empty_like(want), torch.empty(need // 4, dtype=torch.int32, device="cuda")
+    for i in range(5):
+        busy = torch.full((need // 4,), i + 1, dtype=torch.int32, device="cuda")
+        out.zero_()
+        torch.cuda.synchronize()
+        a @ a
+        seen.copy_(busy)  # runs after the product
+        del busy
+        fc.fc_tree_attention(q, kt, vt, kc, vc, plen, tree, out=out, stream=side)
+        torch.cuda.synchronize()
+        assert (seen == i + 1).all() and torch.equal(out, want)
