@@ -291,7 +291,7 @@ def fc_datastore_build(tokens: torch.Tensor, sa_out: torch.Tensor | None = None,
         sa_out = _empty(n, torch.uint32, tokens.device)
     need = fc_datastore_build_workspace_bytes(n)
     if workspace is None:
-        workspace = _empty(max(need, 1), torch.uint8, tokens.device)
+        workspace = _scratch(max(need, 1), tokens.device, stream)
     _check("fc_datastore_build", lib().fc_datastore_build(_ptr(tokens), n, _ptr(sa_out), _ptr(workspace),
                                                          workspace.numel(), _stream(stream)))
     return sa_out
@@ -308,7 +308,7 @@ def fc_datastore_build_stats(tokens: torch.Tensor, sa_out: torch.Tensor | None =
         sa_out = _empty(n, torch.uint32, tokens.device)
     need = fc_datastore_build_workspace_bytes(n)
     if workspace is None:
-        workspace = _empty(max(need, 1), torch.uint8, tokens.device)
+        workspace = _scratch(max(need, 1), tokens.device, stream)
     st = FcBuildStats()
     _check("fc_datastore_build_stats", lib().fc_datastore_build_stats(
         _ptr(tokens), n, _ptr(sa_out), _ptr(workspace), workspace.numel(), ctypes.byref(st), _stream(stream)))
@@ -330,7 +330,7 @@ def fc_datastore_build_batched(tokens: torch.Tensor, seg_off, sa_out: torch.Tens
         sa_out = _empty(n, torch.uint32, tokens.device)
     need = fc_datastore_build_batched_workspace_bytes(n, R) if R >= 1 else 0
     if workspace is None:
-        workspace = _empty(max(need, 1), torch.uint8, tokens.device)
+        workspace = _scratch(max(need, 1), tokens.device, stream)
     _check("fc_datastore_build_batched", lib().fc_datastore_build_batched(
         _ptr(tokens), ctypes.c_void_p(off.ctypes.data), R, _ptr(sa_out), _ptr(workspace), workspace.numel(),
         _stream(stream)))
@@ -357,7 +357,7 @@ def fc_datastore_extend(tokens: torch.Tensor, n_new: int, old_sa: torch.Tensor, 
         sa_out = _empty(n, torch.uint32, tokens.device)
     if workspace is None:
         need = fc_datastore_extend_workspace_bytes(n, n_new, old_isa is not None)
-        workspace = _empty(max(need, 1), torch.uint8, tokens.device)
+        workspace = _scratch(max(need, 1), tokens.device, stream)
     _check("fc_datastore_extend", lib().fc_datastore_extend(
         _ptr(tokens), n, n_new, _ptr(old_sa), _ptr(old_isa), _ptr(sa_out), _ptr(isa_out), _ptr(workspace),
         workspace.numel(), _stream(stream)))
@@ -490,7 +490,7 @@ def fc_retrieve(stores, ctx: torch.Tensor, n_max: int = 16, n_min: int = 2, k: i
     _expect("workspace", workspace, torch.uint8, optional=True)
     need = int(lib().fc_retrieve_workspace_bytes(B, S, p))
     if workspace is None and need > 0:
-        workspace = _empty(need, torch.uint8, ctx.device)
+        workspace = _scratch(need, ctx.device, stream)
     _check("fc_retrieve", lib().fc_retrieve(
         views, S, _ptr(ctx), B, L, p, *_ptrs(results), _ptr(rows), n_rows,
         _ptr(workspace), 0 if workspace is None else workspace.numel(), _stream(stream)))
@@ -671,7 +671,7 @@ def fc_build_tree(taken: torch.Tensor, cont_len: torch.Tensor, cont_tok: torch.T
     _expect_all(TREE_FIELDS, results, _TREE_DTYPES, ((B,), rows_of, rows_of, rows_of, rows_of, (B, R, R)))
     need = fc_build_tree_workspace_bytes(B)
     if workspace is None and need > 0:
-        workspace = _empty(need, torch.uint8, ctx.device)
+        workspace = _scratch(need, ctx.device, stream)
     _check("fc_build_tree", lib().fc_build_tree(
         _ptr(taken), _ptr(cont_len), _ptr(cont_tok), _ptr(ctx), B, L, S, k, m, tp,
         *_ptrs(results), _ptr(rows), n_rows, _ptr(workspace),

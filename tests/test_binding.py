@@ -160,3 +160,26 @@ def test_tree_attention_refuses_a_small_workspace(monkeypatch):
     with pytest.raises(RuntimeError, match="2"):
         fc.fc_tree_attention(**args, workspace=torch.zeros(4095, dtype=torch.uint8))
     assert not gpu.calls
+
+
+@pytest.mark.parametrize("stream", [None, _Stream()])
+@pytest.mark.parametrize("call", ["build", "build_stats", "build_batched", "extend", "retrieve", "build_tree"])
+def test_scratch_comes_from_the_stream_it_is_used_on(monkeypatch, call, stream):
+    tok, u32 = torch.zeros(40, dtype=torch.uint16), lambda n: torch.zeros(n, dtype=torch.uint32)
+    taken, lens, toks, ctx = _tree_inputs()
+    out = fc.retrieve_outputs(4, 1, 10, 3, "cpu") if call == "retrieve" else fc.tree_outputs(3, 4, "cpu")
+    gpu = _Scratch(monkeypatch, 4096)
+    if call == "build":
+        fc.fc_datastore_build(tok, sa_out=u32(40), stream=stream)
+    elif call == "build_stats":
+        fc.fc_datastore_build_stats(tok, sa_out=u32(40), stream=stream)
+    elif call == "build_batched":
+        fc.fc_datastore_build_batched(tok, [0, 10, 40], sa_out=u32(40), stream=stream)
+    elif call == "extend":
+        fc.fc_datastore_extend(tok, 5, u32(35), sa_out=u32(40), stream=stream)
+    elif call == "retrieve":
+        fc.fc_retrieve([_NoStore()], torch.zeros((4, 16), dtype=torch.uint16), k=10, m=3, out=out, stream=stream)
+    else:
+        fc.fc_build_tree(taken, lens, toks, ctx, c=4, out=out, stream=stream)
+    assert [(s, n) for s, n, _ in gpu.made] == [(None if stream is None else stream.cuda_stream, 4096)]
+    assert gpu.made[0][2] in gpu.calls[-1][1]
