@@ -476,14 +476,22 @@ fc_status fc_tree_attention(const uint16_t* q, const uint16_t* k_tree, const uin
                             hipStream_t stream);
 
 /*
- * fc_tree_attention with scratch memory, for few trees: with fewer (tree,
- * head) pairs than the GPU has compute units, each pair's prefix is cut into
- * parts that run side by side and are put together at the end (the same
- * arithmetic; the running sums are added part by part).  ws holds at least
+ * fc_tree_attention with scratch memory, for few trees: where too few (tree,
+ * head) pairs would leave most of the GPU idle (up to 170 pairs, fewer with
+ * more than 64 rows), long prefixes are cut into parts that run side by side
+ * and are put together at the end.  ws holds at least
  * fc_tree_attention_workspace_bytes(B, R, H, Pmax) bytes, 16-byte aligned
- * (FC_ERR_INVALID), its contents on entry do not matter.  That size is 0
+ * (FC_ERR_INVALID); its contents on entry do not matter.  That size is 0
  * where the call runs in one part; with ws NULL or ws_bytes below it the call
  * runs in one part too, as fc_tree_attention does.
+ *
+ * The products and roundings are those of one part but for the softmax
+ * weights, which are rounded to bf16 against their part's own largest score:
+ * an output moves by at most 2^-8 times the largest value's magnitude, on
+ * either side of the exact one.  How a prefix is cut depends on B, R, H, Pmax
+ * and its own length, so the same tree may differ by that between calls of
+ * different sizes; the same call gives the same bits every time.  A tree whose
+ * prefix is too short to cut has the bits of one part.
  */
 size_t fc_tree_attention_workspace_bytes(int32_t B, int32_t R, int32_t H, int32_t Pmax);
 fc_status fc_tree_attention_ws(const uint16_t* q, const uint16_t* k_tree, const uint16_t* v_tree,

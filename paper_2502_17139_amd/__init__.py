@@ -611,7 +611,6 @@ def fc_tree_attention(q: torch.Tensor, k_tree: torch.Tensor, v_tree: torch.Tenso
     _expect("out", out, torch.float32, (B, R, H, D), optional=True)
     if out is None:
         out = _empty((B, R, H, D), torch.float32, q.device)
-    u16 = lambda t: _ptr(t.view(torch.uint16))  # noqa: E731
     need = fc_tree_attention_workspace_bytes(B, R, H, Pmax)
     _expect("workspace", workspace, torch.uint8, optional=True)
     if workspace is None and need > 0:
@@ -620,9 +619,8 @@ def fc_tree_attention(q: torch.Tensor, k_tree: torch.Tensor, v_tree: torch.Tenso
     if size < need:  # the library would run in one part; here a workspace that is too small is a mistake
         _check("fc_tree_attention", FC_ERR_WORKSPACE)
     _check("fc_tree_attention", lib().fc_tree_attention_ws(
-        u16(q), u16(k_tree), u16(v_tree), u16(k_cache), u16(v_cache), _ptr(prefix_len), _ptr(tree["num_nodes"]),
-        _ptr(tree["mask"]), _ptr(tree["pos_ids"]), B, R, H, Hkv, D, Pmax, rope_base, _ptr(out), _ptr(workspace), size,
-        _stream(stream)))
+        *_ptrs((q, k_tree, v_tree, k_cache, v_cache, prefix_len, tree["num_nodes"], tree["mask"], tree["pos_ids"])),
+        B, R, H, Hkv, D, Pmax, rope_base, _ptr(out), _ptr(workspace), size, _stream(stream)))
     return out
 
 

@@ -32,7 +32,7 @@
 // A full batch is bound by HBM (64 trees x 32 heads, 2,048 keys: 490 us, 4.7
 // TB/s of keys and values; 510 before the query rows' loads went ahead of
 // everything else and the tree's blocks were staged together).  A few trees
-// leave CUs idle: their prefixes are cut into parts (part_count), merged by
+// leave CUs idle: their prefixes are cut into parts (split_of), merged by
 // k_tree_merge.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -91,16 +91,20 @@ __device__ __forceinline__ void unpack8(const uint4& u, float (&v)[8]) {
   }
 }
 
+__device__ __forceinline__ int clamp_len(int len, int most) { return len < 0 ? 0 : (len > most ? most : len); }
+__device__ __forceinline__ int prefix_blocks(int P) { return (P + kBlock - 1) / kBlock; }
+
 // kSplit: workgroup blockIdx.y of gridDim.y takes an equal share of the
 // prefix's blocks (the last one the tree's rows instead) and leaves its rows'
 // running maxima, weight sums and unnormalised outputs in part_ml and part_o
-// for k_tree_merge.
+// for k_tree_merge.  A prefix of fewer than split_min blocks stays whole: the
+// last workgroup takes all of it, as without kSplit, and the others leave.
 template <int MAXT, bool kSplit>
 __global__ void __launch_bounds__(MAXT, kSplit && MAXT == 512 ? 2 : 4) k_tree_attn(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_tree, const uint16_t* __restrict__ v_tree,
     const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ num_nodes, const int32_t* __restrict__ mask,
-    const int32_t* __restrict__ pos_ids, int B, int R, int H, int Hkv, int Pmax, double log2_base,
+    const int32_t* __restrict__ pos_ids, int B, int R, int H, int Hkv, int Pmax, int split_min, double log2_base,
     float* __restrict__ out, float2* __restrict__ part_ml, float* __restrict__ part_o) {
   __shared__ __align__(16) uint8_t s_ring[kStages * kStage];
   __shared__ double s_freq[kD / 2];  // rotary frequencies: one double-precision power per pair and workgroup
@@ -131,17 +135,19 @@ __global__ void __launch_bounds__(MAXT, kSplit && MAXT == 512 ? 2 : 4) k_tree_at
   }
   // lengths from the device are clamped to the buffers (a malformed tree,
   // num_nodes = -1, has no rows)
-  const int P = prefix_len[b] < 0 ? 0 : (prefix_len[b] > Pmax ? Pmax : prefix_len[b]);
-  const int n = num_nodes[b] < 0 ? 0 : (num_nodes[b] > R ? R : num_nodes[b]);
+  const int P = clamp_len(prefix_len[b], Pmax);
+  const int n_all = prefix_blocks(P);
+  const int part = kSplit ? (int)blockIdx.y : 0, parts = kSplit ? (int)gridDim.y - 1 : 1;
+  const bool whole = !kSplit || n_all < split_min;
+  if (whole && part < (kSplit ? parts : 0)) return;
+  const int n = clamp_len(num_nodes[b], R);
   const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)s_ring;
 
   // this workgroup's prefix blocks [blk0, n_pre) and tree blocks
-  const int n_all = (P + kBlock - 1) / kBlock;
-  const int part = kSplit ? (int)blockIdx.y : 0, parts = kSplit ? (int)gridDim.y - 1 : 1;
-  const int blk0 = kSplit ? (int)((uint32_t)n_all * (uint32_t)part / (uint32_t)parts) : 0;  // n_all < 2^26
-  const int n_pre = !kSplit ? n_all
+  const int blk0 = whole ? 0 : (int)((uint32_t)n_all * (uint32_t)part / (uint32_t)parts);  // n_all < 2^26
+  const int n_pre = whole ? n_all
                     : part < parts ? (int)((uint32_t)n_all * (uint32_t)(part + 1) / (uint32_t)parts) : blk0;
-  const int n_tree = !kSplit || part == parts ? (n + kBlock - 1) / kBlock : 0;
+  const int n_tree = whole || part == parts ? (n + kBlock - 1) / kBlock : 0;
   const int key_end = P < n_pre * kBlock ? P : n_pre * kBlock;
 
   // Prefix block loads: load u (0..15) of a block covers rows 4(u%8) ..
@@ -344,7 +350,7 @@ __global__ void __launch_bounds__(MAXT, kSplit && MAXT == 512 ? 2 : 4) k_tree_at
   // normalise by the row's total weight (summed over the four lane groups)
   float lt = l_run + __shfl_xor(l_run, 16);
   lt = lt + __shfl_xor(lt, 32);
-  if (kSplit) {
+  if (!whole) {
     if (q_in) {
       const int64_t row = ((int64_t)(b * H + h) * gridDim.y + blockIdx.y) * R + qr;
       if (lg == 0) part_ml[row] = make_float2(m_run, lt);
@@ -368,16 +374,19 @@ __global__ void __launch_bounds__(MAXT, kSplit && MAXT == 512 ? 2 : 4) k_tree_at
 // The parts of a split row put together: out = sum_s e^(m_s - m) o_s / sum_s
 // e^(m_s - m) l_s with m the largest m_s.  32 lanes per (row, head), four dims
 // each, every part's loads issued before any is used; a row at or past
-// num_nodes[b] is 0.
+// num_nodes[b] is 0.  A whole prefix's rows are in place already.
 template <int kMost>
 __global__ void __launch_bounds__(256) k_tree_merge(const float2* __restrict__ part_ml,
                                                       const float* __restrict__ part_o,
-                                                      const int32_t* __restrict__ num_nodes, int B, int R, int H,
-                                                      int parts, float* __restrict__ out) {
-  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5;  // (b, row, h)
-  if (i >= (int64_t)B * R * H) return;
+                                                      const int32_t* __restrict__ prefix_len,
+                                                      const int32_t* __restrict__ num_nodes, int R, int H, int Pmax,
+                                                      int split_min, int parts, float* __restrict__ out) {
+  const int b = (int)blockIdx.y;
+  const int i = (int)((blockIdx.x * 256 + threadIdx.x) >> 5);  // (row, h)
+  if (i >= R * H) return;
   const int d = 4 * (int)(threadIdx.x & 31);
-  const int h = (int)(i % H), qr = (int)(i / H % R), b = (int)(i / H / R);
+  const int h = i % H, qr = i / H;
+  if (prefix_blocks(clamp_len(prefix_len[b], Pmax)) < split_min) return;
   const int64_t row0 = (int64_t)(b * H + h) * parts * R + qr;
   float2 ml[kMost];
   floatx4 o[kMost];
@@ -398,30 +407,48 @@ __global__ void __launch_bounds__(256) k_tree_merge(const float2* __restrict__ p
     acc += w * o[s];
   }
   acc *= qr < num_nodes[b] && l > 0.0f ? 1.0f / l : 0.0f;
-  *(floatx4*)(out + i * kD + d) = acc;
+  *(floatx4*)(out + ((int64_t)b * R * H + i) * kD + d) = acc;
 }
 
-// Workgroups per (tree, head): 1, or parts - 1 for the prefix and one for the
-// tree's rows.  A workgroup walks its prefix at about 1 us per block of 32
-// keys (a chain of LDS reads, products and a softmax step), so with few
-// (tree, head) pairs most of the chip idles while that chain runs.  Parts
-// are added up to a workgroup per CU: past that, two share a CU and gain
-// nothing (1 tree x 32 heads, 3,000 keys: 92 us in one part, 50 in 3, 31 in
-// 5, 24.7 in 8, 35 in 10).  Three parts still pay while the workgroups are all
-// resident, two per CU (128 pairs, 2,048 keys: 71 -> 49 us; 160 pairs, 773
-// keys: 28.9 -> 25.9), and no longer at 256 pairs (73 -> 87).  A part takes two
-// blocks or more, and a prefix under 8 blocks stays whole: the merge costs
-// about 4 us.
+// How a call splits: workgroups per (tree, head) - 1, or `parts` - 1 for the
+// prefix and one for the tree's rows - and the blocks from which a prefix is
+// cut.  A workgroup walks its prefix at about 1 us per block of 32 keys (a
+// chain of LDS reads, products and a softmax step), so with few (tree, head)
+// pairs most of the chip idles while that chain runs; against it stand the
+// parts' rows written and read again, which grow with the tree's rows.
+// Measured against one part (us, two figures: one part -> split):
+//  - up to a workgroup per CU in all (85 pairs): 1 tree x 32 heads, 65 rows:
+//    3,000 keys 92 -> 24.7 in 8 parts (50 in 3, 31 in 5, 35 in 10), 320 keys
+//    19.8 -> 17.8, 192 keys 16.4 -> 17.5; 129 rows: 512 keys 36.0 -> 33.8, 320
+//    keys 29.7 -> 32.2; 256 rows: 384 keys 66.5 -> 65.2.
+//  - 86 to 128 pairs, in three parts: the prefixes have a CU per workgroup, the
+//    trees share one.  128 pairs, 65 rows: 2,048 keys 70.9 -> 50.9, 768 keys 34.8
+//    -> 32.6, 512 keys 28.1 -> 29.1; 17 rows: 512 keys 18.9 -> 14.9; 256 rows:
+//    1,536 keys 118 -> 110, 1,024 keys 96.5 -> 97.8.
+//  - 129 to 170 pairs, in three parts: the prefixes share CUs too, and only
+//    trees of up to 64 rows (four waves) gain.  160 pairs, 49 rows: 1,024 keys
+//    33.1 -> 29.2, 512 keys 22.2 -> 21.1; 65 rows: 39.5 -> 45.6 and 4,096 keys
+//    131.5 -> 132.3.
+// With more, 256 pairs 73 -> 87.  A call is launched in parts where its buffer
+// could hold a prefix long enough, and each tree is cut by its own prefix: the
+// lengths are on the device.  A tree left whole there takes 1 to 2 us more than
+// in a call of one part (the merge's launch): 32 pairs, 65 rows, no prefix 10.7
+// -> 11.8.
 constexpr int kCus = 256;
 constexpr int kMaxParts = 16;
-int part_count(int32_t B, int32_t H, int32_t Pmax) {
+struct Split {
+  int parts, min_blocks;
+};
+Split split_of(int32_t B, int32_t R, int32_t H, int32_t Pmax) {
   const int64_t wgs = (int64_t)B * H, blocks = ((int64_t)Pmax + kBlock - 1) / kBlock;
-  if (3 * wgs > 2 * kCus || blocks < 8) return 1;
-  int64_t parts = kCus / wgs;
-  if (parts < 3) parts = 3;
+  const bool fits = 3 * wgs <= kCus;  // a workgroup per CU in three parts
+  const int least = fits ? (R < 32 ? 6 : R < 128 ? 4 + R / 16 : 12) : 16 + R / 10;
+  if (blocks < least) return {1, 0};
+  if (!fits && 2 * wgs > kCus && (R > 64 || 3 * wgs > 2 * kCus)) return {1, 0};
+  int64_t parts = fits ? kCus / wgs : 3;
   if (parts > kMaxParts) parts = kMaxParts;
-  if (parts > blocks / 2 + 1) parts = blocks / 2 + 1;
-  return (int)parts;
+  if (parts > blocks / 2 + 1) parts = blocks / 2 + 1;  // two blocks or more each
+  return {(int)parts, least};
 }
 
 size_t carve_parts(void* p, int32_t B, int32_t R, int32_t H, int parts, float2** ml, float** o) {
@@ -436,7 +463,7 @@ size_t carve_parts(void* p, int32_t B, int32_t R, int32_t H, int parts, float2**
 
 extern "C" size_t fc_tree_attention_workspace_bytes(int32_t B, int32_t R, int32_t H, int32_t Pmax) {
   if (B < 1 || R < 1 || R > FC_MAX_TREE_ROWS || H < 1 || Pmax < 0) return 0;
-  const int parts = part_count(B, H, Pmax);
+  const int parts = split_of(B, R, H, Pmax).parts;
   float2* ml;
   float* o;
   return parts > 1 ? carve_parts(nullptr, B, R, H, parts, &ml, &o) : 0;
@@ -469,7 +496,8 @@ extern "C" fc_status fc_tree_attention_ws(const uint16_t* q, const uint16_t* k_t
   if ((int64_t)Pmax * Hkv * D * 2 >= (int64_t)1 << 32) return FC_ERR_UNSUPPORTED;
   const int rows_waves = (R + 15) / 16;
   const int waves = rows_waves < 4 ? 4 : rows_waves;  // at least 256 threads stage a block
-  int parts = part_count(B, H, Pmax);
+  const Split sp = split_of(B, R, H, Pmax);
+  int parts = sp.parts;
   float2* ml = nullptr;
   float* po = nullptr;
   if (parts > 1) {
@@ -484,7 +512,7 @@ extern "C" fc_status fc_tree_attention_ws(const uint16_t* q, const uint16_t* k_t
   (void)hipGetLastError();
 #define FC_ATTN(T, SPLIT)                                                                                              \
   hipLaunchKernelGGL((k_tree_attn<T, SPLIT>), grid, block, 0, stream, q, k_tree, v_tree, k_cache, v_cache, prefix_len, \
-                     num_nodes, mask, pos_ids, B, R, H, Hkv, Pmax, log2((double)rope_base), out, ml, po)
+                     num_nodes, mask, pos_ids, B, R, H, Hkv, Pmax, sp.min_blocks, log2((double)rope_base), out, ml, po)
   // trees of up to 128 rows (c <= 127) in workgroups of at most 8 waves,
   // which leaves each lane the registers the accumulators need
   if (waves <= 8 && parts == 1) FC_ATTN(512, false);
@@ -494,14 +522,16 @@ extern "C" fc_status fc_tree_attention_ws(const uint16_t* q, const uint16_t* k_t
 #undef FC_ATTN
   FC_CHECK_LAUNCH();
   if (parts > 1) {
-    const dim3 mgrid(fc::div_up((uint64_t)B * R * H * 32, 256));
+    auto merge = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(fc::div_up((uint64_t)R * H * 32, 256), B), dim3(256), 0, stream, ml, po,
+                         prefix_len, num_nodes, R, H, Pmax, sp.min_blocks, parts, out);
+    };
     if (parts <= 4)
-      hipLaunchKernelGGL(k_tree_merge<4>, mgrid, dim3(256), 0, stream, ml, po, num_nodes, B, R, H, parts, out);
+      merge(k_tree_merge<4>);
     else if (parts <= 8)
-      hipLaunchKernelGGL(k_tree_merge<8>, mgrid, dim3(256), 0, stream, ml, po, num_nodes, B, R, H, parts, out);
+      merge(k_tree_merge<8>);
     else
-      hipLaunchKernelGGL(k_tree_merge<kMaxParts>, mgrid, dim3(256), 0, stream, ml, po, num_nodes, B, R, H, parts,
-                         out);
+      merge(k_tree_merge<kMaxParts>);
     FC_CHECK_LAUNCH();
   }
   return FC_OK;

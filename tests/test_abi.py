@@ -317,3 +317,16 @@ def test_struct_layouts_match_header(tmp_path):
         assert got[(name, "sizeof")] == ctypes.sizeof(cls), name
         for f, _ in cls._fields_:
             assert got[(name, f)] == getattr(cls, f).offset, (name, f)
+
+
+@pytest.mark.parametrize("B,R,H,Pmax,parts", [
+    (1, 65, 32, 8192, 8), (1, 65, 32, 224, 1), (1, 65, 32, 256, 5), (1, 17, 8, 160, 1), (1, 129, 32, 352, 1),
+    (1, 129, 32, 384, 7), (4, 65, 32, 673, 3), (4, 65, 32, 672, 1), (4, 64, 40, 4096, 3), (4, 65, 40, 4096, 1),
+    (171, 16, 1, 4096, 1), (170, 16, 1, 4096, 3),
+])
+def test_tree_attention_is_split_where_that_pays(B, R, H, Pmax, parts):
+    """Scratch is asked for where prefixes are long enough for the rows they
+    leave, and where the parts have compute units to run on."""
+    need = fc.fc_tree_attention_workspace_bytes(B, R, H, Pmax)
+    row = (fc.FC_TREE_ATTN_HEAD_DIM + 2) * 4
+    assert need == 0 if parts == 1 else 0 <= need - B * H * R * parts * row < 1024

@@ -1318,3 +1318,34 @@ def test_tree_attention_on_another_stream():
         fc.fc_tree_attention(q, kt, vt, kc, vc, plen, tree, out=out, stream=side)
         torch.cuda.synchronize()
         assert (seen == i + 1).all() and torch.equal(out, want)
+
+
+@pytest.mark.parametrize("R,H,least", [(17, 8, 6), (65, 8, 8), (130, 8, 12), (40, 40, 20), (65, 30, 22)])
+def test_tree_attention_short_prefixes_stay_whole(R, H, least):
+    """Trees of one call whose prefixes hold fewer than `least` blocks of 32
+    keys are not split, whatever the buffer holds: their rows are bit for bit
+    those of one part, next to split ones (within 2^-8 max|v|, see above)."""
+    B, Hkv, D, Pmax = 4, 2, fc.FC_TREE_ATTN_HEAD_DIM, 1100
+    Pn = np.array([0, 32 * (least - 1), 32 * (least - 1) + 1, Pmax], np.int32)
+    say(f"short prefixes R={R} H={H}")
+    rng = np.random.default_rng(R)
+    q, kt, vt = (_bf16(rng, B, R, h, D).cuda() for h in (H, Hkv, Hkv))
+    kc, vc = (_bf16(rng, B, Pmax, Hkv, D).cuda() for _ in range(2))
+    tree = dict(num_nodes=dev(np.array([R, R - 1, R, R - 2], np.int32)),
+                mask=dev(np.tril(np.ones((B, R, R), np.int32))),
+                pos_ids=dev(np.tile(np.arange(R, dtype=np.int32) % 9, (B, 1))))
+    L, ptr = fc.lib(), fc._ptr
+    need = fc.fc_tree_attention_workspace_bytes(B, R, H, Pmax)
+    assert need > 0
+    ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")  # NaN in every word
+    out = torch.full((B, R, H, D), float("nan"), device="cuda")
+    fc.fc_tree_attention(q, kt, vt, kc, vc, dev(Pn), tree, out=out, workspace=ws)
+    one, plen = torch.empty_like(out), dev(Pn)
+    assert L.fc_tree_attention(*[ptr(x.view(torch.uint16)) for x in (q, kt, vt, kc, vc)], ptr(plen),
+                               *[ptr(tree[f]) for f in ("num_nodes", "mask", "pos_ids")], B, R, H, Hkv, D, Pmax,
+                               10000.0, ptr(one), fc._stream(None)) == 0
+    torch.cuda.synchronize()
+    out, one = host(out), host(one)
+    assert (out[:2] == one[:2]).all()
+    assert (out[2:] != one[2:]).any()
+    assert np.abs(out.astype(np.float64) - one).max() <= 2.0 ** -8 * float(vc.abs().max()) + 1e-5
