@@ -1171,16 +1171,21 @@ struct FlatLayout {
   size_t perm, lm, A, sstr, slen, sidx, sh_key, sh_w, total;
 };
 
-// Head bits (one 64-bit word per 64 merged positions and depth, positions
-// 0..T), at most kHeadWords words per depth.
+// Head bits: one 64-bit word per 64 merged positions and depth, positions
+// 0..T, at most kHeadWords words per depth.  They share the short strings'
+// room.  Where that has to grow for them (several store weights, rows of 16
+// tokens) and costs a resident workgroup, a large batch goes without: 1,024
+// queries of 6,000 strings of 16 tokens, weights 2 and 1, 458 us in two
+// workgroups per CU, 683 with head bits in one.
 constexpr int kHeadWords = 192;
 __host__ __device__ inline int head_words(int T) { return (T + 1 + 63) / 64; }
 __host__ __device__ inline bool flat_masks(int k) { return head_words(k) <= kHeadWords; }
 
 // maxm: the instantiation's row width (rows of maxm/2 32-bit words);
 // cap: short strings held; with_A: alpha prefix sums (stores of different
-// weights); S > 2: the short strings' merged order needs its own index.
-__host__ __device__ inline FlatLayout flat_layout(int k, int maxm, int cap, int S, bool with_A,
+// weights); with_heads: room for head bits; S > 2: the short strings' merged
+// order needs its own index.
+__host__ __device__ inline FlatLayout flat_layout(int k, int maxm, int cap, int S, bool with_A, bool with_heads,
                                                           int list = kFlatList) {
   FlatLayout t;
   size_t o = 0;
@@ -1192,7 +1197,7 @@ __host__ __device__ inline FlatLayout flat_layout(int k, int maxm, int cap, int 
   if (with_A) o = align_up(o + (size_t)(k + 1) * 4, 16);
   t.sstr = o;  // cap rows of maxm/2 words; later the head bits, then the kept tail nodes
   const size_t rows = (size_t)cap * maxm * 2, tails = (size_t)FC_MAX_TREE_ROWS * 4;
-  const size_t heads = flat_masks(k) ? (size_t)maxm * head_words(k) * 8 : 0;
+  const size_t heads = with_heads ? (size_t)maxm * (kHeadWords / 64 + head_words(k)) * 8 : 0;
   size_t region = rows > tails ? rows : tails;
   region = region > heads ? region : heads;
   o = align_up(o + region, 16);
@@ -1380,7 +1385,8 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
                                                             const uint8_t* __restrict__ cont_len,
                                                             const uint16_t* __restrict__ cont_tok,
                                                             const uint16_t* __restrict__ ctx, int L, int S, int k,
-                                                            int m, int c, Alpha alpha, int cap, int list, int words,
+                                                            int m, int c, Alpha alpha, int cap, int list,
+                                                            int with_heads, int words,
                                                             const int32_t* __restrict__ order, int self_plan, int B,
                                                             const int32_t* __restrict__ rows, int n_rows,
                                                             int32_t* __restrict__ num_nodes,
@@ -1412,7 +1418,6 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
   __shared__ int16_t s_end[FC_MAX_TREE_ROWS];
   __shared__ uint32_t s_pick[3];
   __shared__ uint32_t s_scan4[4 * NW];
-  __shared__ uint64_t s_nzw[MAXM][kHeadWords / 64];  // per depth: which head words are non-empty
   __shared__ int16_t s_runj[kFlatShortCap];  // first short string of a run: long strings before it (else -1)
   __shared__ uint8_t s_plcp[kFlatShortCap];  // and its LCP with the long string just before it
 
@@ -1549,7 +1554,7 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
     return;
   }
 
-  const FlatLayout lay = flat_layout(k, MAXM, cap, S, !NARROW, list);
+  const FlatLayout lay = flat_layout(k, MAXM, cap, S, !NARROW, with_heads != 0, list);
   uint16_t* perm = (uint16_t*)(smem + lay.perm);
   LMT* lm = (LMT*)(smem + lay.lm);
   uint32_t* A = (uint32_t*)(smem + lay.A);
@@ -1858,6 +1863,23 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
       ntail += li > lo_t ? (uint32_t)(li - lo_t) : 0u;
       l_after = l;
     }
+    // head bits, below: per depth, which of its words are non-empty, then the words
+    uint64_t* nz = (uint64_t*)(smem + lay.sstr);
+    uint64_t* heads = nz + MAXM * (kHeadWords / 64);
+    if (with_heads && tid < MAXM * (kHeadWords / 64)) nz[tid] = 0ull;  // before the scan's barriers
+    uint32_t a_ex, a_tot, n_tot, sh_ex, sh_tot;
+    {
+      const uint32_t v3[3] = {asum, nodes, nsh};
+      uint32_t ex3[3], tot3[3];
+      ScanK<NT, 3>::run(v3, rw, s_scan4, ex3, tot3, &root_w);
+      a_ex = ex3[0];
+      sh_ex = ex3[2];
+      a_tot = tot3[0];
+      n_tot = tot3[1];
+      sh_tot = tot3[2];
+    }
+    const bool listed = sh_tot <= (uint32_t)list;
+
     // Shared node (q, d) weighs what the strings from q to the next head of
     // depth d weigh (the next position whose LCP is below d, or T): alpha
     // times the distance with one store weight, else a difference of prefix
@@ -1866,13 +1888,10 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
     // of the chunk walk below ("direct").  A head word is built by one thread
     // from 64 packed (LCP, length), a 32-bit word of them at a time: with the
     // LCP in a field's low half, adding 2^kSh - d sets bit kSh exactly when
-    // LCP >= d.
+    // LCP >= d.  (Without a list the walk is taken, and no head bit is needed.)
     const int nwd = head_words(T);
-    const bool direct = flat_masks(k) && m <= MAXM;
-    uint64_t* heads = (uint64_t*)(smem + lay.sstr);
-    if (direct) {
-      if (tid < MAXM * (kHeadWords / 64)) (&s_nzw[0][0])[tid] = 0ull;
-      __syncthreads();
+    const bool direct = with_heads && listed;
+    if (direct) {  // (read after the barrier that follows the list's own writing)
       constexpr int kPerWord = 4 / (int)sizeof(LMT);  // positions per 32-bit word
       constexpr uint32_t kOnes = sizeof(LMT) == 1 ? 0x01010101u : 0x00010001u;
       for (int x = tid; x < m * nwd; x += NT) {
@@ -1897,21 +1916,9 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
         const int past = T - wd * 64;  // positions at or past T are heads
         if (past < 64) hb |= past <= 0 ? ~0ull : (~0ull << past);
         heads[(d - 1) * nwd + wd] = hb;
-        if (hb != 0ull) atomicOr((unsigned long long*)&s_nzw[d - 1][wd >> 6], 1ull << (wd & 63));
+        if (hb != 0ull) atomicOr((unsigned long long*)&nz[(d - 1) * (kHeadWords / 64) + (wd >> 6)], 1ull << (wd & 63));
       }
     }
-    uint32_t a_ex, a_tot, n_tot, sh_ex, sh_tot;
-    {
-      const uint32_t v3[3] = {asum, nodes, nsh};
-      uint32_t ex3[3], tot3[3];
-      ScanK<NT, 3>::run(v3, rw, s_scan4, ex3, tot3, &root_w);
-      a_ex = ex3[0];
-      sh_ex = ex3[2];
-      a_tot = tot3[0];
-      n_tot = tot3[1];
-      sh_tot = tot3[2];
-    }
-    const bool listed = sh_tot <= (uint32_t)list;
 
     // The walk's set-up, done once and only when a walk is needed: the next
     // head per depth after each chunk, and the alpha prefix sums of stores
@@ -2026,7 +2033,7 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
         rbig += Wt >= 256u ? n : 0u;
         if (Wt != 1u && Wt != 2u && Wt < 256u) atomicAdd(&s_hist[Wt], n);
       };
-      if (direct && listed) {
+      if (direct) {
         prepare_sums();
         uint32_t o = sh_ex;
         uint32_t x = p0 < p1 ? (uint32_t)lm[p0] : 0u;
@@ -2057,7 +2064,7 @@ __global__ void __launch_bounds__(NT_, NT_ == kFlatThreads && MAXM <= 10 ? 6 : 4
 #pragma unroll
             for (int c = kHeadWords / 64 - 1; c >= 0; --c) {
               const int lo_bit = c * 64;
-              uint64_t z = s_nzw[d - 1][c];
+              uint64_t z = nz[(d - 1) * (kHeadWords / 64) + c];
               if (j + 1 > lo_bit) z = (j + 1 - lo_bit) >= 64 ? 0ull : z & (~0ull << (j + 1 - lo_bit));
               if (z != 0ull) j2 = lo_bit + __builtin_ctzll(z);
             }
@@ -2512,9 +2519,10 @@ fc_status launch_fast(const int32_t* taken, const uint8_t* cont_len, const uint1
 
 // Entries of the list of shared nodes: a list of k strings of m tokens has at
 // most k m / 2 shared nodes, `room` bytes of LDS are there for the layout.
+constexpr int kCus = 256;
 constexpr size_t kLdsStep = 1280;  // LDS is allocated in pieces of this size
-int flat_list(int k, int m, int maxm, int cap, int S, bool with_A, size_t room) {
-  const size_t least = flat_layout(k, maxm, cap, S, with_A).total;
+int flat_list(int k, int m, int maxm, int cap, int S, bool with_A, bool with_heads, size_t room) {
+  const size_t least = flat_layout(k, maxm, cap, S, with_A, with_heads).total;
   if (least >= room) return kFlatList;
   const size_t most = (size_t)k * (size_t)m / 2, fit = kFlatList + (room - least) / (with_A ? 8 : 6);
   const size_t list = (most < fit ? most : fit) & ~(size_t)15;  // whole 16-byte pieces: no padding on top
@@ -2538,8 +2546,12 @@ fc_status launch_flat(const int32_t* taken, const uint8_t* cont_len, const uint1
   // LDS for every possible short list would cost occupancy for nothing (in
   // typical batches a second store's list holds a few strings)
   int cap = worst_short < kFlatShortCap ? worst_short : kFlatShortCap;
-  while (cap > 0 && flat_layout(k, MAXM, cap, S, !NARROW).total > budget) cap = cap * 7 / 8;
-  if (flat_layout(k, MAXM, cap, S, !NARROW).total > budget) return FC_ERR_UNSUPPORTED;
+  auto total = [&](bool heads, int list = kFlatList) {
+    return flat_layout(k, MAXM, cap, S, !NARROW, heads, list).total;
+  };
+  const bool always = NARROW && MAXM <= 15 && flat_masks(k);  // bytes of head bits fit where the rows did
+  while (cap > 0 && total(always) > budget) cap = cap * 7 / 8;
+  if (total(always) > budget) return FC_ERR_UNSUPPORTED;
   // with two stores a query's short list past the cap is searched in place;
   // with more, such queries go to the full-LDS kernel
   const bool defer = S > 2 && cap < worst_short;
@@ -2561,27 +2573,32 @@ fc_status launch_flat(const int32_t* taken, const uint8_t* cont_len, const uint1
   bool wide = false;
   if constexpr (MAXM == 10) {
     const size_t wstat = dv.wide_static[NARROW ? 1 : 0];
-    wide = !plan && B <= kFlatWideMaxB && flat_layout(k, MAXM, cap, S, !NARROW).total + wstat <= (size_t)dv.max_lds;
+    wide = !plan && B <= kFlatWideMaxB && total(always) + wstat <= (size_t)dv.max_lds;
     if (wide) {  // one per CU, by its registers
-      const int list = flat_list(k, m, MAXM, cap, S, !NARROW, (size_t)dv.max_lds - wstat);
-      hipLaunchKernelGGL((k_tree_flat<MAXM, NARROW, kFlatWide>), dim3(B), dim3(kFlatWide),
-                         flat_layout(k, MAXM, cap, S, !NARROW, list).total, stream, taken, cont_len, cont_tok, ctx, L,
-                         S, k, m, t.c, a, cap, list, words, nullptr, self_plan, B, rows, n_rows, num_nodes, node_tok,
-                         parent, weight, pos_ids, mask);
+      const bool heads = flat_masks(k) && total(true) + wstat <= (size_t)dv.max_lds;
+      const int list = flat_list(k, m, MAXM, cap, S, !NARROW, heads, (size_t)dv.max_lds - wstat);
+      hipLaunchKernelGGL((k_tree_flat<MAXM, NARROW, kFlatWide>), dim3(B), dim3(kFlatWide), total(heads, list), stream,
+                         taken, cont_len, cont_tok, ctx, L, S, k, m, t.c, a, cap, list, heads ? 1 : 0, words, nullptr,
+                         self_plan, B, rows, n_rows, num_nodes, node_tok, parent, weight, pos_ids, mask);
     }
   }
   if (!wide) {
     // as many workgroups per CU as its registers hold (three of up to 80, two
     // of up to 128) and their LDS without a longer list
-    const size_t one = flat_layout(k, MAXM, cap, S, !NARROW).total + stat;
-    size_t groups = MAXM == 10 ? 3 : 2;
-    while (groups > 1 && one > (size_t)dv.max_lds / groups) --groups;
-    const size_t share = (size_t)dv.max_lds / groups / kLdsStep * kLdsStep;
-    const int list = flat_list(k, m, MAXM, cap, S, !NARROW, share > stat ? share - stat : 0);
-    hipLaunchKernelGGL((k_tree_flat<MAXM, NARROW>), dim3(B), dim3(kFlatThreads),
-                       flat_layout(k, MAXM, cap, S, !NARROW, list).total, stream, taken, cont_len, cont_tok, ctx, L,
-                       S, k, m, t.c, a, cap, list, words, plan ? order : nullptr, self_plan, B, rows, n_rows,
-                       num_nodes, node_tok, parent, weight, pos_ids, mask);
+    auto resident = [&](bool heads) {
+      size_t groups = MAXM == 10 ? 3 : 2;
+      while (groups > 1 && total(heads) + stat > (size_t)dv.max_lds / groups) --groups;
+      return groups;
+    };
+    // a batch of up to a workgroup per CU loses nothing to a larger layout
+    const bool heads = always || (flat_masks(k) && total(true) <= budget &&
+                                  (B <= kCus || resident(true) == resident(false)));
+    const size_t share = (size_t)dv.max_lds / resident(heads) / kLdsStep * kLdsStep;
+    const int list = flat_list(k, m, MAXM, cap, S, !NARROW, heads, share > stat ? share - stat : 0);
+    hipLaunchKernelGGL((k_tree_flat<MAXM, NARROW>), dim3(B), dim3(kFlatThreads), total(heads, list), stream, taken,
+                       cont_len, cont_tok, ctx, L, S, k, m, t.c, a, cap, list, heads ? 1 : 0, words,
+                       plan ? order : nullptr, self_plan, B, rows, n_rows, num_nodes, node_tok, parent, weight, pos_ids,
+                       mask);
   }
   FC_CHECK_LAUNCH();
   if (defer) {

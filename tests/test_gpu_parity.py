@@ -682,21 +682,12 @@ def test_search_without_records(B, S, pairs):
     compare_retrieve(gpu_pipeline(stores, ctx, p, (1, 1, 1, 1)[:S], 16), oracle.retrieve(texts, ctx, **p))
 
 
-@pytest.mark.parametrize("m,alpha,B", [(10, (1, 1), 2), (10, (2, 1), 2), (10, (1, 1), 260), (10, (3, 1), 260),
-                                       (16, (1, 1), 2), (16, (1, 2), 2), (15, (2, 1), 2), (7, (0, 1), 2),
-                                       (16, (200, 7), 2), (10, (300, 300), 2)])
-def test_tree_node_weights(m, alpha, B):
-    """Tries with few to very many shared nodes (lists that fit in LDS, that
-    only fit in what it has left, and that do not fit), small and large W*,
-    and W* among the store weights, whatever the weights and the row width."""
-    say(f"tree node weights m={m} alpha={alpha} B={B}")
-    rng = np.random.default_rng(m * 100 + B)
-    k = 5000
+def _node_weight_case(rng, k, m, alpha, B):
     taken = np.zeros((B, 2), np.int32)
     lens, toks = np.zeros((B, k), np.uint8), np.zeros((B, k, m), np.uint16)
     # kept slots per store, vocabulary, chance that a token is the store's usual one, shortest row
-    shapes = [(4700, 300, 2, 0.5, m), (1500, 60, 3, 0.5, 0), (4990, 10, 500, 0.55, m), (900, 0, 4, 0.3, 1),
-              (40, 9, 900, 0.0, 0), (4000, 1000, 30, 0.85, m - 2), (3, 2, 50, 0.5, 0), (0, 5000, 12, 0.6, m)]
+    shapes = [(k - 300, 300, 2, 0.5, m), (1500, 60, 3, 0.5, 0), (k - 10, 10, 500, 0.55, m), (900, 0, 4, 0.3, 1),
+              (40, 9, 900, 0.0, 0), (4000, 1000, 30, 0.85, m - 2), (3, 2, 50, 0.5, 0), (0, k, 12, 0.6, m)]
     for b in range(B):
         n0, n1, v, usual, shortest = shapes[b % len(shapes)] if B > 2 else shapes[(2 * m + 5 * b) % len(shapes)]
         taken[b] = n0, n1
@@ -717,6 +708,27 @@ def test_tree_node_weights(m, alpha, B):
     rows = list(range(min(B, len(shapes))))
     o = oracle.build_tree(taken[rows], lens[rows], toks[rows], ctx[rows], c=64, alpha=alpha)
     compare_tree({f: host(x) for f, x in t.items()}, o, rows)
+
+
+@pytest.mark.parametrize("m,alpha,B", [(10, (1, 1), 2), (10, (2, 1), 2), (10, (1, 1), 260), (10, (3, 1), 260),
+                                       (16, (1, 1), 2), (16, (1, 2), 2), (15, (2, 1), 2), (7, (0, 1), 2),
+                                       (16, (200, 7), 2), (10, (300, 300), 2)])
+def test_tree_node_weights(m, alpha, B):
+    """Tries with few to very many shared nodes (lists that fit in LDS, that
+    only fit in what it has left, and that do not fit), small and large W*,
+    and W* among the store weights, whatever the weights and the row width."""
+    say(f"tree node weights m={m} alpha={alpha} B={B}")
+    _node_weight_case(np.random.default_rng(m * 100 + B), 5000, m, alpha, B)
+
+
+@pytest.mark.parametrize("k,m,alpha,B", [(5800, 16, (2, 1), 260), (6000, 16, (2, 1), 260), (6000, 16, (2, 1), 3),
+                                         (7100, 10, (2, 1), 260), (7400, 10, (2, 1), 260), (7400, 10, (2, 1), 3),
+                                         (8200, 16, (1, 1), 260), (12287, 16, (3, 1), 3), (12288, 11, (1, 1), 3)])
+def test_tree_node_weights_beside_the_head_bits_room(k, m, alpha, B):
+    """Either side of where head bits cost a resident workgroup (or no longer
+    fit), in batches that give them up for it and in ones that do not."""
+    say(f"tree head bits k={k} m={m} alpha={alpha} B={B}")
+    _node_weight_case(np.random.default_rng(k + B), k, m, alpha, B)
 
 
 def test_results_do_not_depend_on_batching():
