@@ -169,6 +169,19 @@ def _concat(parts):
     return np.concatenate([np.asarray(x, np.uint16) for x in parts]), off
 
 
+@pytest.mark.parametrize("empties", [0, 1, 63, 64, 65, 5000])
+def test_sa_batched_tiny_and_empty_stores(empties):
+    """Stores of 1 to 200 tokens, many within a wave's 64 positions, with runs
+    of empty ones between them, at the front and at the end."""
+    say(f"sa batched tiny stores, {empties} empty between")
+    r = np.random.default_rng(empties)
+    parts = []
+    for i in range(400):
+        parts += [np.zeros(0, np.uint16)] * (empties if i % 7 == 0 else i % 2)
+        parts.append(r.integers(0, 4, int(r.choice([1, 2, 3, 62, 63, 64, 65, 66, 200]))).astype(np.uint16))
+    _batched_case(*_concat(parts + [np.zeros(0, np.uint16)] * empties))
+
+
 @pytest.mark.parametrize("vocab", [2, 4, 32256])
 def test_sa_batched_ragged_stores(vocab):
     lens = [0, 1, 2, 3, 0, 7, 64, 4095, 4096, 4097, 0, 9000, 5]
