@@ -133,6 +133,32 @@ def test_sa_group_size_edges(sizes, vocab):
     _extend_case(t[:k], t[k:])
 
 
+@pytest.mark.parametrize("n", [2047, 2050, 4097, 20_000, 70_000, 300_001, 17_000_003])
+@pytest.mark.parametrize("period", [1, 2, 97])
+def test_sa_repeated_text_large_groups(n, period):
+    """Text of one repeated token, or few: groups of up to n suffixes whose
+    labels agree in one or more digits (two to four in all, an odd or an even
+    number of them), in every round for as long as the text repeats.  The
+    suffixes that start on one place of the period are in order of their
+    length, the shorter first."""
+    say(f"sa repeated text n={n} period={period}")
+    unit = np.random.default_rng(period).permutation(period).astype(np.uint16) + 3
+    t = np.tile(unit, n // period + 1)[:n]
+    want = []
+    for tok in range(3, 3 + period):  # each token is at one place of the period
+        at = int(np.nonzero(unit == tok)[0][0])
+        want.append(np.arange(at, n, period, dtype=np.uint32)[::-1])
+    g = host(fc.fc_datastore_build(dev(t)))
+    torch.cuda.synchronize()
+    assert (g == np.concatenate(want)).all()
+    if n <= 300_001:
+        _batched_case(*_concat([t, t[: n // 2], t[:2500]]), full=False)
+        x = np.concatenate([t[: n // 2], np.zeros(1, np.uint16)])
+        sa = fc.fc_datastore_extend(dev(np.concatenate([x, t])), len(x), fc.fc_datastore_build(dev(t)))
+        torch.cuda.synchronize()
+        assert oracle.check_sa(np.concatenate([x, t]), host(sa)) == (0, 0)
+
+
 def test_sa_large_texts_rank_pairs():
     """Stores of 64M suffixes or more take their ranks through sorted
     (suffix, rank) pairs instead of random writes: just past that size, with
