@@ -89,8 +89,9 @@ fc_status fc_datastore_build(const uint16_t* tokens, uint64_t n, uint32_t* sa_ou
  * round leaves none tied, so the longest common prefix of two suffixes is
  * below prefix_len[rounds - 1] and, when rounds > 1, at least
  * prefix_len[rounds - 2].  sort_passes counts the radix passes run over
- * global memory: one per byte of round 0's key, and one per byte of a rank in
- * a round that sorts groups too large for one workgroup.
+ * global memory: one per byte of round 0's key (one in all for a single
+ * suffix), and one per byte of a rank in a round that sorts groups too large
+ * for one workgroup.
  */
 #define FC_MAX_BUILD_ROUNDS 40
 typedef struct fc_build_stats {

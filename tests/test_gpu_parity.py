@@ -133,6 +133,15 @@ def test_sa_group_size_edges(sizes, vocab):
     _extend_case(t[:k], t[k:])
 
 
+def test_sa_lone_suffix_takes_one_pass():
+    say("sa lone suffix")
+    sa, stats = fc.fc_datastore_build_stats(dev(np.array([65535], np.uint16)))
+    assert host(sa).tolist() == [0] and stats["sort_passes"] == 1 and stats["unresolved"] == [0]
+    old = synth.random_text(77, 5000, 9)
+    for new in ([0], [3], [65535]):
+        _extend_case(np.array(new, np.uint16), old)
+
+
 @pytest.mark.parametrize("n", [2047, 2050, 4097, 20_000, 70_000, 300_001, 17_000_003])
 @pytest.mark.parametrize("period", [1, 2, 97])
 def test_sa_repeated_text_large_groups(n, period):
