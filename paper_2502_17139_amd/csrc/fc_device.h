@@ -122,13 +122,6 @@ __device__ __forceinline__ T wave_incl_max(T v) {
 }
 
 template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
-}
-
-template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) {

@@ -289,7 +289,7 @@ __device__ __forceinline__ void search_query(const StoreArgs& st, int S, const u
       const uint64_t ba = fc::ballot(searching && ca);
       const uint64_t bb = fc::ballot(searching && cb);
       if (searching) {
-        // the pivots before the bound form a prefix of the 2G - 1 pivots
+        // the pivots before the bound form a prefix of the P pivots
         const int c = __popcll((ba >> gbase) & gmask) + __popcll((bb >> gbase) & gmask);
         const uint64_t span = chi - clo;
         const uint32_t plo = c > 0 ? clo + (uint32_t)(((uint64_t)c * span) >> log2_p) + 1 : clo;
@@ -312,7 +312,7 @@ __device__ __forceinline__ void search_query(const StoreArgs& st, int S, const u
   __syncthreads();
 }
 
-// One query per workgroup: the 2G-ary search of every (store, n, bound),
+// One query per workgroup: the pivot search of every (store, n, bound),
 // then the kept ranges (the longest non-empty n per store, store priority
 // order) written to the query's row.
 template <int NT, bool kText>

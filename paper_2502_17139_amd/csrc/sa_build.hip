@@ -3,8 +3,9 @@
 // The datastore is indexed for exact suffix matching with a suffix array
 // (Section III-A, after Manber and Myers; datastore organisation in
 // Section IV-A).  Construction is prefix doubling, which is what Manber and
-// Myers' own construction does, with every round's sort done as an LSD radix
-// sort so it runs at HBM bandwidth:
+// Myers' own construction does: a first sort of all suffixes by passes over
+// whole lists, then sorts inside the groups that are still tied, most of them
+// in LDS:
 //
 //   round 0  key(i) = the first 3 tokens of suffix i, each as token+1 in as
 //            many bits as the largest token + 1 needs (at most 17), with 0
@@ -20,11 +21,12 @@
 //   nearly sequential addresses).
 //
 // Round 0's keys are sorted by a global digit histogram followed by one
-// "onesweep" pass per 8-bit digit (Adinets and Merrill 2022): a workgroup takes a tile of 4,096 keys (its tile id from an atomic ticket,
-// so tiles start in order), ranks them stably inside the tile with wave
-// ballots, publishes per-digit tile counts and resolves its global offsets by
-// decoupled look-back over the earlier tiles, stages the tile in LDS in digit
-// order, and writes it out in runs.  The later rounds sort inside the groups
+// "onesweep" pass per 8-bit digit (Adinets and Merrill 2022): a workgroup takes
+// a tile of 4,096 keys (its tile id from an atomic ticket, so tiles start in
+// order), ranks them stably inside the tile with wave ballots, publishes
+// per-digit tile counts and resolves its global offsets by decoupled look-back
+// over the earlier tiles, stages the tile in LDS in digit order, and writes it
+// out in runs.  The later rounds sort inside the groups
 // (see "sorting inside groups").
 //
 // After each sort, head flags of the new and old groups are turned into
@@ -771,7 +773,11 @@ constexpr int kWin = 2048;          // list positions whose groups a workgroup s
 constexpr int kCap = 2 * kWin;      // a window's last group may end this far
 constexpr int kSmallThreads = 256;
 constexpr int kSmallItems = kCap / kSmallThreads;
-constexpr uint32_t kCountMax = 48;  // groups up to this size are ranked by comparing all pairs
+// Groups up to this size are ranked by comparing all pairs.  Builds of 1B
+// tokens (ms), 10M and 64 repositories (us): 24: 176.0, 2,471, 5,126; 32: 176.2,
+// 2,491, 5,163; 48: 171.0, 2,441, 5,004; 64: 171.8, 2,471, 5,066; 96: 173.3, 2,538,
+// 5,177.
+constexpr uint32_t kCountMax = 48;
 constexpr int kMaxLoDigits = 4;
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 
@@ -1605,8 +1611,9 @@ __global__ void __launch_bounds__(kSegThreads) k_seg_apply(Sorted<kRound0> in, c
 }
 
 // Bucket blockIdx.x % buckets (its elements: cursor[bucket]) into its windows,
-// tile after tile; the workgroups of one bucket are on one XCD, whose L2 puts
-// a window's lines together.
+// tile after tile.  (Workgroups are dealt to the eight XCDs in turn, so a
+// bucket's are on one XCD, and share its L2, only where the number of buckets is
+// a multiple of eight; at 1B suffixes there are 239.)
 constexpr int kSplitThreads = 512;
 constexpr int kSplitItems = 16;
 constexpr uint32_t kSplitTile = kSplitThreads * kSplitItems;
@@ -1866,9 +1873,8 @@ __global__ void __launch_bounds__(256) k_pairs_sampled(PairKeys pk, uint32_t* __
 // record's own 64 bytes of text (at the text's 2-byte alignment) and a wave's
 // store covers 1 KB of consecutive records.  Each thread takes kRecRun
 // pieces, their loads issued together; pieces that leave the text are read
-// token by token, 0 past the end.  Bound by the random lines read (about 1.5
-// of 128 bytes a record) next to the 64 bytes written: 100M records 3.52 ms,
-// 7.2 TB/s of both (4.30 with a record per lane, where every load and store
+// token by token, 0 past the end.  Bound by random lines of the text: 100M
+// records 3.52 ms (4.30 with a record per lane, where every load and store
 // touched 64 places; stores marked non-temporal: no change).
 constexpr int kRecRun = 4;
 constexpr uint32_t kRecBlock = 64 * kRecRun;  // records per workgroup

@@ -169,11 +169,11 @@ def test_sa_repeated_text_large_groups(n, period):
 
 
 def test_sa_large_texts_rank_pairs():
-    """Stores of 64M suffixes or more take their ranks through sorted
-    (suffix, rank) pairs instead of random writes: just past that size, with
-    a ragged last tile, a near-periodic text (about 25 doubling rounds,
-    nearly every rank rewritten in each) and a 4-token random text, each
-    checked by the linear-time checker."""
+    """Stores of 64M suffixes or more take their ranks through (suffix, rank)
+    pairs, split into windows of the rank array, instead of random writes:
+    just past that size, with a ragged last tile, a near-periodic text (about
+    25 doubling rounds, nearly every rank rewritten in each) and a 4-token
+    random text, each checked by the linear-time checker."""
     n = (1 << 26) + 4097
     periodic = np.tile(np.array([5, 9, 5, 9, 1], np.uint16), n // 5 + 1)[:n].copy()
     periodic[n // 3] = 7  # one break, so two long runs of the period
@@ -1409,3 +1409,36 @@ def test_tree_attention_short_prefixes_stay_whole(R, H, least):
     assert (out[:2] == one[:2]).all()
     assert (out[2:] != one[2:]).any()
     assert np.abs(out.astype(np.float64) - one).max() <= 2.0 ** -8 * float(vc.abs().max()) + 1e-5
+
+
+@pytest.mark.parametrize("given", [False, True])
+def test_tree_attention_in_a_captured_graph(given):
+    """The split call captured, with its own scratch (from the graph's pool) or
+    the caller's: every replay, on new inputs and with other work between,
+    gives the eager result."""
+    B, R, H, Hkv, D, Pn = 2, 33, 16, 4, fc.FC_TREE_ATTN_HEAD_DIM, 900
+    rng = np.random.default_rng(12)
+    new = lambda h, n: _bf16(rng, B, n, h, D).cuda()  # noqa: E731
+    q, kt, vt, kc, vc = new(H, R), new(Hkv, R), new(Hkv, R), new(Hkv, Pn), new(Hkv, Pn)
+    tree = dict(num_nodes=dev(np.array([R, R - 4], np.int32)), mask=dev(np.tril(np.ones((B, R, R), np.int32))),
+                pos_ids=dev(np.tile(np.arange(R, dtype=np.int32) % 7, (B, 1))))
+    plen = dev(np.array([Pn, 40], np.int32))
+    need = fc.fc_tree_attention_workspace_bytes(B, R, H, Pn)
+    assert need > 0
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda") if given else None
+    out = torch.empty((B, R, H, D), device="cuda")
+    say(f"attention captured, workspace given={given}")
+    fc.fc_tree_attention(q, kt, vt, kc, vc, plen, tree, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fc.fc_tree_attention(q, kt, vt, kc, vc, plen, tree, out=out, workspace=ws)
+    for i in range(4):
+        q.copy_(new(H, R))
+        plen.copy_(dev(np.array([Pn - 200 * i, 40 + 250 * i], np.int32)))
+        out.fill_(float("nan"))
+        graph.replay()
+        busy = torch.full((need,), 255, dtype=torch.uint8, device="cuda")  # eager work between, of the scratch's size
+        torch.cuda.synchronize()
+        assert torch.equal(out, fc.fc_tree_attention(q, kt, vt, kc, vc, plen, tree)), i
+        del busy
