@@ -2168,10 +2168,12 @@ fc_status build_sa(const uint16_t* tokens, uint64_t n, uint32_t n_seg, BuildWs& 
     // the large groups
     cur ^= 1;
     nr.h = h;
-    FC_CHECK_HIP(hipMemsetAsync(L.big.count, 0, sizeof(uint32_t) * kBigCounts, stream));
-    hipLaunchKernelGGL(k_sort_small<M>, dim3(fc::div_up(U, kWin)), dim3(kSmallThreads), 0, stream, L.grp[cur],
-                       L.val[cur], L.lo, w.misc + 1, nr, lo_digits, L.big.first_head, L.big.start, L.big.count);
-    FC_CHECK_LAUNCH();
+    if (U > 1) {  // a lone suffix is tied with none (a one-token store: 101 us before the group sorts, 83 now)
+      FC_CHECK_HIP(hipMemsetAsync(L.big.count, 0, sizeof(uint32_t) * kBigCounts, stream));
+      hipLaunchKernelGGL(k_sort_small<M>, dim3(fc::div_up(U, kWin)), dim3(kSmallThreads), 0, stream, L.grp[cur],
+                         L.val[cur], L.lo, w.misc + 1, nr, lo_digits, L.big.first_head, L.big.start, L.big.count);
+      FC_CHECK_LAUNCH();
+    }
     uint32_t host_misc[3] = {0, 0, 0};
     FC_CHECK_HIP(hipMemcpyAsync(host_misc, w.misc, sizeof(uint32_t) * 3, hipMemcpyDeviceToHost, stream));
     FC_CHECK_HIP(hipStreamSynchronize(stream));
